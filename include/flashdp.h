@@ -36,8 +36,9 @@
  *   - dtype: FLASHDP_BF16 / FLASHDP_F16 / FLASHDP_F32 is the storage type of X and dY; products are
  *     accumulated in fp32; out_grad and out_norms are fp32.
  *   - Pointers must be 16-byte aligned.  Any positive B, T, d_in, d_out is accepted; the
- *     matrix-core path needs d_in and d_out to be multiples of 8 (16-bit types), other shapes
- *     take a slower generic kernel.
+ *     fastest kernels need d_in and d_out to be multiples of 8 (16-bit types) or 4 (fp32); other sizes run on the
+ *     matrix cores at about half that rate, rows of less than 8 (4) elements and very small layers on the
+ *     vector ALUs.
  *   - NaN/Inf in the inputs propagate to out_norms / out_grad: a sample with a NaN norm gets a NaN clip
  *     factor and so turns the whole of out_grad into NaN (it is never let through unclipped).
  *     A per-sample gradient that overflows fp32 (infinite norm) poisons out_grad with NaN/Inf under every
@@ -55,7 +56,7 @@
  *   FLASHDP_TILE = 2 | 3 | 4 | 6 | 7 | 8 forces the matrix-core kernel (256x256 with 64-deep k-tiles, 128x128,
  *                                256x256 with 32-deep k-tiles - these three stage tiles through registers -,
  *                                256x256, 384x192, 192x384 with 32-deep k-tiles loaded straight into LDS);
- *                                -1 sends fp32 inputs to the generic kernel;
+ *                                -1 sends fp32 inputs and sizes that are no multiples of 8 to the generic kernel;
  *   FLASHDP_OVERLAP_GRID = n     workgroups of the aggregation kernel in the overlapped schedule (default: one per
  *                                compute unit).
  */

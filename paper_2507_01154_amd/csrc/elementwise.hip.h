@@ -79,20 +79,22 @@ __device__ __forceinline__ void widen8(const u32x4_t v, float* f) {
 
 // out[e] = sum_i c_i * scratch[i][e] + noise_scale * z[e], 8 consecutive elements per thread
 // (16-byte loads from the 16-bit scratch, two Philox groups, two 16-byte stores).  n8 = S / 8.
+// ANY: S is no multiple of 8, n8 = ceil(S / 8): samples after the first start at any even address, and the last thread's
+// group reaches past the end (its missing elements are neither loaded nor stored).
 // DEEP: four samples' loads in flight per thread (the kernels that have the chip to themselves); otherwise one, which
 // keeps the kernel within the registers left over beside a resident contraction workgroup (the overlapped schedule).
-template <int DT, bool DEEP>
+template <int DT, bool DEEP, bool ANY = false>
 __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch, const float* __restrict__ factors, int B,
                                                 size_t S, size_t v, float noise_scale, uint64_t seed, uint32_t layer,
                                                 float* __restrict__ out, int accumulate);
 
-template <int DT>
+template <int DT, bool ANY>
 __global__ __launch_bounds__(256) void aggregate16_kernel(const void* __restrict__ scratch, const float* __restrict__ factors,
                                                           int B, size_t S, size_t n8, float noise_scale, uint64_t seed,
                                                           uint32_t layer, float* __restrict__ out, int accumulate) {
   const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (v >= n8) return;
-  aggregate16_one<DT, true>(scratch, factors, B, S, v, noise_scale, seed, layer, out, accumulate);
+  aggregate16_one<DT, true, ANY>(scratch, factors, B, S, v, noise_scale, seed, layer, out, accumulate);
 }
 
 // The same work with a fixed, small number of workgroups striding over the elements: the form that runs on
@@ -124,20 +126,45 @@ __global__ __launch_bounds__(256) void clip_aggregate16_kernel(const void* __res
     aggregate16_one<DT, DEEP>(scratch, fac, B, S, v, noise_scale, seed, layer, out, accumulate);
 }
 
-template <int DT, bool DEEP>
+// The same for S no multiple of 8.
+template <int DT>
+__global__ __launch_bounds__(256) void clip_aggregate16_any_kernel(const void* __restrict__ scratch, const float* __restrict__ partials,
+                                                                   int tiles, float C, float* __restrict__ out_norms, int B, size_t S,
+                                                                   size_t n8, float noise_scale, uint64_t seed, uint32_t layer,
+                                                                   float* __restrict__ out, int accumulate) {
+  __shared__ float fac[MAX_FUSED_CLIP_B];
+  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms);
+  const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (v < n8) aggregate16_one<DT, true, true>(scratch, fac, B, S, v, noise_scale, seed, layer, out, accumulate);
+}
+
+template <int DT, bool DEEP, bool ANY>
 __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch, const float* __restrict__ factors, int B,
                                                 size_t S, size_t v, float noise_scale, uint64_t seed, uint32_t layer,
                                                 float* __restrict__ out, int accumulate) {
   float acc[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  if (accumulate) {   // gradient accumulation: continue from the sum of the earlier micro-batches
+  const int n_el = ANY && S - 8 * v < 8 ? (int)(S - 8 * v) : 8;   // elements of this group that exist
+  if (ANY && n_el < 8) {
+    if (accumulate)
+      for (int q = 0; q < n_el; ++q) acc[q] = out[8 * v + q];
+  } else if (accumulate) {   // gradient accumulation: continue from the sum of the earlier micro-batches
     const float4 o0 = ((const float4*)out)[2 * v], o1 = ((const float4*)out)[2 * v + 1];
     acc[0] = o0.x; acc[1] = o0.y; acc[2] = o0.z; acc[3] = o0.w;
     acc[4] = o1.x; acc[5] = o1.y; acc[6] = o1.z; acc[7] = o1.w;
   }
-  const u32x4_t* src = (const u32x4_t*)scratch + v;
-  const size_t stride = S / 8;
+  auto load8 = [&](int i) -> u32x4_t {
+    if constexpr (ANY) {
+      const unsigned short* p = (const unsigned short*)scratch + (size_t)i * S + 8 * v;
+      if (n_el == 8) return *(const u32x4_any_t*)p;
+      u32x4_t r = {0, 0, 0, 0};
+      for (int q = 0; q < n_el; ++q) r[q >> 1] |= (uint32_t)p[q] << (16 * (q & 1));
+      return r;
+    } else {
+      return __builtin_nontemporal_load((const u32x4_t*)scratch + v + (size_t)i * (S / 8));
+    }
+  };
   Normals4 z0 = {}, z1 = {};
   if constexpr (DEEP) {
     // Four samples' loads are issued before the first is used (64 bytes in flight per thread), and the noise, which
@@ -146,7 +173,7 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
     const int first = B < 4 ? B : 4;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (q < first) raw[q] = __builtin_nontemporal_load(src + (size_t)q * stride);
+      if (q < first) raw[q] = load8(q);
     if (noise_scale != 0.0f) {
       z0 = noise_group(seed, layer, 2 * v);
       z1 = noise_group(seed, layer, 2 * v + 1);
@@ -160,7 +187,7 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
       const int nn = B - i - n < 4 ? B - i - n : 4;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (q < nn) raw[q] = __builtin_nontemporal_load(src + (size_t)(i + n + q) * stride);
+        if (q < nn) raw[q] = load8(i + n + q);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (q < n) {
@@ -175,7 +202,7 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
     }
   } else {
     for (int i = 0; i < B; ++i) {
-      const u32x4_t raw = __builtin_nontemporal_load(src + (size_t)i * stride);
+      const u32x4_t raw = load8(i);
       const float c = factors[i];
       float f[8];
       widen8<DT>(raw, f);
@@ -194,52 +221,15 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
       acc[4 + q] = fmaf(noise_scale, z1.z[q], acc[4 + q]);
     }
   }
+  if (ANY && n_el < 8) {
+    for (int q = 0; q < n_el; ++q) out[8 * v + q] = acc[q];
+    return;
+  }
   typedef float f32x4_t __attribute__((ext_vector_type(4)));
   f32x4_t* dst = (f32x4_t*)out + 2 * v;
   const f32x4_t lo = {acc[0], acc[1], acc[2], acc[3]}, hi = {acc[4], acc[5], acc[6], acc[7]};
   __builtin_nontemporal_store(lo, dst);
   __builtin_nontemporal_store(hi, dst + 1);
-}
-
-// Generic version: any scratch type, any S; one Philox group (4 elements) per thread.
-template <int DT>
-__global__ __launch_bounds__(256) void aggregate_generic_kernel(const void* __restrict__ scratch, const float* __restrict__ factors,
-                                                                int B, size_t S, float noise_scale, uint64_t seed,
-                                                                uint32_t layer, float* __restrict__ out, int accumulate) {
-  const size_t g = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (4 * g >= S) return;
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (accumulate) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (4 * g + q < S) acc[q] = out[4 * g + q];
-  }
-  for (int i = 0; i < B; ++i) {
-    const float c = factors[i];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const size_t e = 4 * g + q;
-      if (e < S) {
-        float val;
-        if constexpr (DT == DT_F32) {
-          val = ((const float*)scratch)[(size_t)i * S + e];
-        } else if constexpr (DT == DT_BF16) {
-          val = __builtin_bit_cast(float, (uint32_t)((const unsigned short*)scratch)[(size_t)i * S + e] << 16);
-        } else {
-          val = (float)((const _Float16*)scratch)[(size_t)i * S + e];
-        }
-        acc[q] = fmaf(c, val, acc[q]);
-      }
-    }
-  }
-  if (noise_scale != 0.0f) {
-    const Normals4 z = noise_group(seed, layer, g);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] = fmaf(noise_scale, z.z[q], acc[q]);
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (4 * g + q < S) out[4 * g + q] = acc[q];
 }
 
 // ---- the explicit four-stage flow of Appendix B.2 on a materialised fp32 G[B][S] (measured comparison) ----
@@ -294,7 +284,7 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
   const size_t e = g4 * 4;
   if (e >= S) return;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  const bool vec = e + 3 < S && (S & 3) == 0;
+  const bool vec = e + 3 < S;   // with S no multiple of 4 the samples start at any 4-byte address, which the loads allow
   if (accumulate) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -304,8 +294,7 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
     const float* g = G + (size_t)i * S + e;
     const float c = factors ? factors[i] : 1.0f;
     if (vec) {
-      typedef float f32x4_t __attribute__((ext_vector_type(4)));
-      const f32x4_t v = __builtin_nontemporal_load((const f32x4_t*)g);
+      const f32x4_any_t v = __builtin_nontemporal_load((const f32x4_any_t*)g);
       acc[0] = fmaf(c, v.x, acc[0]); acc[1] = fmaf(c, v.y, acc[1]); acc[2] = fmaf(c, v.z, acc[2]); acc[3] = fmaf(c, v.w, acc[3]);
     } else {
 #pragma unroll

@@ -103,6 +103,7 @@ struct Plan {
   Path accum_path;   // batch-accumulating pass (second pass of the two-pass schedule, plain gradient)
   int bm, bn;
   int tiles_m, tiles_n;
+  bool any;          // rows that are no multiple of 16 bytes: the instantiation with 2- resp. 4-byte aligned accesses
   int accum_tiles_m, accum_tiles_n;   // the accumulating pass has one workgroup per tile (not per sample and tile)
 };
 
@@ -165,9 +166,28 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   const bool mfma_ok = dtype != FLASHDP_F32 && P % 8 == 0 && D % 8 == 0 &&
                        (T + 320) * (P > D ? P : D) * 2 < (int64_t(1) << 31);   // incl. the parked prefetches past the end
   // fp32 inputs: fp32 matrix-core kernel when rows are 16-byte multiples and the problem spans a few tiles
-  const bool f32_ok = dtype == FLASHDP_F32 && P % 4 == 0 && D % 4 == 0 && P * D >= 128 * 128 &&
+  // Features that are no multiple of 4: the same kernel in its unaligned form where its 256x256 tiles are at most half
+  // padding and the generic kernel's 64x64 ones would already fill half the chip (measured, fp32: 5 x 1097 x 2313,
+  // T = 333: 123 us against 267; 2 x 2000 x 77, T = 2048 - 128 tiles -: 493 against 814; 2 x 515 x 129 - 54 tiles -:
+  // 60 against 39, stays with the generic one).
+  auto padded = [&](int64_t b) { return (P + b - 1) / b * b * ((D + b - 1) / b * b); };
+  const bool f32_any = P >= 4 && D >= 4 && padded(256) <= 2 * padded(64) && padded(64) / 4096 * B >= 128;
+  const bool f32_ok = dtype == FLASHDP_F32 && ((P % 4 == 0 && D % 4 == 0) || f32_any) && P * D >= 128 * 128 &&
                       (T + 48) * (P > D ? P : D) * 4 < (int64_t(1) << 31) && env().tile != -1;
-  if (f32_ok) {
+  // 16-bit inputs of other sizes: the register-staged kernels with 2-byte aligned accesses.  Bound by the rate of the
+  // staged main loop (about 0.6 of the direct-to-LDS one); the generic kernel on the vector ALUs is 2 to 17 times slower
+  // (768 x 50257, B = 2, T = 1024: 287 us against 2800; 130 x 257, B = 8, T = 64: 16 against 32) and is kept for rows
+  // shorter than one 16-byte access and for problems of a single small tile, where it is all launch cost (33 x 35,
+  // B = 4, T = 16: 11 us against 13).
+  const bool any16_ok = dtype != FLASHDP_F32 && (P % 8 != 0 || D % 8 != 0) && P >= 8 && D >= 8 && env().tile != -1 &&
+                        !(P <= 64 && D <= 64 && T <= 32);
+  p.any = any16_ok || (f32_ok && (P % 4 != 0 || D % 4 != 0));
+  if (any16_ok) {
+    const int64_t tiles = ((D + 255) / 256) * ((P + 255) / 256);
+    p.path = tiles * B >= 128 ? PATH_256x8k32 : PATH_128x4;
+    p.accum_path = tiles >= 128 ? p.path : PATH_128x4;
+    p.bm = p.bn = p.path == PATH_128x4 ? 128 : 256;
+  } else if (f32_ok) {
     p.path = p.accum_path = PATH_F32; p.bm = p.bn = 256;
   } else if (!mfma_ok) {
     p.path = p.accum_path = PATH_SIMPLE; p.bm = 64; p.bn = 64;
@@ -297,9 +317,9 @@ hipError_t launch_tiled(void (*kern)(GemmArgs), int mode, const GemmArgs& a, hip
   return hipGetLastError();
 }
 
-template <typename Cfg, int MODE, int DT>
+template <typename Cfg, int MODE, int DT, bool ANY = false>
 hipError_t launch_mfma(const GemmArgs& a, hipStream_t st) {
-  return launch_tiled<Cfg>(gemm_mfma_kernel<Cfg, MODE, DT>, MODE, a, st);
+  return launch_tiled<Cfg>(gemm_mfma_kernel<Cfg, MODE, DT, ANY>, MODE, a, st);
 }
 
 template <int MODE, int DT>
@@ -307,6 +327,9 @@ hipError_t launch_gemm_dt(const Plan& p, const GemmArgs& args, hipStream_t st) {
   GemmArgs a = args;
   if (MODE == MODE_ACCUM) { a.tiles_m = p.accum_tiles_m; a.tiles_n = p.accum_tiles_n; }
   if constexpr (DT != DT_F32) {
+    if (p.any)
+      return (MODE == MODE_ACCUM ? p.accum_path : p.path) == PATH_128x4 ? launch_mfma<Cfg128x4, MODE, DT, true>(a, st)
+                                                                        : launch_mfma<Cfg256x8k32, MODE, DT, true>(a, st);
     switch (MODE == MODE_ACCUM ? p.accum_path : p.path) {
       case PATH_256x8: return launch_mfma<Cfg256x8, MODE, DT>(a, st);
       case PATH_128x4: return launch_mfma<Cfg128x4, MODE, DT>(a, st);
@@ -327,6 +350,7 @@ hipError_t launch_gemm_dt(const Plan& p, const GemmArgs& args, hipStream_t st) {
   const int tiles = a.tiles_m * a.tiles_n;
   const int grid = (MODE == MODE_ACCUM) ? tiles : tiles * a.B;
   if constexpr (DT == DT_F32) {
+    if (p.path == PATH_F32 && p.any) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE, true>, MODE, a, st, /*lockstep=*/true);
     if (p.path == PATH_F32) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE>, MODE, a, st, /*lockstep=*/true);
   }
   hipLaunchKernelGGL((gemm_simple_kernel<MODE, DT>), dim3(grid), dim3(256), 0, st, a);
@@ -349,17 +373,15 @@ hipError_t launch_aggregate(int dtype, const void* scratch, const float* factors
     hipLaunchKernelGGL((aggregate16_persistent_kernel<DT_BF16>), dim3(persistent_grid), dim3(256), 0, st, scratch, factors, B, S, n8, noise_scale, seed, layer, out, accumulate);
     return hipGetLastError();
   }
-  if (dtype != FLASHDP_F32 && S % 8 == 0) {
-    const size_t n8 = S / 8;
+  if (dtype != FLASHDP_F32) {   // the scratch of both 16-bit input types is bfloat16
+    const size_t n8 = (S + 7) / 8;
     const unsigned grid = (unsigned)((n8 + 255) / 256);
-    hipLaunchKernelGGL((aggregate16_kernel<DT_BF16>), dim3(grid), dim3(256), 0, st, scratch, factors, B, S, n8, noise_scale, seed, layer, out, accumulate);
+    auto kern = S % 8 == 0 ? aggregate16_kernel<DT_BF16, false> : aggregate16_kernel<DT_BF16, true>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, scratch, factors, B, S, n8, noise_scale, seed, layer, out, accumulate);
   } else {
     const size_t groups = (S + 3) / 4;
     const unsigned grid = (unsigned)((groups + 255) / 256);
-    if (dtype != FLASHDP_F32)   // the scratch of both 16-bit input types is bfloat16
-      hipLaunchKernelGGL((aggregate_generic_kernel<DT_BF16>), dim3(grid), dim3(256), 0, st, scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
-    else
-      hipLaunchKernelGGL(aggregate32_kernel, dim3(grid), dim3(256), 0, st, (const float*)scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
+    hipLaunchKernelGGL(aggregate32_kernel, dim3(grid), dim3(256), 0, st, (const float*)scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
   }
   return hipGetLastError();
 }
@@ -555,19 +577,20 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
     }
   } else if (use_scratch) {
     if (stages & FLASHDP_STAGE_CONTRACT) HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
-    // 16-bit scratch in whole 16-byte groups: the inter-block reduce and the clip factors are done by the streaming
+    // 16-bit scratch: the inter-block reduce and the clip factors are done by the streaming
     // kernel itself (one launch less per layer) when that is cheap: every workgroup reads all B * tiles partials, so
     // with the ordinary grid (one workgroup per 2048 elements) this is only done while those redundant reads stay
     // below 64 MB (a 4096 x 4096 layer: 32 MB; the Llama-13B layers would re-read 0.16-1.2 GB, and a grid bounded
     // to avoid that streams measurably slower: 191 vs 153 + 7 us per layer); the bounded grid of the overlapped
     // schedule always qualifies.
-    const size_t n8_all = S / 8, full_grid = (n8_all + 255) / 256;
+    const size_t n8_all = (S + 7) / 8, full_grid = (n8_all + 255) / 256;
     const size_t agg_grid = persistent_grid > 0 ? std::min((size_t)persistent_grid, full_grid) : full_grid;
-    const bool fold_clip = dtype != FLASHDP_F32 && S % 8 == 0 && B <= MAX_FUSED_CLIP_B &&
+    const bool fold_clip = dtype != FLASHDP_F32 && B <= MAX_FUSED_CLIP_B &&
                            agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20) &&
                            (stages & (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE)) == (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE);
     if (fold_clip) {
-      auto kern = persistent_grid > 0 ? clip_aggregate16_kernel<DT_BF16, false> : clip_aggregate16_kernel<DT_BF16, true>;
+      auto kern = persistent_grid > 0 ? clip_aggregate16_kernel<DT_BF16, false>   // (S is a multiple of 8 there)
+                  : S % 8 == 0 ? clip_aggregate16_kernel<DT_BF16, true> : clip_aggregate16_any_kernel<DT_BF16>;
       hipLaunchKernelGGL(kern, dim3((unsigned)agg_grid), dim3(256), 0, st, a.scratch, a.partials, tiles,
                          L.C, L.out_norms, (int)B, S, n8_all, noise_scale, L.seed, L.layer, L.out_grad, accumulate ? 1 : 0);
       HIP_TRY(hipGetLastError());
@@ -646,7 +669,7 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
       // (not the 384x192 / 192x384 kernels: their 248 registers leave no room for an aggregation wave beside two
       // contraction waves per SIMD, and a bounded aggregation workgroup that takes a CU would keep the next
       // contraction workgroup out of it until its whole share is done)
-      ok = (p.path == PATH_256x8k32 || p.path == PATH_256x8 || p.path == PATH_DMA || p.path == PATH_DMA16) && ((size_t)layers[l].d_in * layers[l].d_out) % 8 == 0;
+      ok = !p.any && (p.path == PATH_256x8k32 || p.path == PATH_256x8 || p.path == PATH_DMA || p.path == PATH_DMA16) && ((size_t)layers[l].d_in * layers[l].d_out) % 8 == 0;
     }
     return ok;
   };

@@ -28,7 +28,19 @@ struct F32Cfg {
   static constexpr int KS = BK / 2;                                // matrix-core k-steps per k-tile
 };
 
-template <int MODE>
+// The four floats of v moved down by s >= 0 places, zeros moving in from above.
+__device__ __forceinline__ u32x4_t shift_down4(const u32x4_t v, int s) {
+  u32x4_t r = {0, 0, 0, 0};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int f = e; f < 4; ++f) r[e] = (s == f - e) ? v[f] : r[e];
+  return r;
+}
+
+// ANY: feature sizes that are no multiple of 4 (see the note on such rows in gemm_mfma.hip.h; 4-byte alignment is all
+// a buffer load needs).  A chunk that reaches past its row's end is fetched from the last four columns and moved down.
+template <int MODE, bool ANY = false>
 __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a) {
   using C = F32Cfg;
   constexpr int FM = C::FM, FN = C::FN, LDA = C::LDA, LDB = C::LDB, KS = C::KS;
@@ -53,8 +65,10 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a)
   // global -> LDS copy plan (16-byte chunks of 4 floats; out-of-range columns are sent beyond num_records)
   const int c_row = tid / C::CPR, c_cc = tid % C::CPR;
   const bool a_ok = m0 + c_cc * 4 < a.D, b_ok = n0 + c_cc * 4 < a.P;
-  const uint32_t a_off0 = a_ok ? (uint32_t)(c_row * a.D + m0 + c_cc * 4) * 4u : 0x80000000u;
-  const uint32_t b_off0 = b_ok ? (uint32_t)(c_row * a.P + n0 + c_cc * 4) * 4u : 0x80000000u;
+  const int a_col = ANY ? min(m0 + c_cc * 4, a.D - 4) : m0 + c_cc * 4, b_col = ANY ? min(n0 + c_cc * 4, a.P - 4) : n0 + c_cc * 4;
+  const int a_sh = m0 + c_cc * 4 - a_col, b_sh = n0 + c_cc * 4 - b_col;
+  const uint32_t a_off0 = a_ok ? (uint32_t)(c_row * a.D + a_col) * 4u : 0x80000000u;
+  const uint32_t b_off0 = b_ok ? (uint32_t)(c_row * a.P + b_col) * 4u : 0x80000000u;
   const uint32_t a_rstep = (uint32_t)(C::RSTEP * a.D) * 4u, b_rstep = (uint32_t)(C::RSTEP * a.P) * 4u;
   const uint32_t a_kstep = (uint32_t)(C::BK * a.D) * 4u, b_kstep = (uint32_t)(C::BK * a.P) * 4u;
   const uint32_t a_bytes = (uint32_t)a.T * (uint32_t)a.D * 4u, b_bytes = (uint32_t)a.T * (uint32_t)a.P * 4u;
@@ -80,6 +94,16 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a)
     ld_kt = wrap ? 0 : ld_kt;
   };
   auto store_lds = [&](int stage) {
+    if constexpr (ANY) {   // taken on the tiles at the lower and right edge only
+      if (a_sh > 0) {
+#pragma unroll
+        for (int j = 0; j < C::CA; ++j) ra[j] = shift_down4(ra[j], a_sh);
+      }
+      if (b_sh > 0) {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j) rb[j] = shift_down4(rb[j], b_sh);
+      }
+    }
     float* pa = As + stage * C::A_STAGE + a_lds_w;
     float* pb = Bs + stage * C::B_STAGE + b_lds_w;
 #pragma unroll
@@ -191,6 +215,10 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a)
           const int col = col_base + j * 32 + 8 * q;
           if (col < a.P) {   // P is a multiple of 4 on this path: a 4-column group is all in or all out
             float4 v = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+            if constexpr (ANY) {
+              store_any(prow, col, a.P, v, MODE == MODE_ACCUM && a.accumulate);
+              continue;
+            }
             if (MODE == MODE_ACCUM && a.accumulate) {
               const float4 o = *(const float4*)(prow + col);
               v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;

@@ -1,6 +1,6 @@
 // Generic (any shape, any supported storage type) version of the per-sample contraction of Algorithm 1,
-// on the vector ALUs with fp32 accumulation: used for fp32 inputs and for 16-bit inputs whose feature
-// dimensions are not multiples of 8.  Same three modes and the same outputs as the matrix-core kernel.
+// on the vector ALUs with fp32 accumulation: used for rows too short for a 16-byte access and for layers too small to
+// occupy the matrix-core tiles.  Same three modes and the same outputs as the matrix-core kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

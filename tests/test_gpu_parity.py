@@ -149,6 +149,26 @@ def test_odd_dims_take_generic_kernel(schedule):
 
 
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
+@pytest.mark.parametrize("dtype,shape", [("bf16", s) for s in [(2, 33, 9, 72), (1, 1, 15, 131), (3, 70, 129, 257), (2, 64, 255, 136),
+                                                               (2, 40, 264, 135), (130, 20, 265, 10), (3, 97, 2049, 2303)]]
+                         + [("f16", (2, 65, 71, 383)), ("fp32", (10, 37, 509, 255)), ("fp32", (2, 18, 769, 1021))])
+def test_sizes_no_vector_width_divides(dtype, shape, schedule):
+    # edges of the 128 and 256 tiles, chunks that reach 1..7 columns past a row, one token, single short rows
+    B, T, P, D = shape
+    rng = np.random.default_rng(B * T + P)
+    X = rng.standard_normal((B, T, P)).astype(np.float32)
+    dY = (rng.standard_normal((B, T, D)) * 0.05 * (10.0 ** rng.uniform(-1, 1, size=(B, 1, 1)))).astype(np.float32)
+    want = None
+    if dtype == "f16":
+        X, dY = X.astype(np.float16), dY.astype(np.float16)
+        want = O.linear_dp_grad(X.astype(np.float32), dY.astype(np.float32), 1.0, 0.0, 9, 2)
+    elif dtype == "bf16":
+        X, dY = ((a.view(np.uint32) >> 16).astype(np.uint16) for a in (X, dY))
+    check_case(X, dY, 1.0, 1.0, 9, 2, dtype, schedule, oracle=want)
+    assert F.flashdp_last_kernel() == ("gemm_mfma_f32_kernel" if dtype == "fp32" else "gemm_mfma_kernel")
+
+
+@pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
 @pytest.mark.parametrize("shape", [(3, 100, 136, 264), (2, 33, 50, 70), (3, 70, 332, 520), (2, 16, 128, 128)])
 def test_f16_and_fp32_inputs(schedule, shape):
     B, T, P, D = shape
