@@ -119,7 +119,9 @@ enum { FLASHDP_BF16 = 0, FLASHDP_F32 = 1, FLASHDP_F16 = 2 };
  *            streaming kernel then runs beside chunk k+1's contraction), every chunk's clipped sum added to
  *            out_grad and the noise added with the last: memory bounded by the workspace whatever B is, each
  *            G_i still computed once (flashdp_workspace_bytes_chunked sizes such a workspace).  Only a
- *            workspace too small for a single sample falls back to TWOPASS.                              */
+ *            workspace too small for a single sample falls back to TWOPASS.  Rows without a sequence (T = 1) are
+ *            outer products, G_i = dy_i x_i^T with n_i = |dy_i| |x_i|: AUTO takes norms and factors from the rows and
+ *            forms the clipped sum as one product over the batch, whatever the workspace ("rows").        */
 enum { FLASHDP_SCHEDULE_AUTO = 0, FLASHDP_SCHEDULE_TWOPASS = 1, FLASHDP_SCHEDULE_SCRATCH = 2, FLASHDP_SCHEDULE_EXPLICIT = 3,
        FLASHDP_SCHEDULE_OVERLAP = 4, FLASHDP_SCHEDULE_GHOST = 5, FLASHDP_SCHEDULE_FUSED = 6 };
 
@@ -280,12 +282,13 @@ int flashdp_set_stages(int mask);
 /* Frees the library-owned workspaces, side streams and events (synchronises the device first). */
 int flashdp_release(void);
 
-/* Name of the schedule the last call on this thread used: "twopass", "scratch", "overlap", "explicit", "ghost" or "fused" ("none" before any). */
+/* Name of the schedule the last call on this thread used: "twopass", "scratch", "overlap", "explicit", "ghost", "fused",
+ * or "rows" (what AUTO takes where T = 1); "none" before any. */
 const char* flashdp_last_schedule(void);
 
 /* Name of the contraction kernel the last layer enqueued on this thread took (the per-sample pass of Algorithm 1):
  * "gemm_mfma_dma_kernel" (16-bit inputs, tiles loaded straight into LDS), "gemm_mfma_kernel" (16-bit, register-staged,
- * small shapes), "gemm_mfma_f32_kernel" (fp32 inputs), "gemm_simple_kernel" (any shape); "none" before any call. */
+ * small shapes), "gemm_mfma_f32_kernel" (fp32 inputs), "rows_accum_kernel" (T = 1, AUTO), "gemm_simple_kernel" (any shape); "none" before any call. */
 const char* flashdp_last_kernel(void);
 
 const char* flashdp_status_string(int status);

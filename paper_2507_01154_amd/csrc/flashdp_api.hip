@@ -24,6 +24,7 @@
 #include "gemm_simple.hip.h"
 #include "gram_norm.hip.h"
 #include "mfma_probe.hip.h"
+#include "rows_dp.hip.h"
 
 using namespace flashdp;
 
@@ -498,6 +499,44 @@ size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype,
   return ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode).total;
 }
 
+// Rows without a sequence (rows_dp.hip.h) are taken by every call that leaves the schedule to the library: nothing of
+// size B * P * D is moved, and the working memory (the clip factors) fits any workspace such a call accepts.
+// Not for one 16-bit sample: parking it costs 2 + 2 bytes an element beside the 4 of the output, and the streaming kernel
+// writes the output as fast or faster (bf16, 4096 x 13824: 126 us against 128 to 137; two samples: 163, 125; fp32, one sample:
+// 192, 128).
+bool rows_ok(int64_t B, int64_t T, int dtype) {
+  return T == 1 && (B > 1 || dtype == FLASHDP_F32) && g_ctx.stages == FLASHDP_STAGE_ALL && env().tile == 0;
+}
+
+template <int DT>
+hipError_t launch_rows(RowsArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((rows_clip_kernel<DT>), dim3((unsigned)a.B), dim3(256), 0, st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // 128-wide tiles (a quarter of the LDS reads per product) once they occupy the chip twice over
+  const int64_t tiles128 = (int64_t)((a.D + 127) / 128) * ((a.P + 127) / 128);
+  const bool large = tiles128 >= 512;
+  const int bm = large ? 128 : 64;
+  a.tiles_m = (a.D + bm - 1) / bm;
+  a.tiles_n = (a.P + bm - 1) / bm;
+  auto kern = large ? rows_accum_kernel<2, DT> : rows_accum_kernel<1, DT>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t run_rows(const flashdp_layer_t& L, int64_t B, int dtype, char* ws, hipStream_t st, bool accumulate, bool add_noise) {
+  RowsArgs a;
+  a.X = L.X; a.dY = L.dY; a.B = (int)B; a.P = (int)L.d_in; a.D = (int)L.d_out;
+  a.tiles_m = a.tiles_n = 0;
+  a.factors = reinterpret_cast<float*>(ws);
+  a.out_norms = L.out_norms; a.out = L.out_grad;
+  a.C = L.C; a.noise_scale = add_noise ? L.sigma * L.C : 0.0f;
+  a.seed = L.seed; a.layer = L.layer;
+  a.accumulate = accumulate ? 1 : 0;
+  g_ctx.last_kernel = "rows_accum_kernel";
+  return dtype == FLASHDP_BF16 ? launch_rows<DT_BF16>(a, st) : dtype == FLASHDP_F16 ? launch_rows<DT_F16>(a, st) : launch_rows<DT_F32>(a, st);
+}
+
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) { (void)hipGetLastError(); return FLASHDP_HIP_ERROR; } } while (0)
 
 // Enqueues Algorithm 1 for one layer.
@@ -682,6 +721,20 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
   const bool overlap_ok = n_layers >= 2 && overlap_fits(B);
   const size_t need_overlap = 2 * scratch_need(B);
   char* ws = static_cast<char*>(workspace);
+  if (schedule == FLASHDP_SCHEDULE_AUTO && rows_ok(B, T, dtype)) {
+    if (workspace && workspace_bytes < need_small) return FLASHDP_WORKSPACE_TOO_SMALL;
+    if (!workspace) {
+      void* p = nullptr; size_t got = 0;
+      st = owned_workspace(need_small, &p, &got);
+      if (st != FLASHDP_OK) return st;
+      ws = static_cast<char*>(p);
+    }
+    for (int l = 0; l < n_layers; ++l)
+      HIP_TRY(run_rows(layers[l], B, dtype, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
+    g_ctx.last_chunk = B;
+    g_ctx.last_schedule = "rows";
+    return FLASHDP_OK;
+  }
   int mode;
   int64_t chunk = B;   // samples parked at a time
   if (workspace) {
@@ -835,6 +888,11 @@ int flashdp_linear_dp_grad_static(const void* X, const void* dY, int64_t B, int6
   char* ws = nullptr;
   st = static_scratch_ptr(dev, &ws);
   if (st != FLASHDP_OK) return st;
+  if (rows_ok(B, T, dtype)) {
+    HIP_TRY(run_rows(L, B, dtype, ws, static_cast<hipStream_t>(stream), false, true));
+    g_ctx.last_schedule = "rows";
+    return FLASHDP_OK;
+  }
   // Every part of the workspace a call reads it has written itself first (partials by the contraction, factors
   // by the clip kernel, the parked tiles by the spill), so nothing has to be cleared between calls.
   st = run_layer(L, B, T, dtype, FLASHDP_SCHEDULE_SCRATCH, ws, static_cast<hipStream_t>(stream), false, true);

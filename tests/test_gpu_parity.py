@@ -168,6 +168,32 @@ def test_sizes_no_vector_width_divides(dtype, shape, schedule):
     assert F.flashdp_last_kernel() == ("gemm_mfma_f32_kernel" if dtype == "fp32" else "gemm_mfma_kernel")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "fp32"])
+@pytest.mark.parametrize("shape", [(17, 1, 1), (2, 3, 65), (33, 64, 64), (65, 130, 61), (256, 257, 10), (17, 2884, 2950), (31, 2816, 3072)])
+def test_rows_without_a_sequence(shape, dtype):
+    # both tile sizes (2816 x 3072 and 2884 x 2950: 128), edges of tiles and of the batch's steps, features that no vector
+    # width divides, a second micro-batch added to the first one's sum, a workspace of the smallest size that is accepted
+    B, P, D = shape
+    rng = np.random.default_rng(B + P * D)
+    X = rng.standard_normal((B, 1, P)).astype(np.float32)
+    dY = (rng.standard_normal((B, 1, D)) * 0.05 * (10.0 ** rng.uniform(-1, 1, size=(B, 1, 1)))).astype(np.float32)
+    want = None
+    if dtype == "f16":
+        X, dY = X.astype(np.float16), dY.astype(np.float16)
+        want = O.linear_dp_grad(X.astype(np.float32), dY.astype(np.float32), 1.0, 0.0, 9, 2)
+    elif dtype == "bf16":
+        X, dY = ((a.view(np.uint32) >> 16).astype(np.uint16) for a in (X, dY))
+    e_sig, e_norm, _, used = check_case(X, dY, 1.0, 1.0, 9, 2, dtype, "auto", oracle=want)
+    assert used == "rows" and e_sig <= 2e-6 and e_norm <= 2e-7     # fp32 sums of at most 256 products; norms rounded once
+    dX, ddY = to_device(X), to_device(dY)
+    once, twice = (torch.empty((D, P), device=DEV) for _ in range(2))
+    L = [dict(X=dX, dY=ddY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=9, layer=2, out_grad=o, out_norms=None) for o in (once, twice)]
+    ws = torch.empty((F.flashdp_workspace_bytes([L[0]], B, 1, F.dtype_code(dX), "twopass"),), dtype=torch.uint8, device=DEV)
+    for k in range(3):
+        F.flashdp_block_dp_grad_micro([L[min(k, 1)]], B, 1, F.dtype_code(dX), "auto", ws, accumulate=k == 2, add_noise=False)
+    assert torch.equal(twice, 2.0 * once)
+
+
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
 @pytest.mark.parametrize("shape", [(3, 100, 136, 264), (2, 33, 50, 70), (3, 70, 332, 520), (2, 16, 128, 128)])
 def test_f16_and_fp32_inputs(schedule, shape):
