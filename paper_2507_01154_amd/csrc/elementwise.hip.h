@@ -44,17 +44,17 @@ __global__ __launch_bounds__(256) void clip_factors_kernel(const float* __restri
 }
 
 // The same inside a streaming kernel: every workgroup (4 waves) works out all clip factors into LDS for itself, wave w
-// taking samples w, w + 4, ...; workgroup 0 also reports the norms.  Costs a workgroup about a microsecond and
+// taking samples w, w + 4, ...; one workgroup (report) also writes the norms out.  Costs a workgroup about a microsecond and
 // B * tiles * 4 bytes of (cached) reads, and saves a kernel launch per layer; B <= MAX_FUSED_CLIP_B.
 constexpr int MAX_FUSED_CLIP_B = 64;
 __device__ __forceinline__ void clip_factors_to_lds(const float* __restrict__ partials, int tiles, float C, int B,
-                                                    float* lds_factors, float* __restrict__ out_norms) {
+                                                    float* lds_factors, float* __restrict__ out_norms, bool report) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i = wave; i < B; i += 4) {
     const double n = sqrt(sample_norm_sq(partials + (size_t)i * tiles, tiles, lane));
     if (lane == 0) {
       lds_factors[i] = clip_factor_of(n, C);
-      if (blockIdx.x == 0 && out_norms) out_norms[i] = (float)n;
+      if (report && out_norms) out_norms[i] = (float)n;
     }
   }
   __syncthreads();
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void clip_aggregate16_kernel(const void* __res
                                                                size_t n8, float noise_scale, uint64_t seed, uint32_t layer,
                                                                float* __restrict__ out, int accumulate) {
   __shared__ float fac[MAX_FUSED_CLIP_B];
-  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms);
+  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms, blockIdx.x == 0);
   const size_t stride = (size_t)gridDim.x * 256;
   for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < n8; v += stride)
     aggregate16_one<DT, DEEP>(scratch, fac, B, S, v, noise_scale, seed, layer, out, accumulate);
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void clip_aggregate16_any_kernel(const void* _
                                                                    size_t n8, float noise_scale, uint64_t seed, uint32_t layer,
                                                                    float* __restrict__ out, int accumulate) {
   __shared__ float fac[MAX_FUSED_CLIP_B];
-  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms);
+  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms, blockIdx.x == 0);
   const size_t v = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (v < n8) aggregate16_one<DT, true, true>(scratch, fac, B, S, v, noise_scale, seed, layer, out, accumulate);
 }
@@ -230,6 +230,33 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
   const f32x4_t lo = {acc[0], acc[1], acc[2], acc[3]}, hi = {acc[4], acc[5], acc[6], acc[7]};
   __builtin_nontemporal_store(lo, dst);
   __builtin_nontemporal_store(hi, dst + 1);
+}
+
+// The tails of the layers of a grouped contraction (gemm_mfma_grouped_kernel) in one launch.
+struct GroupedTailArgs {
+  int n, B;
+  int first[GROUP_MAX + 1];
+  struct Layer {
+    const void* scratch;
+    const float* partials;
+    float* out_norms;
+    float* out;
+    size_t S;
+    uint64_t seed;
+    float C, noise_scale;
+    uint32_t layer;
+    int tiles, accumulate;
+  } layer[GROUP_MAX];
+};
+template <int DT>
+__global__ __launch_bounds__(256) void clip_aggregate16_grouped_kernel(const GroupedTailArgs g) {
+  __shared__ float fac[MAX_FUSED_CLIP_B];
+  const int l = group_of(g.first, g.n, blockIdx.x);
+  const GroupedTailArgs::Layer& a = g.layer[l];
+  const int bid = (int)blockIdx.x - g.first[l];
+  clip_factors_to_lds(a.partials, a.tiles, a.C, g.B, fac, a.out_norms, bid == 0);
+  const size_t v = (size_t)bid * 256 + threadIdx.x;
+  if (v < a.S / 8) aggregate16_one<DT, true>(a.scratch, fac, g.B, a.S, v, a.noise_scale, a.seed, a.layer, a.out, a.accumulate);
 }
 
 // ---- the explicit four-stage flow of Appendix B.2 on a materialised fp32 G[B][S] (measured comparison) ----

@@ -434,7 +434,8 @@ int device_or_error(int* dev) {
   return FLASHDP_OK;
 }
 
-int owned_workspace(size_t need, void** ptr, size_t* bytes) {
+// wish: the size to take, if more than need, when the workspace has to grow anyway.
+int owned_workspace(size_t need, void** ptr, size_t* bytes, size_t wish = 0) {
   int dev = 0;
   int st = device_or_error(&dev);
   if (st != FLASHDP_OK) return st;
@@ -445,7 +446,7 @@ int owned_workspace(size_t need, void** ptr, size_t* bytes) {
     // allocation, inside what may be a training step: grow by at least half, so that a sequence of slowly growing
     // requests (layers met in increasing size) reallocates a few times, not every time.  A caller that must not
     // stall passes its own workspace.
-    const size_t want = std::max(need, w.bytes + w.bytes / 2);
+    const size_t want = std::max(std::max(need, wish), w.bytes + w.bytes / 2);
     if (w.ptr) {
       if (hipDeviceSynchronize() != hipSuccess) return FLASHDP_HIP_ERROR;
       (void)hipFree(w.ptr);
@@ -539,6 +540,100 @@ hipError_t run_rows(const flashdp_layer_t& L, int64_t B, int dtype, char* ws, hi
 
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) { (void)hipGetLastError(); return FLASHDP_HIP_ERROR; } } while (0)
 
+// Whether the streaming kernel of the scratch schedule works out the clip factors itself (see run_layer).
+bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
+  return dtype != FLASHDP_F32 && B <= MAX_FUSED_CLIP_B && agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20);
+}
+
+// Layers of one call that share their two launches (scratch schedule): those on the 128 x 128 kernel, which by make_plan's
+// rule have too few tiles to fill the chip with large ones, as many in a row as the workspace holds parked together.
+// Same kernels' code on the same tiles: results are bit-identical to one launch per layer.
+// Such layers are bound by the length of one workgroup's reduction and by launches, so sharing them helps at every size
+// the path takes (bf16, together against one after the other: a GPT-2 block at B = 1, T = 1024, 37 us, 83 before, 56 when
+// the workspace holds three of the four; at B = 3, 83, 112; two layers of 2048 x 2048, T = 2048, 64, 75; eight of
+// 128 x 128, T = 1024, 19, 136).
+struct GroupSlot { size_t partials, scratch, end; };
+GroupSlot group_slot(const Plan& p, int64_t B, int64_t P, int64_t D, size_t begin) {
+  GroupSlot g;
+  g.partials = begin;
+  g.scratch = g.partials + align_up((size_t)B * p.tiles_m * p.tiles_n * 4, 256);
+  g.end = g.scratch + align_up((size_t)B * P * D * 2, 256);
+  return g;
+}
+bool group_ok(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
+  if (dtype == FLASHDP_F32 || g_ctx.stages != FLASHDP_STAGE_ALL) return false;
+  const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
+  return p.path == PATH_128x4 && !p.any &&
+         fold_clip_ok(dtype, B, p.tiles_m * p.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
+}
+// Neither layer writes what the other reads or writes (a caller may pass one buffer twice: such layers keep their order).
+bool group_disjoint(const flashdp_layer_t& x, const flashdp_layer_t& y, int64_t B, int64_t T) {
+  struct Range { uintptr_t lo, hi; };
+  auto range = [](const void* p, size_t n) { return Range{(uintptr_t)p, (uintptr_t)p + (p ? n : 0)}; };
+  auto meet = [](Range u, Range v) { return u.lo < v.hi && v.lo < u.hi; };
+  auto clash = [&](const flashdp_layer_t& w, const flashdp_layer_t& r) {
+    const Range writes[2] = {range(w.out_grad, (size_t)w.d_in * w.d_out * 4), range(w.out_norms, (size_t)B * 4)};
+    const Range touches[4] = {range(r.X, (size_t)B * T * r.d_in * 2), range(r.dY, (size_t)B * T * r.d_out * 2),
+                              range(r.out_grad, (size_t)r.d_in * r.d_out * 4), range(r.out_norms, (size_t)B * 4)};
+    for (const Range& u : writes)
+      for (const Range& v : touches)
+        if (meet(u, v)) return true;
+    return false;
+  };
+  return !clash(x, y) && !clash(y, x);
+}
+// How many layers from the first on go into one launch (1: take the ordinary way).
+int group_length(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype, size_t ws_bytes) {
+  size_t used = 0;
+  int k = 0;
+  for (; k < n && k < GROUP_MAX && group_ok(layers[k], B, T, dtype); ++k) {
+    used = group_slot(make_plan(B, T, layers[k].d_in, layers[k].d_out, dtype), B, layers[k].d_in, layers[k].d_out, used).end;
+    if (used > ws_bytes) break;
+    bool apart = true;
+    for (int j = 0; j < k && apart; ++j) apart = group_disjoint(layers[j], layers[k], B, T);
+    if (!apart) break;
+  }
+  return std::max(k, 1);
+}
+
+template <int DT>
+hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype, char* ws, hipStream_t st,
+                     bool accumulate, bool add_noise) {
+  GroupedGemmArgs g;
+  GroupedTailArgs t;
+  g.n = t.n = n;
+  t.B = (int)B;
+  g.first[0] = t.first[0] = 0;
+  size_t used = 0;
+  for (int l = 0; l < n; ++l) {
+    const flashdp_layer_t& L = layers[l];
+    const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
+    const GroupSlot s = group_slot(p, B, L.d_in, L.d_out, used);
+    used = s.end;
+    GemmArgs& a = g.layer[l];
+    a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
+    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
+    a.partials = reinterpret_cast<float*>(ws + s.partials);
+    a.scratch = ws + s.scratch;
+    a.factors = nullptr; a.out = L.out_grad; a.accumulate = 0; a.trace = nullptr;
+    GroupedTailArgs::Layer& q = t.layer[l];
+    q.scratch = a.scratch; q.partials = a.partials; q.out_norms = L.out_norms; q.out = L.out_grad;
+    q.S = (size_t)L.d_in * L.d_out; q.seed = L.seed; q.C = L.C; q.noise_scale = add_noise ? L.sigma * L.C : 0.0f;
+    q.layer = L.layer; q.tiles = p.tiles_m * p.tiles_n; q.accumulate = accumulate ? 1 : 0;
+    g.first[l + 1] = g.first[l] + (int)(q.tiles * B);   // a few hundred each by the path's rule
+    t.first[l + 1] = t.first[l] + (int)((q.S / 8 + 255) / 256);
+  }
+  auto kern = gemm_mfma_grouped_kernel<Cfg128x4, DT>;
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), Cfg128x4::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[n]), dim3(Cfg128x4::NT), Cfg128x4::LDS_BYTES, st, g);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((clip_aggregate16_grouped_kernel<DT_BF16>), dim3((unsigned)t.first[n]), dim3(256), 0, st, t);
+  g_ctx.last_kernel = path_kernel_name(PATH_128x4);
+  return hipGetLastError();
+}
+
 // Enqueues Algorithm 1 for one layer.
 // `parts` restricts what is enqueued (a subset of the stage mask); persistent_grid > 0 selects the bounded
 // aggregation grid of the overlapped schedule.
@@ -624,8 +719,7 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
     // schedule always qualifies.
     const size_t n8_all = (S + 7) / 8, full_grid = (n8_all + 255) / 256;
     const size_t agg_grid = persistent_grid > 0 ? std::min((size_t)persistent_grid, full_grid) : full_grid;
-    const bool fold_clip = dtype != FLASHDP_F32 && B <= MAX_FUSED_CLIP_B &&
-                           agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20) &&
+    const bool fold_clip = fold_clip_ok(dtype, B, tiles, agg_grid) &&
                            (stages & (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE)) == (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE);
     if (fold_clip) {
       auto kern = persistent_grid > 0 ? clip_aggregate16_kernel<DT_BF16, false>   // (S is a multiple of 8 there)
@@ -721,6 +815,7 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
   const bool overlap_ok = n_layers >= 2 && overlap_fits(B);
   const size_t need_overlap = 2 * scratch_need(B);
   char* ws = static_cast<char*>(workspace);
+  size_t ws_bytes = workspace_bytes;
   if (schedule == FLASHDP_SCHEDULE_AUTO && rows_ok(B, T, dtype)) {
     if (workspace && workspace_bytes < need_small) return FLASHDP_WORKSPACE_TOO_SMALL;
     if (!workspace) {
@@ -773,10 +868,20 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     const size_t need = mode == FLASHDP_SCHEDULE_OVERLAP ? need_overlap : mode == FLASHDP_SCHEDULE_SCRATCH ? need_scratch
                         : mode == FLASHDP_SCHEDULE_EXPLICIT ? need_explicit : mode == FLASHDP_SCHEDULE_GHOST ? need_ghost
                         : mode == FLASHDP_SCHEDULE_FUSED ? need_fused : need_small;
+    // room for a group of small layers, if the library's workspace has to grow anyway
+    size_t wish = 0;
+    if (mode == FLASHDP_SCHEDULE_SCRATCH && n_layers >= 2) {
+      for (int l = 0; l < n_layers && l < GROUP_MAX && group_ok(layers[l], B, T, dtype); ++l) {
+        const size_t end = group_slot(make_plan(B, T, layers[l].d_in, layers[l].d_out, dtype), B, layers[l].d_in, layers[l].d_out, wish).end;
+        if (end > (size_t(64) << 20)) break;
+        wish = end;
+      }
+    }
     void* p = nullptr; size_t got = 0;
-    st = owned_workspace(need, &p, &got);
+    st = owned_workspace(need, &p, &got, wish);
     if (st != FLASHDP_OK) return st;
     ws = static_cast<char*>(p);
+    ws_bytes = got;
   }
   g_ctx.last_chunk = chunk;
   hipStream_t main_st = static_cast<hipStream_t>(stream);
@@ -848,7 +953,17 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     g_ctx.last_schedule = "overlap";
     return FLASHDP_OK;
   }
-  for (const Item& it : items) {
+  for (int k = 0; k < n_items; ++k) {
+    if (mode == FLASHDP_SCHEDULE_SCRATCH && chunk == B && n_layers >= 2) {   // items are the layers in the caller's order
+      const int n = group_length(layers + k, n_layers - k, B, T, dtype, ws_bytes);
+      if (n >= 2) {
+        HIP_TRY(dtype == FLASHDP_BF16 ? run_group<DT_BF16>(layers + k, n, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0)
+                                      : run_group<DT_F16>(layers + k, n, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0));
+        k += n - 1;
+        continue;
+      }
+    }
+    const Item& it = items[k];
     st = run_layer(layers[it.layer], it.b, T, dtype, mode, ws, main_st, it.acc, it.noise, FLASHDP_STAGE_ALL, 0, it.s0);
     if (st != FLASHDP_OK) return st;
   }

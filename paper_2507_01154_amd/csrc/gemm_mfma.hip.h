@@ -335,8 +335,9 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, f32x16_t (&acc)
   }
 }
 
-template <typename Cfg, int MODE, int DT, bool ANY = false>
-__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(const GemmArgs a) {
+// bid: which of the layer's workgroups this one is.
+template <typename Cfg, int MODE, int DT, bool ANY>
+__device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, NT = Cfg::NT;
   constexpr int FM = Cfg::FM, FN = Cfg::FN, LDA = Cfg::LDA, LDB = Cfg::LDB;
   constexpr int CA = Cfg::CA, CB = Cfg::CB;
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(c
 
   const int tiles = a.tiles_m * a.tiles_n;
   const int total = (MODE == MODE_ACCUM) ? tiles : tiles * a.B;
-  const int item = xcd_remap(blockIdx.x, total);
+  const int item = xcd_remap(bid, total);
   const int sample0 = (MODE == MODE_ACCUM) ? 0 : item / tiles;
   const int n_samples = (MODE == MODE_ACCUM) ? a.B : 1;
   const int tile = (MODE == MODE_ACCUM) ? item : item - sample0 * tiles;
@@ -529,6 +530,32 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(c
   __syncthreads();   // the reduction below reuses the LDS tiles
 
   tile_epilogue<Cfg, MODE, DT, ANY>(a, acc, lds, m0, n0, sample0, tile, tiles);
+}
+
+template <typename Cfg, int MODE, int DT, bool ANY = false>
+__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(const GemmArgs a) {
+  gemm_mfma_body<Cfg, MODE, DT, ANY>(a, blockIdx.x);
+}
+
+// Several layers in one launch: workgroups first[l] .. first[l + 1] - 1 are layer l's.  For layers too small to fill the
+// chip by themselves (a GPT-2 block at one sample has 36 to 144 workgroups per layer on 256 CUs), which are bound by the
+// length of one workgroup's reduction and by the gaps between launches, not by a rate.
+constexpr int GROUP_MAX = 8;
+struct GroupedGemmArgs {
+  int n;
+  int first[GROUP_MAX + 1];
+  GemmArgs layer[GROUP_MAX];
+};
+template <int N>
+__device__ __forceinline__ int group_of(const int (&first)[N], int n, int bid) {
+  int l = 0;
+  while (l + 1 < n && bid >= first[l + 1]) ++l;
+  return l;
+}
+template <typename Cfg, int DT>
+__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_grouped_kernel(const GroupedGemmArgs g) {
+  const int l = group_of(g.first, g.n, blockIdx.x);
+  gemm_mfma_body<Cfg, MODE_SPILL, DT, false>(g.layer[l], (int)blockIdx.x - g.first[l]);
 }
 
 }  // namespace flashdp

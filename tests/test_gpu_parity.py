@@ -168,6 +168,37 @@ def test_sizes_no_vector_width_divides(dtype, shape, schedule):
     assert F.flashdp_last_kernel() == ("gemm_mfma_f32_kernel" if dtype == "fp32" else "gemm_mfma_kernel")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("B,T,dims", [(1, 100, [(136, 264), (8, 8), (768, 128)]), (3, 33, [(256, 384)] * 9), (2, 64, [(130, 257), (128, 64), (264, 72)])])
+def test_layers_of_a_call_are_those_of_single_calls(B, T, dims, dtype):
+    # layers that share launches (16-bit, small), more of them than one launch takes, one among them that takes another
+    # kernel, workspaces that hold all, two or one of them, and one output buffer named twice (the later layer stands)
+    rng = np.random.default_rng(B + T)
+    tt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    layers, want = [], []
+    for l, (P, D) in enumerate(dims):
+        X = torch.from_numpy(rng.standard_normal((B, T, P)).astype(np.float32)).to(DEV).to(tt)
+        dY = torch.from_numpy((rng.standard_normal((B, T, D)) * 0.05).astype(np.float32)).to(DEV).to(tt)
+        L = dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0 + l, sigma=0.5, seed=9 + l, layer=l,
+                 out_grad=torch.empty((D, P), device=DEV), out_norms=torch.empty((B,), device=DEV))
+        F.flashdp_block_dp_grad([L], B, T, F.dtype_code(X), "scratch")
+        want.append((L["out_grad"].clone(), L["out_norms"].clone()))
+        layers.append(L)
+    code = F.dtype_code(layers[0]["X"])
+    one = F.flashdp_workspace_bytes(layers, B, T, code, "scratch")
+    for ws in (one, 2 * one, 9 * one, None):
+        for L in layers:
+            L["out_grad"].fill_(float("nan"))
+            L["out_norms"].fill_(float("nan"))
+        F.flashdp_block_dp_grad(layers, B, T, code, "scratch", None if ws is None else torch.empty((ws,), dtype=torch.uint8, device=DEV))
+        for L, (g, n) in zip(layers, want):
+            assert torch.equal(L["out_grad"], g) and torch.equal(L["out_norms"], n), ws
+    if len(set(dims)) == 1:
+        F.flashdp_block_dp_grad([layers[0], dict(layers[1], out_grad=layers[0]["out_grad"])], B, T, code, "scratch",
+                                torch.empty((9 * one,), dtype=torch.uint8, device=DEV))
+        assert torch.equal(layers[0]["out_grad"], want[1][0])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "fp32"])
 @pytest.mark.parametrize("shape", [(17, 1, 1), (2, 3, 65), (33, 64, 64), (65, 130, 61), (256, 257, 10), (17, 2884, 2950), (31, 2816, 3072)])
 def test_rows_without_a_sequence(shape, dtype):
