@@ -42,7 +42,8 @@
  *   - NaN/Inf in the inputs propagate to out_norms / out_grad: a sample with a NaN norm gets a NaN clip
  *     factor and so turns the whole of out_grad into NaN (it is never let through unclipped).
  *     A per-sample gradient that overflows fp32 (infinite norm) poisons out_grad with NaN/Inf under every
- *     schedule.  TWOPASS and GHOST rescale the running sum by c_i / c_(i+1) at sample boundaries; two
+ *     schedule, and where T = 1 under AUTO, which forms no G_i, too (every element is then NaN).  A clip factor too
+ *     small for a normal float is rounded towards zero, so that the clipped sample stays within C.  TWOPASS and GHOST rescale the running sum by c_i / c_(i+1) at sample boundaries; two
  *     consecutive clip factors further apart than about 1e38 (a norm beyond 1e38 * C) overflow that ratio and
  *     give Inf/NaN as well, where SCRATCH / OVERLAP / EXPLICIT still give the finite result.
  *   - Return value: FLASHDP_OK (0) or a negative flashdp_status.  Argument errors (everything but

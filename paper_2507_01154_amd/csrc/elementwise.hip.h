@@ -23,10 +23,14 @@ __device__ __forceinline__ double sample_norm_sq(const float* __restrict__ parti
 }
 
 // c_i = 1 / max(1, n_i / C), written so that a NaN norm gives a NaN factor: a sample whose norm is unknown must not
-// pass unclipped.
+// pass unclipped.  A factor below the smallest normal float has few bits (n_i / C = 1.2e45 would round to the smallest
+// subnormal, 1.7 times too large), so it is rounded towards zero: the clipped sample never ends above C.
 __device__ __forceinline__ float clip_factor_of(double norm, float C) {
   const double ratio = norm / (double)C;
-  return (float)(1.0 / (ratio <= 1.0 ? 1.0 : ratio));
+  const double c = 1.0 / (ratio <= 1.0 ? 1.0 : ratio);
+  const float f = (float)c;
+  if (f < 1.17549435e-38f && (double)f > c) return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, f) - 1u);
+  return f;
 }
 
 // n_i = sqrt(sum of partials), c_i: one wave per sample, four samples per workgroup.  (The streaming kernels of the

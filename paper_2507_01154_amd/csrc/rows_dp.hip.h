@@ -58,8 +58,11 @@ __global__ __launch_bounds__(256) void rows_clip_kernel(const RowsArgs a) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const double n = sqrt(((red[0] + red[1]) + (red[2] + red[3])) * ((red[4] + red[5]) + (red[6] + red[7])));
-    a.factors[i] = clip_factor_of(n, a.C);
-    if (a.out_norms) a.out_norms[i] = (float)n;
+    // G_i is never formed, so its overflow has to be brought in here: where n_i is no fp32 number the factor is NaN and
+    // poisons out_grad (C / n_i would underflow to a finite zero and drop the sample in silence).
+    const float nf = (float)n;
+    a.factors[i] = __builtin_isinf(nf) ? __builtin_nanf("") : clip_factor_of(n, a.C);
+    if (a.out_norms) a.out_norms[i] = nf;
   }
 }
 

@@ -225,6 +225,48 @@ def test_rows_without_a_sequence(shape, dtype):
     assert torch.equal(twice, 2.0 * once)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_rows_without_a_sequence_that_are_not_finite_or_overflow(dtype):
+    # G_i is not formed there, so what its elements would show has to show all the same
+    g = torch.Generator(device=DEV).manual_seed(3)
+    B, P, D = 5, 72, 40
+    x0, y0 = (torch.randn((B, 1, n), generator=g, device=DEV) for n in (P, D))
+
+    def run(x, y, C):
+        x, y = x.to(dtype), y.to(dtype)
+        out, norms = torch.full((D, P), 7.0, device=DEV), torch.full((B,), 7.0, device=DEV)
+        F.flashdp_block_dp_grad([dict(X=x, dY=y, d_in=P, d_out=D, C=C, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)],
+                                B, 1, F.dtype_code(x), "auto")
+        assert F.flashdp_last_schedule() == "rows"
+        want = x.double().square().sum(2).sqrt() * y.double().square().sum(2).sqrt()
+        return out, norms, want[:, 0], x.double()[:, 0], y.double()[:, 0]
+
+    for bad in (float("nan"), float("inf")):
+        for operand in (0, 1):
+            x, y = x0.clone(), y0.clone()
+            (x, y)[operand][2, 0, 11] = bad
+            out, norms, want, _, _ = run(x, y, 1.0)
+            assert torch.isnan(out).all() and not torch.isfinite(norms[2])
+            keep = [0, 1, 3, 4]
+            assert torch.allclose(norms[keep].double(), want[keep], rtol=1e-6)
+    # finite rows whose outer product overflows fp32
+    x, y = x0.clone(), y0.clone()
+    x[2] *= 1e30
+    y[2] *= 1e30
+    out, norms, _, _, _ = run(x, y, 1.0)
+    assert torch.isnan(out).all() and torch.isinf(norms[2])
+    # clip factors down to and below the smallest normal float: one sample that counts, so the output is its contribution
+    for norm, C in ((1e11, 1.0), (1e31, 1.0), (2.5e37, 1.0), (1e21, 1e-19), (1.5e34, 1e-9), (1.2e33, 1e-12), (1e34, 1e-12)):
+        x = torch.zeros_like(x0)
+        x[2] = x0[2] * (norm / (x0[2].norm() * y0[2].norm()))
+        out, norms, want, xd, yd = run(x, y0, C)
+        n = float(out.double().norm())
+        assert torch.isfinite(norms).all() and n <= C * (1 + 3e-7), (norm, C, n / C)
+        if float(want[2]) / C < 1e38:      # the factor is a normal float: the direction and the length are right too
+            exact = yd[2][:, None] * xd[2][None, :] * (C / float(want[2]))
+            assert float((out.double() - exact).norm()) <= 1e-5 * C, (norm, C)
+
+
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
 @pytest.mark.parametrize("shape", [(3, 100, 136, 264), (2, 33, 50, 70), (3, 70, 332, 520), (2, 16, 128, 128)])
 def test_f16_and_fp32_inputs(schedule, shape):
