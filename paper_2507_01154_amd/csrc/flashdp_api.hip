@@ -515,11 +515,11 @@ hipError_t launch_rows(RowsArgs& a, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // 128-wide tiles (a quarter of the LDS reads per product) once they occupy the chip twice over
-  const int64_t tiles128 = (int64_t)((a.D + 127) / 128) * ((a.P + 127) / 128);
+  const int64_t tiles128 = (int64_t)edge_plan::tiles(a.D, 128) * edge_plan::tiles(a.P, 128);
   const bool large = tiles128 >= 512;
   const int bm = large ? 128 : 64;
-  a.tiles_m = (a.D + bm - 1) / bm;
-  a.tiles_n = (a.P + bm - 1) / bm;
+  a.tiles_m = edge_plan::tiles(a.D, bm);
+  a.tiles_n = edge_plan::tiles(a.P, bm);
   auto kern = large ? rows_accum_kernel<2, DT> : rows_accum_kernel<1, DT>;
   hipLaunchKernelGGL(kern, dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(256), 0, st, a);
   return hipGetLastError();

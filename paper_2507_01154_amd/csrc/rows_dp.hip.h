@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "edge_plan.h"
 #include "elementwise.hip.h"
 #include "gemm_mfma.hip.h"
 #include "gemm_simple.hip.h"
@@ -32,13 +33,13 @@ struct RowsArgs {
 template <int DT>
 __device__ __forceinline__ double row_square_sum(const void* p, size_t base, int n) {
   double s[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = threadIdx.x; k < n; k += 1024) {
+  edge_plan::walk_row(n, threadIdx.x, [&](uint32_t k) {
     float v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = k + 256 * q < n ? load_elem<DT>(p, base + k + 256 * q) : 0.0f;
+    for (int q = 0; q < 4; ++q) v[q] = k + 256 * q < (uint32_t)n ? load_elem<DT>(p, base + k + 256 * q) : 0.0f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) s[q] = fma((double)v[q], (double)v[q], s[q]);
-  }
+  });
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
 

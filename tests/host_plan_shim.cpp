@@ -58,3 +58,24 @@ int p16_kept_at(int row, int col) { return flashdp::lds_plan16::kept_at(row, col
 int p16_frag_offset(int lane, int block) { return flashdp::lds_plan16::frag_offset(lane, block); }
 int p16_tile_base(int stage, int operand) { return flashdp::lds_plan16::tile_base(stage, operand); }
 }
+
+// Index arithmetic at the ends of very long rows.
+#include "../paper_2507_01154_amd/csrc/edge_plan.h"
+extern "C" {
+int ep_tiles(int n, int side) { return flashdp::edge_plan::tiles(n, side); }
+// walks thread's share of a row; returns how many elements it takes, *lo and *hi the smallest and largest index among them
+long ep_walk(int n, int thread, long* lo, long* hi) {
+  long count = 0;
+  *lo = 1L << 62; *hi = -1;
+  flashdp::edge_plan::walk_row(n, thread, [&](auto k) {
+    for (int q = 0; q < 4; ++q)
+      if (k + 256 * q < (decltype(k))n) {
+        const long e = (long)(decltype(k))(k + 256 * q);
+        ++count;
+        *lo = e < *lo ? e : *lo;
+        *hi = e > *hi ? e : *hi;
+      }
+  });
+  return count;
+}
+}

@@ -332,3 +332,17 @@ def test_16x16x32_plan_transposed_reads_are_bank_conflict_free(plan):
                     byte = 2 * (plan.p16_frag_offset(lane, block) + half * 4 * ROW)
                     banks += [(byte // 4) % 64, (byte // 4 + 1) % 64]
                 assert len(set(banks)) == 64
+
+
+@pytest.mark.parametrize("n", [1, 255, 1023, 1024, 1025, 13824, 2 ** 31 - 1025, 2 ** 31 - 1024, 2 ** 31 - 256, 2 ** 31 - 2, 2 ** 31 - 1])
+def test_rows_up_to_the_longest_are_walked_once_and_stay_inside(plan, n):
+    # csrc/edge_plan.h: what the row kernels index with at T = 1, where features up to 2^31 - 1 are accepted
+    plan.ep_walk.restype = ctypes.c_long
+    for side in (64, 128):
+        assert plan.ep_tiles(n, side) == (n + side - 1) // side
+    for thread in (0, 1, 127, 254, 255):
+        lo, hi = ctypes.c_long(), ctypes.c_long()
+        count = plan.ep_walk(n, thread, ctypes.byref(lo), ctypes.byref(hi))
+        assert count == len(range(thread, n, 256))                   # every 256th element, each once
+        if count:
+            assert lo.value == thread and hi.value == range(thread, n, 256)[-1]
