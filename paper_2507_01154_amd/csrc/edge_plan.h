@@ -15,6 +15,9 @@ namespace edge_plan {
 // Tiles of the given side that cover n elements.
 FLASHDP_EP_HD int tiles(int n, int side) { return (int)(((int64_t)n + side - 1) / side); }
 
+// Whether `width` elements from column col on, col < n, lie inside a row of n.
+FLASHDP_EP_HD bool chunk_fits(int col, int n, int width) { return n - col >= width; }
+
 constexpr int WALK_STEP = 1024;   // elements of a row that one step of a workgroup of 256 threads takes
 
 // f(k) for every step of one thread through a row of n elements; the thread's elements of the step are

@@ -28,6 +28,8 @@
 #include <type_traits>
 #include <utility>
 
+#include "edge_plan.h"
+
 namespace flashdp {
 
 // Compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>).
@@ -165,7 +167,7 @@ __device__ __forceinline__ u32x4_t shift_down(const u32x4_t v, int s) {
 
 // 16-bit elements v[0..7] / floats v[0..3] to columns col.. of a row of P elements, those beyond the row left out.
 __device__ __forceinline__ void store_any(unsigned short* row, int col, int P, const u32x4_t v) {
-  if (col + 8 <= P) {
+  if (edge_plan::chunk_fits(col, P, 8)) {
     *(u32x4_any_t*)(row + col) = v;
   } else {
     for (int e = 0; e < 8 && col + e < P; ++e) row[col + e] = (unsigned short)(v[e >> 1] >> (16 * (e & 1)));
@@ -173,7 +175,7 @@ __device__ __forceinline__ void store_any(unsigned short* row, int col, int P, c
 }
 __device__ __forceinline__ void store_any(float* row, int col, int P, float4 v, bool add) {
   const float w[4] = {v.x, v.y, v.z, v.w};
-  if (col + 4 <= P && !add) {
+  if (edge_plan::chunk_fits(col, P, 4) && !add) {
     const f32x4_any_t q = {v.x, v.y, v.z, v.w};
     *(f32x4_any_t*)(row + col) = q;
   } else {

@@ -62,6 +62,7 @@ int p16_tile_base(int stage, int operand) { return flashdp::lds_plan16::tile_bas
 // Index arithmetic at the ends of very long rows.
 #include "../paper_2507_01154_amd/csrc/edge_plan.h"
 extern "C" {
+int ep_chunk_fits(int col, int n, int width) { return flashdp::edge_plan::chunk_fits(col, n, width); }
 int ep_tiles(int n, int side) { return flashdp::edge_plan::tiles(n, side); }
 // walks thread's share of a row; returns how many elements it takes, *lo and *hi the smallest and largest index among them
 long ep_walk(int n, int thread, long* lo, long* hi) {

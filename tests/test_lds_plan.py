@@ -346,3 +346,10 @@ def test_rows_up_to_the_longest_are_walked_once_and_stay_inside(plan, n):
         assert count == len(range(thread, n, 256))                   # every 256th element, each once
         if count:
             assert lo.value == thread and hi.value == range(thread, n, 256)[-1]
+
+
+@pytest.mark.parametrize("n", [8, 9, 15, 257, 2 ** 31 - 8, 2 ** 31 - 3, 2 ** 31 - 1])
+def test_a_chunk_is_written_whole_only_where_all_of_it_is_in_the_row(plan, n):
+    for width in (4, 8):
+        for col in range((n - 1) // width * width, max(-1, n - 40), -width):       # the chunks a tile's threads store, from the last
+            assert bool(plan.ep_chunk_fits(col, n, width)) == (col + width <= n), (col, n, width)
