@@ -1003,11 +1003,6 @@ int flashdp_linear_dp_grad_static(const void* X, const void* dY, int64_t B, int6
   char* ws = nullptr;
   st = static_scratch_ptr(dev, &ws);
   if (st != FLASHDP_OK) return st;
-  if (rows_ok(B, T, dtype)) {
-    HIP_TRY(run_rows(L, B, dtype, ws, static_cast<hipStream_t>(stream), false, true));
-    g_ctx.last_schedule = "rows";
-    return FLASHDP_OK;
-  }
   // Every part of the workspace a call reads it has written itself first (partials by the contraction, factors
   // by the clip kernel, the parked tiles by the spill), so nothing has to be cleared between calls.
   st = run_layer(L, B, T, dtype, FLASHDP_SCHEDULE_SCRATCH, ws, static_cast<hipStream_t>(stream), false, true);

@@ -65,3 +65,17 @@ def test_static_entry_point_rejects_what_does_not_fit():
     # exactly at the limit of what fits: B * S * 2 bytes of tiles plus the small header
     L = [dict(X=None, dY=None, d_in=768, d_out=3072, C=1.0, sigma=1.0, seed=0, layer=0, out_grad=None)]
     assert F.flashdp_workspace_bytes(L, 8, 1024, F.BF16, "scratch") <= F.flashdp_static_scratch_bytes()
+
+
+@pytest.mark.parametrize("B,P,D", [(1, 136, 40), (5, 136, 40), (4, 77, 131)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32])
+def test_static_entry_point_keeps_the_scratch_schedule_for_rows_without_a_sequence(B, P, D, dtype):
+    g = torch.Generator(device=DEV).manual_seed(B + P)
+    X, dY = (torch.randn((B, 1, n), generator=g, device=DEV).to(dtype) for n in (P, D))
+    out = [torch.full((D, P), float("nan"), device=DEV) for _ in range(2)]
+    norms = [torch.full((B,), float("nan"), device=DEV) for _ in range(2)]
+    F.flashdp_block_dp_grad([dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.7, seed=3, layer=2, out_grad=out[0], out_norms=norms[0])],
+                            B, 1, F.dtype_code(X), "scratch")
+    F.flashdp_linear_dp_grad_static(X, dY, B, 1, P, D, F.dtype_code(X), 1.0, 0.7, 3, 2, out[1], norms[1])
+    assert F.flashdp_last_schedule() == "scratch"
+    assert torch.equal(out[0], out[1]) and torch.equal(norms[0], norms[1])
