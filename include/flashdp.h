@@ -122,7 +122,7 @@ enum { FLASHDP_BF16 = 0, FLASHDP_F32 = 1, FLASHDP_F16 = 2 };
  *            G_i still computed once (flashdp_workspace_bytes_chunked sizes such a workspace).  Only a
  *            workspace too small for a single sample falls back to TWOPASS.  Rows without a sequence (T = 1) are
  *            outer products, G_i = dy_i x_i^T with n_i = |dy_i| |x_i|: AUTO takes norms and factors from the rows and
- *            forms the clipped sum as one product over the batch, whatever the workspace ("rows").        */
+ *            forms the clipped sum as one product over the batch in any workspace that TWOPASS accepts ("rows"). */
 enum { FLASHDP_SCHEDULE_AUTO = 0, FLASHDP_SCHEDULE_TWOPASS = 1, FLASHDP_SCHEDULE_SCRATCH = 2, FLASHDP_SCHEDULE_EXPLICIT = 3,
        FLASHDP_SCHEDULE_OVERLAP = 4, FLASHDP_SCHEDULE_GHOST = 5, FLASHDP_SCHEDULE_FUSED = 6 };
 

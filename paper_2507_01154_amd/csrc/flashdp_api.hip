@@ -501,7 +501,7 @@ size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype,
 }
 
 // Rows without a sequence (rows_dp.hip.h) are taken by every call that leaves the schedule to the library: nothing of
-// size B * P * D is moved, and the working memory (the clip factors) fits any workspace such a call accepts.
+// size B * P * D is moved, and the working memory (the clip factors) is less than the two-pass schedule's workspace.
 // Not for one 16-bit sample: parking it costs 2 + 2 bytes an element beside the 4 of the output, and the streaming kernel
 // writes the output as fast or faster (bf16, 4096 x 13824: 126 us against 128 to 137; two samples: 163, 125; fp32, one sample:
 // 192, 128).
@@ -816,8 +816,8 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
   const size_t need_overlap = 2 * scratch_need(B);
   char* ws = static_cast<char*>(workspace);
   size_t ws_bytes = workspace_bytes;
-  if (schedule == FLASHDP_SCHEDULE_AUTO && rows_ok(B, T, dtype)) {
-    if (workspace && workspace_bytes < need_small) return FLASHDP_WORKSPACE_TOO_SMALL;
+  // (a workspace smaller than the batch's partials may still hold a chunk of samples: the general way decides)
+  if (schedule == FLASHDP_SCHEDULE_AUTO && rows_ok(B, T, dtype) && (!workspace || workspace_bytes >= need_small)) {
     if (!workspace) {
       void* p = nullptr; size_t got = 0;
       st = owned_workspace(need_small, &p, &got);

@@ -225,6 +225,28 @@ def test_rows_without_a_sequence(shape, dtype):
     assert torch.equal(twice, 2.0 * once)
 
 
+def test_rows_without_a_sequence_take_any_workspace_that_holds_a_chunk():
+    # many samples of a small layer: a workspace for one parked sample is smaller than the batch's factors and partials
+    B, P, D = 2000, 10, 6
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X, dY = (torch.randn((B, 1, n), generator=g, device=DEV) for n in (P, D))
+    out, norms = (torch.empty(s, device=DEV) for s in ((D, P), (B,)))
+    L = [dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)]
+    want_n = X.double().norm(dim=2)[:, 0] * dY.double().norm(dim=2)[:, 0]
+    want = (dY.double()[:, 0] / want_n.clamp(min=1.0)[:, None]).T @ X.double()[:, 0]
+    small = F.flashdp_workspace_bytes(L, B, 1, F.F32, "twopass")
+    for n_ws, used in ((F.flashdp_workspace_bytes_chunked(L, B, 1, F.F32, 3, 1), "scratch"), (small, "rows")):
+        assert used == "rows" or n_ws < small
+        out.fill_(float("nan"))
+        F.flashdp_block_dp_grad(L, B, 1, F.F32, "auto", torch.empty((n_ws,), dtype=torch.uint8, device=DEV))
+        assert F.flashdp_last_schedule() == used
+        assert torch.allclose(norms.double(), want_n, rtol=1e-6)
+        assert float((out.double() - want).norm() / want.norm()) <= 5e-5
+    with pytest.raises(F.FlashDPError) as ei:
+        F.flashdp_block_dp_grad(L, B, 1, F.F32, "auto", torch.empty((512,), dtype=torch.uint8, device=DEV))
+    assert ei.value.status == F.WORKSPACE_TOO_SMALL
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_rows_without_a_sequence_that_are_not_finite_or_overflow(dtype):
     # G_i is not formed there, so what its elements would show has to show all the same
