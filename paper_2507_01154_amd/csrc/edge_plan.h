@@ -18,13 +18,13 @@ FLASHDP_EP_HD int tiles(int n, int side) { return (int)(((int64_t)n + side - 1) 
 // Whether `width` elements from column col on, col < n, lie inside a row of n.
 FLASHDP_EP_HD bool chunk_fits(int col, int n, int width) { return n - col >= width; }
 
-constexpr int WALK_STEP = 1024;   // elements of a row that one step of a workgroup of 256 threads takes
+constexpr int WALK_CHUNKS = 4;    // chunks of V elements that a thread takes in one step
 
-// f(k) for every step of one thread through a row of n elements; the thread's elements of the step are
-// k, k + 256, k + 512, k + 768 as far as they are below n.
-template <typename F>
+// f(k) for every step of one of 256 threads through a row of n elements; the thread's elements of the step are
+// k + 256 * V * q + 0..V-1 for q below WALK_CHUNKS, as far as they are below n.
+template <int V, typename F>
 FLASHDP_EP_HD void walk_row(int n, int thread, F f) {
-  for (uint32_t k = (uint32_t)thread; k < (uint32_t)n; k += WALK_STEP) f(k);
+  for (uint32_t k = (uint32_t)(thread * V); k < (uint32_t)n; k += 256 * V * WALK_CHUNKS) f(k);
 }
 
 }  // namespace edge_plan

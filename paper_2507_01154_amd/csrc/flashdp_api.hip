@@ -505,8 +505,12 @@ size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype,
 // Not for one 16-bit sample: parking it costs 2 + 2 bytes an element beside the 4 of the output, and the streaming kernel
 // writes the output as fast or faster (bf16, 4096 x 13824: 126 us against 128 to 137; two samples: 163, 125; fp32, one sample:
 // 192, 128).
-bool rows_ok(int64_t B, int64_t T, int dtype) {
-  return T == 1 && (B > 1 || dtype == FLASHDP_F32) && g_ctx.stages == FLASHDP_STAGE_ALL && env().tile == 0;
+// Nor for one or two samples with a long row on one side and a short one on the other, where one workgroup per sample
+// reads the long row for its norm: fp32, parked against rows, B = 1, 200000 x 8: 36, 51; 50257 x 128: 38, 44; B = 2,
+// 1000000 x 32: 302, 393; against 50257 x 768, B = 1: 156, 142; 1000000 x 8, B = 4: 443, 362; 13824 x 24, B = 1: 14.1, 11.3.
+bool rows_ok(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
+  if (T != 1 || (B == 1 && dtype != FLASHDP_F32) || g_ctx.stages != FLASHDP_STAGE_ALL || env().tile != 0) return false;
+  return B > 2 || std::max(P, D) <= 16384 || std::min(P, D) >= 512;
 }
 
 template <int DT>
@@ -816,8 +820,10 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
   const size_t need_overlap = 2 * scratch_need(B);
   char* ws = static_cast<char*>(workspace);
   size_t ws_bytes = workspace_bytes;
+  bool rows = schedule == FLASHDP_SCHEDULE_AUTO;
+  for (int l = 0; l < n_layers && rows; ++l) rows = rows_ok(B, T, layers[l].d_in, layers[l].d_out, dtype);
   // (a workspace smaller than the batch's partials may still hold a chunk of samples: the general way decides)
-  if (schedule == FLASHDP_SCHEDULE_AUTO && rows_ok(B, T, dtype) && (!workspace || workspace_bytes >= need_small)) {
+  if (rows && (!workspace || workspace_bytes >= need_small)) {
     if (!workspace) {
       void* p = nullptr; size_t got = 0;
       st = owned_workspace(need_small, &p, &got);

@@ -64,19 +64,26 @@ int p16_tile_base(int stage, int operand) { return flashdp::lds_plan16::tile_bas
 extern "C" {
 int ep_chunk_fits(int col, int n, int width) { return flashdp::edge_plan::chunk_fits(col, n, width); }
 int ep_tiles(int n, int side) { return flashdp::edge_plan::tiles(n, side); }
-// walks thread's share of a row; returns how many elements it takes, *lo and *hi the smallest and largest index among them
-long ep_walk(int n, int thread, long* lo, long* hi) {
+// walks one thread's share of a row in chunks of v (1, 4 or 8); returns how many elements it takes, *lo and *hi the smallest
+// and largest index among them, *sum the sum of all of them
+long ep_walk(int n, int thread, int v, long* lo, long* hi, long* sum) {
   long count = 0;
-  *lo = 1L << 62; *hi = -1;
-  flashdp::edge_plan::walk_row(n, thread, [&](auto k) {
-    for (int q = 0; q < 4; ++q)
-      if (k + 256 * q < (decltype(k))n) {
-        const long e = (long)(decltype(k))(k + 256 * q);
-        ++count;
-        *lo = e < *lo ? e : *lo;
-        *hi = e > *hi ? e : *hi;
+  *lo = 1L << 62; *hi = -1; *sum = 0;
+  auto take = [&](auto k) {
+    for (int q = 0; q < flashdp::edge_plan::WALK_CHUNKS; ++q)
+      for (int e = 0; e < v; ++e) {
+        const auto at = k + 256 * v * q + e;
+        if (at < (decltype(at))n) {
+          ++count;
+          *lo = (long)at < *lo ? (long)at : *lo;
+          *hi = (long)at > *hi ? (long)at : *hi;
+          *sum += (long)at;
+        }
       }
-  });
+  };
+  if (v == 1) flashdp::edge_plan::walk_row<1>(n, thread, take);
+  else if (v == 4) flashdp::edge_plan::walk_row<4>(n, thread, take);
+  else flashdp::edge_plan::walk_row<8>(n, thread, take);
   return count;
 }
 }

@@ -225,6 +225,25 @@ def test_rows_without_a_sequence(shape, dtype):
     assert torch.equal(twice, 2.0 * once)
 
 
+@pytest.mark.parametrize("B,P,D,dtype,used", [(1, 16388, 12, torch.float32, "scratch"), (2, 11, 20001, torch.bfloat16, "scratch"),
+                                              (1, 16384, 12, torch.float32, "rows"), (4, 2048, 2049, torch.float32, "rows"),
+                                              (4, 2047, 2051, torch.float16, "rows"), (3, 11, 20001, torch.bfloat16, "rows"),
+                                              (2, 17001, 512, torch.float32, "rows")])
+def test_rows_without_a_sequence_that_are_long(B, P, D, dtype, used):
+    g = torch.Generator(device=DEV).manual_seed(P)
+    X, dY = (torch.randn((B, 1, n), generator=g, device=DEV).to(dtype) for n in (P, D))
+    out, norms = torch.full((D, P), float("nan"), device=DEV), torch.full((B,), float("nan"), device=DEV)
+    F.flashdp_block_dp_grad([dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)],
+                            B, 1, F.dtype_code(X), "auto")
+    assert F.flashdp_last_schedule() == used
+    x, y = X.double()[:, 0], dY.double()[:, 0]
+    n = x.norm(dim=1) * y.norm(dim=1)
+    want = (y / n[:, None]).T @ x
+    # scratch: norms of fp32 sums or of 2^16 or more values parked as bfloat16, 1e-4 as stated at the head of this file
+    assert float(((norms - n) / n).abs().max()) <= (2e-7 if used == "rows" else 1e-4)
+    assert float((out - want).norm() / want.norm()) <= (4e-3 if used == "scratch" and dtype != torch.float32 else 2e-6)
+
+
 def test_rows_without_a_sequence_take_any_workspace_that_holds_a_chunk():
     # many samples of a small layer: a workspace for one parked sample is smaller than the batch's factors and partials
     B, P, D = 2000, 10, 6

@@ -340,12 +340,15 @@ def test_rows_up_to_the_longest_are_walked_once_and_stay_inside(plan, n):
     plan.ep_walk.restype = ctypes.c_long
     for side in (64, 128):
         assert plan.ep_tiles(n, side) == (n + side - 1) // side
-    for thread in (0, 1, 127, 254, 255):
-        lo, hi = ctypes.c_long(), ctypes.c_long()
-        count = plan.ep_walk(n, thread, ctypes.byref(lo), ctypes.byref(hi))
-        assert count == len(range(thread, n, 256))                   # every 256th element, each once
-        if count:
-            assert lo.value == thread and hi.value == range(thread, n, 256)[-1]
+    for v in (1, 4, 8):
+        for thread in (0, 1, 127, 254, 255):
+            lo, hi, total = ctypes.c_long(), ctypes.c_long(), ctypes.c_long()
+            count = plan.ep_walk(n, thread, v, ctypes.byref(lo), ctypes.byref(hi), ctypes.byref(total))
+            parts = [range(thread * v + e, n, 256 * v) for e in range(v)]          # the thread's chunk of every 256 v elements
+            assert count == sum(len(p) for p in parts)
+            assert total.value == sum(len(p) * (p[0] + p[-1]) // 2 for p in parts if len(p))
+            if count:
+                assert lo.value == thread * v and hi.value == max(p[-1] for p in parts if len(p))
 
 
 @pytest.mark.parametrize("n", [8, 9, 15, 257, 2 ** 31 - 8, 2 ** 31 - 3, 2 ** 31 - 1])
