@@ -308,6 +308,12 @@ __global__ __launch_bounds__(256) void explicit_clip_kernel(float* __restrict__ 
 // Stage 4: out = sum_i G'_i + noise (one Philox group of 4 elements per thread).  With `factors` the clip
 // factor is applied here instead (out = sum_i c_i G_i + noise): the aggregation of the scratch schedule
 // for fp32 inputs, whose scratch is fp32 as well.
+// With S no multiple of 4 the samples start at any 4-byte address, which the loads allow.  Neighbouring threads' groups
+// then share cache lines, and a load that passes the caches by (STREAM) fetches them again: aggregate32_streams takes it
+// for such samples only where the caches (256 MB) could not hold them (fp32, one call, through the caches and past them:
+// 257 x 130, B = 256, 168 and 205 us; 1999 x 2001, B = 16, 127 and 137, B = 64, 655 and 583).
+inline bool aggregate32_streams(int64_t B, size_t S) { return S % 4 == 0 || (size_t)B * S >= ((size_t)1 << 26); }
+template <bool STREAM>
 __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restrict__ G, const float* __restrict__ factors, int B,
                                                           size_t S, float noise_scale, uint64_t seed, uint32_t layer,
                                                           float* __restrict__ out, int accumulate) {
@@ -315,7 +321,7 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
   const size_t e = g4 * 4;
   if (e >= S) return;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  const bool vec = e + 3 < S;   // with S no multiple of 4 the samples start at any 4-byte address, which the loads allow
+  const bool vec = e + 3 < S;
   if (accumulate) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -325,7 +331,9 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
     const float* g = G + (size_t)i * S + e;
     const float c = factors ? factors[i] : 1.0f;
     if (vec) {
-      const f32x4_any_t v = __builtin_nontemporal_load((const f32x4_any_t*)g);
+      f32x4_any_t v;
+      if constexpr (STREAM) v = __builtin_nontemporal_load((const f32x4_any_t*)g);
+      else v = *(const f32x4_any_t*)g;
       acc[0] = fmaf(c, v.x, acc[0]); acc[1] = fmaf(c, v.y, acc[1]); acc[2] = fmaf(c, v.z, acc[2]); acc[3] = fmaf(c, v.w, acc[3]);
     } else {
 #pragma unroll

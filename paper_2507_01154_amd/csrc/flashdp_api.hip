@@ -382,7 +382,8 @@ hipError_t launch_aggregate(int dtype, const void* scratch, const float* factors
   } else {
     const size_t groups = (S + 3) / 4;
     const unsigned grid = (unsigned)((groups + 255) / 256);
-    hipLaunchKernelGGL(aggregate32_kernel, dim3(grid), dim3(256), 0, st, (const float*)scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
+    auto kern = aggregate32_streams(B, S) ? aggregate32_kernel<true> : aggregate32_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const float*)scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
   }
   return hipGetLastError();
 }
@@ -709,7 +710,8 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
       HIP_TRY(hipGetLastError());
     }
     if (stages & FLASHDP_STAGE_AGGREGATE) {
-      hipLaunchKernelGGL(aggregate32_kernel, dim3((unsigned)(((S + 3) / 4 + 255) / 256)), dim3(256), 0, st, G, (const float*)nullptr, (int)B, S,
+      auto kern = aggregate32_streams(B, S) ? aggregate32_kernel<true> : aggregate32_kernel<false>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)(((S + 3) / 4 + 255) / 256)), dim3(256), 0, st, G, (const float*)nullptr, (int)B, S,
                          noise_scale, L.seed, L.layer, L.out_grad, accumulate ? 1 : 0);                                                             // stage 4
       HIP_TRY(hipGetLastError());
     }

@@ -168,6 +168,21 @@ def test_sizes_no_vector_width_divides(dtype, shape, schedule):
     assert F.flashdp_last_kernel() == ("gemm_mfma_f32_kernel" if dtype == "fp32" else "gemm_mfma_kernel")
 
 
+@pytest.mark.parametrize("B,P,D", [(17, 1999, 2001), (16, 1999, 2001), (17, 1999, 2004)])
+def test_fp32_samples_that_no_cache_holds_are_summed_past_the_caches(B, P, D):
+    # both forms of the fp32 aggregation, with and without samples that start between two 16-byte groups; fp64 on the GPU
+    g = torch.Generator(device=DEV).manual_seed(D)
+    X, dY = torch.randn((B, 2, P), generator=g, device=DEV), torch.randn((B, 2, D), generator=g, device=DEV)
+    out, norms = torch.full((D, P), float("nan"), device=DEV), torch.empty((B,), device=DEV)
+    F.flashdp_block_dp_grad([dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)],
+                            B, 2, F.F32, "scratch")
+    want = torch.zeros((D, P), dtype=torch.float64, device=DEV)
+    for i in range(B):
+        G = dY[i].double().T @ X[i].double()
+        want += G / G.norm().clamp(min=1.0)
+    assert float((out - want).norm() / want.norm()) <= 5e-5
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("B,T,dims", [(1, 100, [(136, 264), (8, 8), (768, 128)]), (3, 33, [(256, 384)] * 9), (2, 64, [(130, 257), (128, 64), (264, 72)])])
 def test_layers_of_a_call_are_those_of_single_calls(B, T, dims, dtype):
