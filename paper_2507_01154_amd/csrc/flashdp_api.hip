@@ -166,15 +166,25 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   Plan p;
   const bool mfma_ok = dtype != FLASHDP_F32 && P % 8 == 0 && D % 8 == 0 &&
                        (T + 320) * (P > D ? P : D) * 2 < (int64_t(1) << 31);   // incl. the parked prefetches past the end
-  // fp32 inputs: fp32 matrix-core kernel when rows are 16-byte multiples and the problem spans a few tiles
-  // Features that are no multiple of 4: the same kernel in its unaligned form where its 256x256 tiles are at most half
-  // padding and the generic kernel's 64x64 ones would already fill half the chip (measured, fp32: 5 x 1097 x 2313,
-  // T = 333: 123 us against 267; 2 x 2000 x 77, T = 2048 - 128 tiles -: 493 against 814; 2 x 515 x 129 - 54 tiles -:
-  // 60 against 39, stays with the generic one).
-  auto padded = [&](int64_t b) { return (P + b - 1) / b * b * ((D + b - 1) / b * b); };
-  const bool f32_any = P >= 4 && D >= 4 && padded(256) <= 2 * padded(64) && padded(64) / 4096 * B >= 128;
-  const bool f32_ok = dtype == FLASHDP_F32 && ((P % 4 == 0 && D % 4 == 0) || f32_any) && P * D >= 128 * 128 &&
-                      (T + 48) * (P > D ? P : D) * 4 < (int64_t(1) << 31) && env().tile != -1;
+  // fp32 inputs: fp32 matrix-core kernel when rows are 16-byte multiples and the problem spans a few tiles.
+  // Features that are no multiple of 4: the same kernel in its unaligned form where it is the faster one.  A round of one
+  // 256x256 tile per CU takes it as long as the generic kernel takes for a third of that area (in 64x64 tiles), so the
+  // rounds decide, of the tiles of all samples or, in the accumulating pass, of one (fp32, generic against matrix cores:
+  // 3001 x 3001, B = 1, T = 2048: 923 us, 509; 769 x 1025, B = 8, T = 333: 112, 102; 255 x 255, T = 64, B = 128: 113, 82;
+  // left with the generic one: 2222 x 2222, B = 1, T = 2048: 462, 503; 1001 x 1001, B = 4, T = 512: 131, 145; 257 x 3001,
+  // B = 2, T = 1024: 215, 257; 2000 x 77, B = 2, T = 2048: 409, 495; accumulating pass: 3001 x 3001: 838, 490; 768 x 5025,
+  // B = 2, T = 1024: 411, 474; 500 x 250, B = 200, T = 8: 426, 755).
+  auto tiles_of = [&](int64_t b) { return ((P + b - 1) / b) * ((D + b - 1) / b); };
+  auto cu_count = [] { const int n = device_cus(); return (int64_t)(n > 0 ? n : 256); };   // sizing calls may come before a device is there
+  auto f32_any = [&](int64_t samples) {
+    const int64_t cus = cu_count();
+    const int64_t rounds = (tiles_of(256) * samples + cus - 1) / cus;
+    return P >= 4 && D >= 4 && rounds * cus * 256 * 256 <= 3 * tiles_of(64) * 64 * 64 * samples;
+  };
+  const bool f32_fits = dtype == FLASHDP_F32 && P * D >= 128 * 128 && (T + 48) * (P > D ? P : D) * 4 < (int64_t(1) << 31) &&
+                        env().tile != -1;
+  const bool f32_aligned = P % 4 == 0 && D % 4 == 0;
+  const bool f32_ok = f32_fits && (f32_aligned || f32_any(B));
   // 16-bit inputs of other sizes: the register-staged kernels with 2-byte aligned accesses.  Bound by the rate of the
   // staged main loop (about 0.6 of the direct-to-LDS one); the generic kernel on the vector ALUs is 2 to 17 times slower
   // (768 x 50257, B = 2, T = 1024: 287 us against 2800; 130 x 257, B = 8, T = 64: 16 against 32) and is kept for rows
@@ -182,14 +192,15 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   // B = 4, T = 16: 11 us against 13).
   const bool any16_ok = dtype != FLASHDP_F32 && (P % 8 != 0 || D % 8 != 0) && P >= 8 && D >= 8 && env().tile != -1 &&
                         !(P <= 64 && D <= 64 && T <= 32);
-  p.any = any16_ok || (f32_ok && (P % 4 != 0 || D % 4 != 0));
+  p.any = any16_ok || (f32_ok && !f32_aligned);
   if (any16_ok) {
     const int64_t tiles = ((D + 255) / 256) * ((P + 255) / 256);
     p.path = tiles * B >= 128 ? PATH_256x8k32 : PATH_128x4;
     p.accum_path = tiles >= 128 ? p.path : PATH_128x4;
     p.bm = p.bn = p.path == PATH_128x4 ? 128 : 256;
   } else if (f32_ok) {
-    p.path = p.accum_path = PATH_F32; p.bm = p.bn = 256;
+    p.path = PATH_F32; p.bm = p.bn = 256;
+    p.accum_path = f32_aligned || f32_any(1) ? PATH_F32 : PATH_SIMPLE;
   } else if (!mfma_ok) {
     p.path = p.accum_path = PATH_SIMPLE; p.bm = 64; p.bn = 64;
   } else {
@@ -214,7 +225,7 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
         // 384x192 or 192x384 tiles (9/8 the work of a 256x256 one) need enough fewer rounds, they are taken
         // (3072 x 768 at B = 8: 288 items = 2 rounds, against 256 = 1 round of 1.125).  A clear margin is asked for:
         // the 256x256 kernel is the one tuned and measured on the large layers.
-        const int64_t cus = device_cus() > 0 ? device_cus() : 256;   // sizing calls may come before a device is there
+        const int64_t cus = cu_count();
         auto rounds = [&](int64_t bm, int64_t bn) { return (((D + bm - 1) / bm) * ((P + bn - 1) / bn) * B + cus - 1) / cus; };
         const double c256 = (double)rounds(256, 256), ca = 1.125 * rounds(384, 192), cb = 1.125 * rounds(192, 384);
         if (std::min(ca, cb) <= 0.9 * c256) choice = ca <= cb ? PATH_DMA_384x192 : PATH_DMA_192x384;
@@ -233,8 +244,9 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   }
   p.tiles_m = (int)((D + p.bm - 1) / p.bm);
   p.tiles_n = (int)((P + p.bn - 1) / p.bn);
-  const int abm = (p.accum_path == p.path) ? p.bm : p.accum_path == PATH_128x4 ? 128 : 256;
-  const int abn = (p.accum_path == p.path) ? p.bn : p.accum_path == PATH_128x4 ? 128 : 256;
+  const int ab = p.accum_path == PATH_128x4 ? 128 : p.accum_path == PATH_SIMPLE ? 64 : 256;
+  const int abm = (p.accum_path == p.path) ? p.bm : ab;
+  const int abn = (p.accum_path == p.path) ? p.bn : ab;
   p.accum_tiles_m = (int)((D + abm - 1) / abm);
   p.accum_tiles_n = (int)((P + abn - 1) / abn);
   return p;
@@ -351,8 +363,9 @@ hipError_t launch_gemm_dt(const Plan& p, const GemmArgs& args, hipStream_t st) {
   const int tiles = a.tiles_m * a.tiles_n;
   const int grid = (MODE == MODE_ACCUM) ? tiles : tiles * a.B;
   if constexpr (DT == DT_F32) {
-    if (p.path == PATH_F32 && p.any) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE, true>, MODE, a, st, /*lockstep=*/true);
-    if (p.path == PATH_F32) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE>, MODE, a, st, /*lockstep=*/true);
+    const bool f32 = (MODE == MODE_ACCUM ? p.accum_path : p.path) == PATH_F32;
+    if (f32 && p.any) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE, true>, MODE, a, st, /*lockstep=*/true);
+    if (f32) return launch_tiled<F32Cfg>(gemm_mfma_f32_kernel<MODE>, MODE, a, st, /*lockstep=*/true);
   }
   hipLaunchKernelGGL((gemm_simple_kernel<MODE, DT>), dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();

@@ -120,6 +120,22 @@ def test_tile_shape_follows_the_rounds_of_equally_long_work_items(monkeypatch):
     assert partial_bytes(1024, 3072, 8, 1024) == up(8 * 48 * 4)
 
 
+def test_fp32_sizes_no_multiple_of_4_take_the_kernel_that_is_faster_there():
+    # read off the norm partials as above (64 x 64 tiles: generic kernel, 256 x 256: matrix cores); 256 compute units
+    def tiles(p, d, B, T):
+        L = [dict(X=None, dY=None, d_in=p, d_out=d, C=1.0, sigma=1.0, seed=0, layer=0, out_grad=None)]
+        up = lambda n: (n + 255) // 256 * 256
+        n = F.flashdp_workspace_bytes(L, B, T, F.F32, "twopass") - up(4 * B)
+        t = lambda b: -(-p // b) * -(-d // b)
+        assert n in (up(4 * B * t(64)), up(4 * B * t(256)))
+        return 64 if n == up(4 * B * t(64)) else 256
+
+    for shape, side in (((1001, 1001, 4, 512), 64), ((257, 3001, 2, 1024), 64), ((255, 255, 64, 512), 64), ((200, 90, 64, 256), 64),
+                        ((1001, 1001, 64, 16), 256), ((3001, 3001, 1, 2048), 256), ((255, 255, 128, 64), 256), ((769, 1025, 8, 333), 256),
+                        ((512, 512, 8, 64), 256), ((2222, 2222, 1, 2048), 64), ((509, 255, 40, 37), 64), ((509, 255, 44, 37), 256), ((3, 40000, 8, 64), 64)):
+        assert tiles(*shape) == side, shape
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="only meaningful on a host without a GPU")
 def test_no_device_is_an_error_not_a_crash():
     assert F.lib().flashdp_linear_dp_grad(A, B_, 1, 1, 8, 8, 1.0, 0.0, 0, O_, None) == F.NO_DEVICE
