@@ -43,9 +43,11 @@
  *     factor and so turns the whole of out_grad into NaN (it is never let through unclipped).
  *     A per-sample gradient that overflows fp32 (infinite norm) poisons out_grad with NaN/Inf under every
  *     schedule, and where T = 1 under AUTO, which forms no G_i, too (every element is then NaN).  A clip factor too
- *     small for a normal float is rounded towards zero, so that the clipped sample stays within C.  TWOPASS and GHOST rescale the running sum by c_i / c_(i+1) at sample boundaries; two
- *     consecutive clip factors further apart than about 1e38 (a norm beyond 1e38 * C) overflow that ratio and
- *     give Inf/NaN as well, where SCRATCH / OVERLAP / EXPLICIT still give the finite result.
+ *     small for a normal float is rounded towards zero, so that the clipped sample stays within C.  TWOPASS and GHOST
+ *     rescale the running sum by c_i / c_(i+1) at sample boundaries where d_in and d_out are multiples of 8 (16-bit types)
+ *     or 4 (fp32); two consecutive clip factors further apart than about 1e38 (a norm beyond 1e38 * C, or one whose square
+ *     overflows fp32, beyond 1.8e19) overflow that ratio and give Inf/NaN as well, where other sizes and SCRATCH / OVERLAP /
+ *     EXPLICIT still give the finite result, with that sample's factor 0.
  *   - Return value: FLASHDP_OK (0) or a negative flashdp_status.  Argument errors (everything but
  *     FLASHDP_HIP_ERROR) are found before anything is enqueued; a FLASHDP_HIP_ERROR comes from the runtime
  *     while enqueuing, and kernels of earlier layers or stages of the same call may then already be enqueued:

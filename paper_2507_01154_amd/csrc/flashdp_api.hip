@@ -196,11 +196,14 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   if (any16_ok) {
     const int64_t tiles = ((D + 255) / 256) * ((P + 255) / 256);
     p.path = tiles * B >= 128 ? PATH_256x8k32 : PATH_128x4;
-    p.accum_path = tiles >= 128 ? p.path : PATH_128x4;
+    // batches: the tiling whose accumulating pass keeps its total apart from the sample in progress (accum_totals; bf16,
+    // 4 x 4001 x 4001, T = 512, two-pass: 241 us, 175 and twice the error on 256 x 256 tiles, 2601 with the generic kernel)
+    p.accum_path = tiles >= 128 && B == 1 ? p.path : PATH_128x4;
     p.bm = p.bn = p.path == PATH_128x4 ? 128 : 256;
   } else if (f32_ok) {
     p.path = PATH_F32; p.bm = p.bn = 256;
-    p.accum_path = f32_aligned || f32_any(1) ? PATH_F32 : PATH_SIMPLE;
+    // (batches of unaligned rows: the generic kernel, which keeps its total apart from the sample in progress)
+    p.accum_path = f32_aligned || (f32_any(1) && B == 1) ? PATH_F32 : PATH_SIMPLE;
   } else if (!mfma_ok) {
     p.path = p.accum_path = PATH_SIMPLE; p.bm = 64; p.bn = 64;
   } else {

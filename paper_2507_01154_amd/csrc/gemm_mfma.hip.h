@@ -337,6 +337,14 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& a, f32x16_t (&acc)
   }
 }
 
+// Whether the batch-accumulating pass keeps the total sum_i c_i G_i in accumulators of its own, beside the sample in
+// progress (64 registers more at 64 x 64 per wave): no rounding of earlier samples at sample boundaries, no sample's
+// products added to a large total one by one, and a clip factor of 0 is harmless.  The 256 x 256 tilings have no registers
+// left for that and rescale by c_i / c_(i+1) instead; with unaligned rows they take single samples only, where the two
+// are the same.  (Relative error against fp64, two-pass, bf16, 64 x 300 x 30, T = 128: 6.1e-7 rescaled, 1.6e-7 so.)
+template <typename Cfg, int MODE, bool ANY>
+constexpr bool accum_totals = MODE == MODE_ACCUM && ANY && Cfg::FM * Cfg::FN <= 4;
+
 // bid: which of the layer's workgroups this one is.
 template <typename Cfg, int MODE, int DT, bool ANY>
 __device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
@@ -452,6 +460,18 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
+  constexpr bool TOTALS = accum_totals<Cfg, MODE, ANY>;
+  f32x16_t tot[TOTALS ? FM : 1][TOTALS ? FN : 1];
+  int sample = 0, sample_end = kt_per_sample;   // the sample in progress and the k-tile after its last
+  if constexpr (TOTALS) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tot[i][j][e] = 0.0f;
+  }
+
   // Fragments are double-buffered: the transposed LDS reads of k-step ks+1 are issued before the
   // matrix-core work of k-step ks, and the first reads of the next k-tile right after the barrier,
   // ahead of the last k-step of this tile.
@@ -503,7 +523,22 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
         for (int j = 0; j < FN; ++j) acc[i][j] = mfma32<DT>(fb[cb][j], fa[cb][i], acc[i][j]);
       sched_interleave<0, N_MMA, N_RD, do_store ? CA + CB : 0, do_fetch ? CA + CB : 0>();
     });
-    if constexpr (MODE == MODE_ACCUM) {
+    if constexpr (TOTALS) {
+      if (k + 1 == sample_end && sample < n_samples) {
+        const float c = a.factors != nullptr ? a.factors[sample] : 1.0f;
+        ++sample;
+        sample_end += kt_per_sample;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              tot[i][j][e] = fmaf(c, acc[i][j][e], tot[i][j][e]);
+              acc[i][j][e] = 0.0f;
+            }
+      }
+    } else if constexpr (MODE == MODE_ACCUM) {
       // sample boundary: rescale so that acc always holds sum_{j<=i} (c_j / c_i) G_j; exact up to one
       // fp32 rounding per boundary, and needs no second set of accumulators
       if (a.factors != nullptr && k < nk && (k + 1) % kt_per_sample == 0) {
@@ -518,7 +553,7 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
       }
     }
   };
-  if constexpr (KS >= 4) {
+  if constexpr (KS >= 4 && !TOTALS) {   // (with totals the doubled boundary code costs more: 768 x 10, B = 8, T = 1024: 125 us, 114)
     // 64-deep k-tiles: two k-tiles per loop trip with the LDS stage a compile-time constant (measured 3 %
     // faster); an odd tile count runs one extra k-tile on the zeros the parked fetch cursor delivers.
     for (int k = 0; k < nk; k += 2) {
@@ -530,6 +565,12 @@ __device__ __forceinline__ void gemm_mfma_body(const GemmArgs& a, int bid) {
     for (int k = 0; k < nk; ++k) k_tile(k, k & 1);
   }
   __syncthreads();   // the reduction below reuses the LDS tiles
+  if constexpr (TOTALS) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = tot[i][j];
+  }
 
   tile_epilogue<Cfg, MODE, DT, ANY>(a, acc, lds, m0, n0, sample0, tile, tiles);
 }

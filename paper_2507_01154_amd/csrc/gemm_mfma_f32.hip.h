@@ -162,7 +162,7 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a)
       // instructions instead of in front of the ones that consume them
       sched_interleave<0, FM * FN, FM + FN, do_store ? C::CA + C::CB : 0, do_fetch ? C::CA + C::CB : 0>();
     });
-    if constexpr (MODE == MODE_ACCUM) {
+    if constexpr (MODE == MODE_ACCUM) {   // (ANY: single samples only, so that there is no boundary to rescale at)
       // sample boundary: keep acc = sum_{j<=i} (c_j / c_i) G_j (see the 16-bit kernel)
       if (a.factors != nullptr && (k + 1) % kt_per_sample == 0) {
         const int s = k / kt_per_sample;

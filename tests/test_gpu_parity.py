@@ -185,6 +185,53 @@ def test_fp32_samples_that_no_cache_holds_are_summed_past_the_caches(B, P, D):
     assert float((out - want).norm() / want.norm()) <= 5e-5
 
 
+@pytest.mark.parametrize("dtype,B,T,P,D", [(torch.bfloat16, 64, 128, 300, 30), (torch.bfloat16, 8, 1024, 768, 10), (torch.float16, 4, 200, 4001, 2049),
+                                           (torch.float32, 44, 37, 509, 255), (torch.float32, 3, 100, 2222, 3333)])
+def test_accumulation_of_unaligned_sizes_adds_whole_samples(dtype, B, T, P, D):
+    # Each sample is summed by itself and then added to the total.  A sum of T products in steps of 8 to 16 rounds T / 8
+    # times at the size it has grown to, 2^-24 / sqrt(3) each: 3e-7 of the result for T = 1024, less for fewer, and B
+    # additions add as much for B = 64.  (All B * T products in one running sum: 6e-7 to 7e-7 on these shapes.)
+    g = torch.Generator(device=DEV).manual_seed(P)
+    x, y = torch.randn((B, T, P), generator=g, device=DEV).to(dtype), (0.05 * torch.randn((B, T, D), generator=g, device=DEV)).to(dtype)
+    out = [torch.full((D, P), float("nan"), device=DEV) for _ in range(2)]
+    F.flashdp_plain_grad(x, y, B, T, P, D, F.dtype_code(x), out[0])
+    F.flashdp_block_dp_grad([dict(X=x, dY=y, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out[1], out_norms=None)],
+                            B, T, F.dtype_code(x), "twopass")
+    want = torch.zeros((2, D, P), dtype=torch.float64, device=DEV)
+    for i in range(B):
+        G = y[i].double().T @ x[i].double()
+        want[0] += G
+        want[1] += G / G.norm().clamp(min=1.0)
+    for o, w in zip(out, want):
+        assert float((o - w).norm() / w.norm()) <= 3.5e-7
+
+
+@pytest.mark.parametrize("schedule,scale,C", [("twopass", 1e13, 1.0), ("twopass", 1e7, 1e-30), ("ghost", 1e7, 1e-30)])
+@pytest.mark.parametrize("dtype,B,T,P,D", [(torch.bfloat16, 5, 37, 77, 131), (torch.bfloat16, 4, 70, 136, 257), (torch.bfloat16, 3, 20, 4001, 2049),
+                                           (torch.float32, 5, 37, 77, 131), (torch.float32, 44, 37, 509, 255), (torch.float32, 3, 9, 4001, 2049)])
+def test_accumulation_of_unaligned_sizes_survives_a_factor_of_zero(dtype, B, T, P, D, schedule, scale, C):
+    # one sample's clip factor is 0 (its norm is beyond what fp32 sums of squares hold, or 1e45 times C), its elements are
+    # finite: the other samples' sum has to stay what it is, wherever in the batch that sample stands (a total rescaled by
+    # c_i / c_(i+1) would not)
+    g = torch.Generator(device=DEV).manual_seed(P)
+    x0, y0 = torch.randn((B, T, P), generator=g, device=DEV), 0.05 * torch.randn((B, T, D), generator=g, device=DEV)
+    for at in (0, 1, B - 1):
+        x, y = x0.clone(), y0.clone()
+        x[at] *= scale
+        y[at] *= scale
+        x, y = x.to(dtype), y.to(dtype)
+        out, norms = torch.full((D, P), float("nan"), device=DEV), torch.empty((B,), device=DEV)
+        F.flashdp_block_dp_grad([dict(X=x, dY=y, d_in=P, d_out=D, C=C, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)],
+                                B, T, F.dtype_code(x), schedule)
+        want = torch.zeros((D, P), dtype=torch.float64, device=DEV)
+        for i in range(B):
+            if i != at:
+                G = y[i].double().T @ x[i].double()
+                want += G / (G.norm() / C).clamp(min=1.0)
+        assert float(norms[at]) / C > 1.5e45
+        assert float((out - want).norm() / want.norm()) <= 5e-5, at
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("B,T,dims", [(1, 100, [(136, 264), (8, 8), (768, 128)]), (3, 33, [(256, 384)] * 9), (2, 64, [(130, 257), (128, 64), (264, 72)])])
 def test_layers_of_a_call_are_those_of_single_calls(B, T, dims, dtype):
