@@ -390,7 +390,9 @@ hipError_t launch_aggregate(int dtype, const void* scratch, const float* factors
     hipLaunchKernelGGL((aggregate16_persistent_kernel<DT_BF16>), dim3(persistent_grid), dim3(256), 0, st, scratch, factors, B, S, n8, noise_scale, seed, layer, out, accumulate);
     return hipGetLastError();
   }
-  if (dtype != FLASHDP_F32) {   // the scratch of both 16-bit input types is bfloat16
+  if (dtype != FLASHDP_F32 && S < 8) {   // the scratch of both 16-bit input types is bfloat16
+    hipLaunchKernelGGL((aggregate16_tiny_kernel<DT_BF16>), dim3(1), dim3(64), 0, st, scratch, factors, B, (int)S, noise_scale, seed, layer, out, accumulate);
+  } else if (dtype != FLASHDP_F32) {
     const size_t n8 = (S + 7) / 8;
     const unsigned grid = (unsigned)((n8 + 255) / 256);
     auto kern = S % 8 == 0 ? aggregate16_kernel<DT_BF16, false> : aggregate16_kernel<DT_BF16, true>;
@@ -741,7 +743,7 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
     // schedule always qualifies.
     const size_t n8_all = (S + 7) / 8, full_grid = (n8_all + 255) / 256;
     const size_t agg_grid = persistent_grid > 0 ? std::min((size_t)persistent_grid, full_grid) : full_grid;
-    const bool fold_clip = fold_clip_ok(dtype, B, tiles, agg_grid) &&
+    const bool fold_clip = S >= 8 && fold_clip_ok(dtype, B, tiles, agg_grid) &&
                            (stages & (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE)) == (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE);
     if (fold_clip) {
       auto kern = persistent_grid > 0 ? clip_aggregate16_kernel<DT_BF16, false>   // (S is a multiple of 8 there)

@@ -185,6 +185,33 @@ def test_fp32_samples_that_no_cache_holds_are_summed_past_the_caches(B, P, D):
     assert float((out - want).norm() / want.norm()) <= 5e-5
 
 
+@pytest.mark.parametrize("B", [1, 3, 70])
+@pytest.mark.parametrize("P,D", [(9, d) for d in range(8, 16)] + [(3, 3), (1, 1), (2, 3), (7, 1), (1, 8), (67, 31)])
+def test_last_group_of_the_16_bit_aggregation(B, P, D):
+    # every remainder of the layer's size by eight, layers of fewer than eight elements, clip factors worked out by the
+    # aggregation itself (up to 64 samples) and before it; noise; a second micro-batch added to the first
+    rng = np.random.default_rng(B * 100 + P * D)
+    X = W.float32_to_bf16_bits(rng.standard_normal((B, 5, P)).astype(np.float32))
+    dY = W.float32_to_bf16_bits((rng.standard_normal((B, 5, D)) * 0.3).astype(np.float32))
+    sig, wn, bound = oracle_signal_and_bound(X, dY, 1.0)
+    z = O.noise_field(9, 2, D * P).reshape(D, P)
+    for sigma in (0.0, 0.5):
+        got, gn, _ = run_layer(X, dY, 1.0, sigma, 9, 2, "scratch")
+        # a value parked as bfloat16 moves by up to 2^-8 of itself, and so does a norm of few values; noise as elsewhere here
+        assert np.all(np.abs(gn - wn) <= (2.0 ** -8 + 1e-6) * wn)
+        assert np.all(np.abs(got - sig - sigma * z) <= 2.0 ** -7 * bound + 4e-6)
+    dX, ddY = to_device(X), to_device(dY)
+    out = torch.full((D * P + 8,), float("nan"), device=DEV)
+    L = [dict(X=dX, dY=ddY, d_in=P, d_out=D, C=1.0, sigma=0.5, seed=9, layer=2, out_grad=out, out_norms=None)]
+    F.flashdp_block_dp_grad_micro(L, B, 5, F.BF16, "scratch", accumulate=False, add_noise=False)
+    once = out.clone()
+    F.flashdp_block_dp_grad_micro(L, B, 5, F.BF16, "scratch", accumulate=True, add_noise=True)
+    assert torch.isnan(out[D * P:]).all()                                      # nothing written past the layer
+    want = 2.0 * once[:D * P].double() + 0.5 * torch.from_numpy(z.reshape(-1)).to(DEV)
+    # two orders of at most 71 fp32 additions each, and the noise field's 2e-6
+    assert float((out[:D * P] - want).abs().max()) <= 4e-6 * max(1.0, float(once[:D * P].abs().max()))
+
+
 @pytest.mark.parametrize("dtype,B,T,P,D", [(torch.bfloat16, 64, 128, 300, 30), (torch.bfloat16, 8, 1024, 768, 10), (torch.float16, 4, 200, 4001, 2049),
                                            (torch.float32, 44, 37, 509, 255), (torch.float32, 3, 100, 2222, 3333)])
 def test_accumulation_of_unaligned_sizes_adds_whole_samples(dtype, B, T, P, D):
