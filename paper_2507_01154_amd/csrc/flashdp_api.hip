@@ -187,19 +187,28 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   const bool f32_ok = f32_fits && (f32_aligned || f32_any(B));
   // 16-bit inputs of other sizes: the register-staged kernels with 2-byte aligned accesses.  Bound by the rate of the
   // staged main loop (about 0.6 of the direct-to-LDS one); the generic kernel on the vector ALUs is 2 to 17 times slower
-  // (768 x 50257, B = 2, T = 1024: 287 us against 2800; 130 x 257, B = 8, T = 64: 16 against 32) and is kept for rows
+  // (768 x 50257, B = 2, T = 1024: 245 us against 2650; 130 x 257, B = 32, T = 64: 21 against 34) and is kept for rows
   // shorter than one 16-byte access and for problems of a single small tile, where it is all launch cost (33 x 35,
   // B = 4, T = 16: 11 us against 13).
   const bool any16_ok = dtype != FLASHDP_F32 && (P % 8 != 0 || D % 8 != 0) && P >= 8 && D >= 8 && env().tile != -1 &&
                         !(P <= 64 && D <= 64 && T <= 32);
   p.any = any16_ok || (f32_ok && !f32_aligned);
   if (any16_ok) {
-    const int64_t tiles = ((D + 255) / 256) * ((P + 255) / 256);
-    p.path = tiles * B >= 128 ? PATH_256x8k32 : PATH_128x4;
+    // Tile by rounds of the chip: one 256x256 workgroup or two 128x128 ones per CU, about 6 us + 28.5 ns a token a round
+    // resp. 5.5 us + 21 ns (fitted to the contractions below).  Thin layers, whose 256x256 tiles would be mostly padding,
+    // come out on the small tile.  bf16, contraction in us, 256 and 128: 768 x 10, B = 64, T = 1024: 31, 22; 100 x 33, B = 128,
+    // T = 2048: 53, 32; 257 x 129, B = 130, T = 512: 38, 32; 3001 x 3001, B = 1, T = 2048: 58, 78; 250 x 250, B = 200, T = 512:
+    // 24, 32; 513 x 513, B = 64, T = 17: 24, 30.
+    // Thin, short and many: the generic kernel's 64x64 tiles (1000 x 10, B = 256, T = 16: 24 us, 17).
+    const int64_t cus = cu_count();
+    const double t256 = (double)((tiles_of(256) * B + cus - 1) / cus) * (6.0 + 0.0285 * T);
+    const double t128 = (double)((tiles_of(128) * B + 2 * cus - 1) / (2 * cus)) * (5.5 + 0.021 * T);
+    const bool thin = std::min(P, D) <= 64 && T <= 16 && tiles_of(64) * B >= 512;
+    p.path = thin ? PATH_SIMPLE : t256 < t128 ? PATH_256x8k32 : PATH_128x4;
     // batches: the tiling whose accumulating pass keeps its total apart from the sample in progress (accum_totals; bf16,
     // 4 x 4001 x 4001, T = 512, two-pass: 241 us, 175 and twice the error on 256 x 256 tiles, 2601 with the generic kernel)
-    p.accum_path = tiles >= 128 && B == 1 ? p.path : PATH_128x4;
-    p.bm = p.bn = p.path == PATH_128x4 ? 128 : 256;
+    p.accum_path = B == 1 && !thin ? p.path : PATH_128x4;
+    p.bm = p.bn = thin ? 64 : p.path == PATH_128x4 ? 128 : 256;
   } else if (f32_ok) {
     p.path = PATH_F32; p.bm = p.bn = 256;
     // (batches of unaligned rows: the generic kernel, which keeps its total apart from the sample in progress)
@@ -343,13 +352,10 @@ hipError_t launch_gemm_dt(const Plan& p, const GemmArgs& args, hipStream_t st) {
   GemmArgs a = args;
   if (MODE == MODE_ACCUM) { a.tiles_m = p.accum_tiles_m; a.tiles_n = p.accum_tiles_n; }
   if constexpr (DT != DT_F32) {
-    if (p.any)
-      return (MODE == MODE_ACCUM ? p.accum_path : p.path) == PATH_128x4 ? launch_mfma<Cfg128x4, MODE, DT, true>(a, st)
-                                                                        : launch_mfma<Cfg256x8k32, MODE, DT, true>(a, st);
     switch (MODE == MODE_ACCUM ? p.accum_path : p.path) {
       case PATH_256x8: return launch_mfma<Cfg256x8, MODE, DT>(a, st);
-      case PATH_128x4: return launch_mfma<Cfg128x4, MODE, DT>(a, st);
-      case PATH_256x8k32: return launch_mfma<Cfg256x8k32, MODE, DT>(a, st);
+      case PATH_128x4: return p.any ? launch_mfma<Cfg128x4, MODE, DT, true>(a, st) : launch_mfma<Cfg128x4, MODE, DT>(a, st);
+      case PATH_256x8k32: return p.any ? launch_mfma<Cfg256x8k32, MODE, DT, true>(a, st) : launch_mfma<Cfg256x8k32, MODE, DT>(a, st);
       case PATH_DMA: return launch_tiled<CfgDma>(gemm_mfma_dma_kernel<CfgDma, MODE, DT>, MODE, a, st, /*lockstep=*/true);
       case PATH_DMA16: return launch_tiled<CfgDma>(gemm_mfma_dma16_kernel<CfgDma, MODE, DT>, MODE, a, st, /*lockstep=*/true);
       case PATH_DMA_384x192:

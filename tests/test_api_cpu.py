@@ -136,6 +136,24 @@ def test_fp32_sizes_no_multiple_of_4_take_the_kernel_that_is_faster_there():
         assert tiles(*shape) == side, shape
 
 
+def test_16_bit_sizes_no_multiple_of_8_take_the_tile_with_the_shorter_rounds():
+    # read off the norm partials as above; 256 compute units
+    def tiles(p, d, B, T):
+        L = [dict(X=None, dY=None, d_in=p, d_out=d, C=1.0, sigma=1.0, seed=0, layer=0, out_grad=None)]
+        up = lambda n: (n + 255) // 256 * 256
+        n = F.flashdp_workspace_bytes(L, B, T, F.BF16, "twopass") - up(4 * B)
+        t = {b: up(4 * B * -(-p // b) * -(-d // b)) for b in (64, 128, 256)}
+        assert len(set(t.values())) == 3                  # the shape tells the three apart
+        return next(b for b in t if t[b] == n)
+
+    for shape, side in (((768, 10, 64, 1024), 128), ((300, 30, 64, 256), 128), ((265, 129, 130, 512), 128), ((4096, 33, 16, 1024), 128),
+                        ((3001, 3001, 1, 2048), 256), ((250, 250, 200, 512), 256), ((513, 513, 64, 17), 256), ((2049, 129, 16, 100), 256),
+                        ((768, 50257, 2, 1024), 256), ((1001, 1001, 4, 512), 128),
+                        ((1000, 10, 256, 16), 64), ((1000, 10, 256, 17), 128), ((1000, 10, 31, 16), 128), ((1000, 65, 256, 16), 128),
+                        ((1000, 7, 256, 64), 64)):
+        assert tiles(*shape) == side, shape
+
+
 @pytest.mark.skipif(torch.cuda.is_available(), reason="only meaningful on a host without a GPU")
 def test_no_device_is_an_error_not_a_crash():
     assert F.lib().flashdp_linear_dp_grad(A, B_, 1, 1, 8, 8, 1.0, 0.0, 0, O_, None) == F.NO_DEVICE

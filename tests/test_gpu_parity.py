@@ -185,6 +185,18 @@ def test_fp32_samples_that_no_cache_holds_are_summed_past_the_caches(B, P, D):
     assert float((out - want).norm() / want.norm()) <= 5e-5
 
 
+@pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
+@pytest.mark.parametrize("B,T,P,D,kernel", [(70, 16, 500, 10, "gemm_simple_kernel"), (70, 17, 500, 10, "gemm_mfma_kernel"),
+                                            (130, 40, 10, 265, "gemm_mfma_kernel"), (128, 4, 513, 250, "gemm_mfma_kernel")])
+def test_thin_layers_of_many_samples(B, T, P, D, kernel, schedule):
+    # on both sides of the rules between the generic kernel and the two tilings of unaligned rows
+    rng = np.random.default_rng(B + T + P)
+    X = W.float32_to_bf16_bits(rng.standard_normal((B, T, P)).astype(np.float32))
+    dY = W.float32_to_bf16_bits((rng.standard_normal((B, T, D)) * 0.05 * (10.0 ** rng.uniform(-1, 1, size=(B, 1, 1)))).astype(np.float32))
+    check_case(X, dY, 1.0, 0.5, 9, 2, "bf16", schedule)
+    assert F.flashdp_last_kernel() == kernel
+
+
 @pytest.mark.parametrize("B", [1, 3, 70])
 @pytest.mark.parametrize("P,D", [(9, d) for d in range(8, 16)] + [(3, 3), (1, 1), (2, 3), (7, 1), (1, 8), (67, 31)])
 def test_last_group_of_the_16_bit_aggregation(B, P, D):
