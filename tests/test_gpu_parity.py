@@ -141,11 +141,52 @@ def test_small_bf16_all_tiles(shape, schedule, tile):
 
 
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
-def test_odd_dims_take_generic_kernel(schedule):
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape,tile", [((3, 37, 77, 5), None), ((2, 40, 3, 131), None), ((4, 16, 33, 35), None), ((3, 37, 77, 131), -1)])
+def test_16_bit_shapes_of_the_generic_kernel(shape, tile, dtype, schedule):
+    # rows shorter than 16 bytes, one small tile, and sizes that take the matrix cores unless switched off; the total of
+    # the accumulating pass differs from the matrix cores' by the order of fp32 additions only
+    B, T, P, D = shape
+    w = W.scaled_down(W.WORKLOADS["gpt2_small_mlp_up"], B=B, T=T, dims=[(P, D)])
+    X, dY = W.make_layer(w, 0)
+    want = None
+    if dtype == "f16":
+        X, dY = O.widen(X).astype(np.float16), O.widen(dY).astype(np.float16)
+        want = O.linear_dp_grad(X.astype(np.float32), dY.astype(np.float32), 1.0, 0.0, 5, 1)
+    check_case(X, dY, 1.0, 0.5, 5, 1, dtype, schedule, tile=tile, oracle=want)
+    assert F.flashdp_last_kernel() == "gemm_simple_kernel"
+    if tile is not None:
+        generic, n0, _ = run_layer(X, dY, 1.0, 0.0, 5, 1, schedule, tile=tile)
+        cores, n1, _ = run_layer(X, dY, 1.0, 0.0, 5, 1, schedule)
+        assert F.flashdp_last_kernel() == "gemm_mfma_kernel"
+        tol = 4e-3 if schedule == "scratch" else 1e-5      # parked values may round the other way
+        assert rel_fro(generic, cores.astype(np.float64)) <= tol and np.allclose(n0, n1, rtol=1e-4 if schedule == "scratch" else 1e-5, atol=0)
+
+
+@pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
+def test_odd_dims(schedule):
     base = W.WORKLOADS["gpt2_small_mlp_up"]
     w = W.scaled_down(base, B=3, T=37, dims=[(77, 131)])
     X, dY = W.make_layer(w, 0)
     check_case(X, dY, 1.0, 0.5, 5, 1, "bf16", schedule)
+
+
+@pytest.mark.parametrize("dtype,B,T,P,D,kernel", [(torch.float32, 44, 37, 509, 255, "gemm_mfma_f32_kernel"), (torch.float32, 1, 9, 3001, 3001, "gemm_mfma_f32_kernel"),
+                                                  (torch.float32, 2, 40, 77, 131, "gemm_simple_kernel"), (torch.bfloat16, 3, 70, 129, 257, "gemm_mfma_kernel"),
+                                                  (torch.bfloat16, 1, 33, 3001, 3001, "gemm_mfma_kernel")])
+@pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
+def test_unaligned_sizes_add_to_an_earlier_micro_batch(dtype, B, T, P, D, kernel, schedule):
+    g = torch.Generator(device=DEV).manual_seed(P + D)
+    x, y = torch.randn((B, T, P), generator=g, device=DEV).to(dtype), (0.05 * torch.randn((B, T, D), generator=g, device=DEV)).to(dtype)
+    out = torch.full((D, P), float("nan"), device=DEV)
+    L = [dict(X=x, dY=y, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=None)]
+    F.flashdp_block_dp_grad_micro(L, B, T, F.dtype_code(x), schedule, accumulate=False, add_noise=False)
+    assert F.flashdp_last_kernel() == kernel
+    once = out.clone()
+    assert torch.isfinite(once).all()
+    F.flashdp_block_dp_grad_micro(L, B, T, F.dtype_code(x), schedule, accumulate=True, add_noise=False)
+    # the same sum added to itself, in one of two orders of at most 45 fp32 additions
+    assert float((out.double() - 2.0 * once.double()).norm() / (2.0 * once.double()).norm()) <= 1e-6
 
 
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
@@ -431,7 +472,7 @@ def test_f16_and_fp32_inputs(schedule, shape):
 @pytest.mark.parametrize("shape", SMALL + [
     (3, 300, 328, 520),      # 3 x 3 blocks of 128 rows: diagonal and off-diagonal blocks, ragged last block
     (2, 513, 72, 40),        # long sequence, small features: the regime the identity is meant for
-    (2, 150, 77, 131),       # odd feature sizes: generic kernel, 64-row blocks, ragged
+    (2, 150, 77, 131),       # odd feature sizes: generic Gram kernel, 64-row blocks, ragged
 ])
 def test_ghost_norm_schedule_bf16(shape):
     B, T, P, D = shape
