@@ -543,7 +543,7 @@ hipError_t launch_rows(RowsArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((rows_clip_kernel<DT>), dim3((unsigned)a.B), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // 128-wide tiles (a quarter of the LDS reads per product) once they occupy the chip twice over
+  // 128-wide tiles (half the LDS reads per product) once they occupy the chip twice over
   const int64_t tiles128 = (int64_t)edge_plan::tiles(a.D, 128) * edge_plan::tiles(a.P, 128);
   const bool large = tiles128 >= 512;
   const int bm = large ? 128 : 64;
@@ -900,7 +900,8 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     const size_t need = mode == FLASHDP_SCHEDULE_OVERLAP ? need_overlap : mode == FLASHDP_SCHEDULE_SCRATCH ? need_scratch
                         : mode == FLASHDP_SCHEDULE_EXPLICIT ? need_explicit : mode == FLASHDP_SCHEDULE_GHOST ? need_ghost
                         : mode == FLASHDP_SCHEDULE_FUSED ? need_fused : need_small;
-    // room for a group of small layers, if the library's workspace has to grow anyway
+    // room for a group of small layers, if the library's workspace has to grow anyway (never for that alone: growing
+    // synchronises the device and frees a block that a captured graph may still name)
     size_t wish = 0;
     if (mode == FLASHDP_SCHEDULE_SCRATCH && n_layers >= 2) {
       for (int l = 0; l < n_layers && l < GROUP_MAX && group_ok(layers[l], B, T, dtype); ++l) {

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(512, 2) void gemm_mfma_f32_kernel(const GemmArgs a)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int col = col_base + j * 32 + 8 * q;
-          if (col < a.P) {   // P is a multiple of 4 on this path: a 4-column group is all in or all out
+          if (col < a.P) {   // P a multiple of 4 (all but ANY): a 4-column group is all in or all out
             float4 v = make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
             if constexpr (ANY) {
               store_any(prow, col, a.P, v, MODE == MODE_ACCUM && a.accumulate);

@@ -1,6 +1,7 @@
 // Generic (any shape, any supported storage type) version of the per-sample contraction of Algorithm 1,
-// on the vector ALUs with fp32 accumulation: used for rows too short for a 16-byte access and for layers too small to
-// occupy the matrix-core tiles.  Same three modes and the same outputs as the matrix-core kernel.
+// on the vector ALUs with fp32 accumulation: used for rows too short for a 16-byte access and for layers that do not
+// occupy the matrix-core tiles (small, thin, or fp32 of odd sizes with few tiles; the rules are in make_plan).  Same
+// modes and the same outputs as the matrix-core kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
