@@ -344,7 +344,7 @@ def test_layers_of_a_call_are_those_of_single_calls(B, T, dims, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "fp32"])
-@pytest.mark.parametrize("shape", [(17, 1, 1), (2, 3, 65), (33, 64, 64), (65, 130, 61), (256, 257, 10), (17, 2884, 2950), (31, 2816, 3072)])
+@pytest.mark.parametrize("shape", [(17, 1, 1), (3, 63, 130), (2, 65, 67), (2, 66, 3), (2, 3, 65), (33, 64, 64), (65, 130, 61), (256, 257, 10), (17, 2884, 2950), (31, 2816, 3072)])
 def test_rows_without_a_sequence(shape, dtype):
     # both tile sizes (2816 x 3072 and 2884 x 2950: 128), edges of tiles and of the batch's steps, features that no vector
     # width divides, a second micro-batch added to the first one's sum, a workspace of the smallest size that is accepted
