@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -162,6 +163,19 @@ int device_cus() {
   return it->second;
 }
 
+// The number of compute units that plans are made for: the first device's that is asked (256 while there is none, as in
+// sizing calls on a host without one).  Plans are made several times a call, and asking the runtime each time cost small
+// calls about a microsecond of ten.
+int64_t plan_cus() {
+  static std::atomic<int> known{0};
+  int n = known.load(std::memory_order_relaxed);
+  if (n == 0) {
+    n = device_cus();
+    if (n > 0) known.store(n, std::memory_order_relaxed);
+  }
+  return n > 0 ? n : 256;
+}
+
 Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   Plan p;
   const bool mfma_ok = dtype != FLASHDP_F32 && P % 8 == 0 && D % 8 == 0 &&
@@ -175,9 +189,8 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   // B = 2, T = 1024: 215, 257; 2000 x 77, B = 2, T = 2048: 409, 495; accumulating pass: 3001 x 3001: 838, 490; 768 x 5025,
   // B = 2, T = 1024: 411, 474; 500 x 250, B = 200, T = 8: 426, 755).
   auto tiles_of = [&](int64_t b) { return ((P + b - 1) / b) * ((D + b - 1) / b); };
-  auto cu_count = [] { const int n = device_cus(); return (int64_t)(n > 0 ? n : 256); };   // sizing calls may come before a device is there
   auto f32_any = [&](int64_t samples) {
-    const int64_t cus = cu_count();
+    const int64_t cus = plan_cus();
     const int64_t rounds = (tiles_of(256) * samples + cus - 1) / cus;
     return P >= 4 && D >= 4 && rounds * cus * 256 * 256 <= 3 * tiles_of(64) * 64 * 64 * samples;
   };
@@ -200,7 +213,7 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
     // T = 2048: 53, 32; 257 x 129, B = 130, T = 512: 38, 32; 3001 x 3001, B = 1, T = 2048: 58, 78; 250 x 250, B = 200, T = 512:
     // 24, 32; 513 x 513, B = 64, T = 17: 24, 30.
     // Thin, short and many: the generic kernel's 64x64 tiles (1000 x 10, B = 256, T = 16: 24 us, 17).
-    const int64_t cus = cu_count();
+    const int64_t cus = plan_cus();
     const double t256 = (double)((tiles_of(256) * B + cus - 1) / cus) * (6.0 + 0.0285 * T);
     const double t128 = (double)((tiles_of(128) * B + 2 * cus - 1) / (2 * cus)) * (5.5 + 0.021 * T);
     const bool thin = std::min(P, D) <= 64 && T <= 16 && tiles_of(64) * B >= 512;
@@ -237,7 +250,7 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
         // 384x192 or 192x384 tiles (9/8 the work of a 256x256 one) need enough fewer rounds, they are taken
         // (3072 x 768 at B = 8: 288 items = 2 rounds, against 256 = 1 round of 1.125).  A clear margin is asked for:
         // the 256x256 kernel is the one tuned and measured on the large layers.
-        const int64_t cus = cu_count();
+        const int64_t cus = plan_cus();
         auto rounds = [&](int64_t bm, int64_t bn) { return (((D + bm - 1) / bm) * ((P + bn - 1) / bn) * B + cus - 1) / cus; };
         const double c256 = (double)rounds(256, 256), ca = 1.125 * rounds(384, 192), cb = 1.125 * rounds(192, 384);
         if (std::min(ca, cb) <= 0.9 * c256) choice = ca <= cb ? PATH_DMA_384x192 : PATH_DMA_192x384;
