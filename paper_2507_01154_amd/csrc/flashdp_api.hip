@@ -182,17 +182,18 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
                        (T + 320) * (P > D ? P : D) * 2 < (int64_t(1) << 31);   // incl. the parked prefetches past the end
   // fp32 inputs: fp32 matrix-core kernel when rows are 16-byte multiples and the problem spans a few tiles.
   // Features that are no multiple of 4: the same kernel in its unaligned form where it is the faster one.  A round of one
-  // 256x256 tile per CU takes it as long as the generic kernel takes for a third of that area (in 64x64 tiles), so the
+  // 256x256 tile per CU takes it as long as the generic kernel takes for 0.4 of that area (in 64x64 tiles), so the
   // rounds decide, of the tiles of all samples or, in the accumulating pass, of one (fp32, generic against matrix cores:
   // 3001 x 3001, B = 1, T = 2048: 923 us, 509; 769 x 1025, B = 8, T = 333: 112, 102; 255 x 255, T = 64, B = 128: 113, 82;
-  // left with the generic one: 2222 x 2222, B = 1, T = 2048: 462, 503; 1001 x 1001, B = 4, T = 512: 131, 145; 257 x 3001,
+  // as good: 2500 x 2500, B = 1, T = 2048: 502, 503; left with the generic one: 2222 x 2222, the same: 462, 503; 106 x 2964,
+  // B = 50, T = 85: 114, 126; 1001 x 1001, B = 4, T = 512: 131, 145; 257 x 3001,
   // B = 2, T = 1024: 215, 257; 2000 x 77, B = 2, T = 2048: 409, 495; accumulating pass: 3001 x 3001: 838, 490; 768 x 5025,
   // B = 2, T = 1024: 411, 474; 500 x 250, B = 200, T = 8: 426, 755).
   auto tiles_of = [&](int64_t b) { return ((P + b - 1) / b) * ((D + b - 1) / b); };
   auto f32_any = [&](int64_t samples) {
     const int64_t cus = plan_cus();
     const int64_t rounds = (tiles_of(256) * samples + cus - 1) / cus;
-    return P >= 4 && D >= 4 && rounds * cus * 256 * 256 <= 3 * tiles_of(64) * 64 * 64 * samples;
+    return P >= 4 && D >= 4 && 2 * rounds * cus * 256 * 256 <= 5 * tiles_of(64) * 64 * 64 * samples;
   };
   const bool f32_fits = dtype == FLASHDP_F32 && P * D >= 128 * 128 && (T + 48) * (P > D ? P : D) * 4 < (int64_t(1) << 31) &&
                         env().tile != -1;
@@ -208,16 +209,17 @@ Plan make_plan(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   p.any = any16_ok || (f32_ok && !f32_aligned);
   if (any16_ok) {
     // Tile by rounds of the chip: one 256x256 workgroup or two 128x128 ones per CU, about 6 us + 28.5 ns a token a round
-    // resp. 5.5 us + 21 ns (fitted to the contractions below).  Thin layers, whose 256x256 tiles would be mostly padding,
+    // resp. 6.3 us + 21 ns (fitted to the contractions below).  Thin layers, whose 256x256 tiles would be mostly padding,
     // come out on the small tile.  bf16, contraction in us, 256 and 128: 768 x 10, B = 64, T = 1024: 31, 22; 100 x 33, B = 128,
     // T = 2048: 53, 32; 257 x 129, B = 130, T = 512: 38, 32; 3001 x 3001, B = 1, T = 2048: 58, 78; 250 x 250, B = 200, T = 512:
-    // 24, 32; 513 x 513, B = 64, T = 17: 24, 30.
+    // 24, 32; 513 x 513, B = 64, T = 17: 24, 30; 77 x 3001, B = 64, T = 2: 28, 33.
     // Thin, short and many: the generic kernel's 64x64 tiles (1000 x 10, B = 256, T = 16: 24 us, 17).
     const int64_t cus = plan_cus();
     const double t256 = (double)((tiles_of(256) * B + cus - 1) / cus) * (6.0 + 0.0285 * T);
-    const double t128 = (double)((tiles_of(128) * B + 2 * cus - 1) / (2 * cus)) * (5.5 + 0.021 * T);
+    const double t128 = (double)((tiles_of(128) * B + 2 * cus - 1) / (2 * cus)) * (6.3 + 0.021 * T);
     const bool thin = std::min(P, D) <= 64 && T <= 16 && tiles_of(64) * B >= 512;
-    p.path = thin ? PATH_SIMPLE : t256 < t128 ? PATH_256x8k32 : PATH_128x4;
+    const bool large = t256 < t128 && tiles_of(256) * B >= 128;   // (one round of few workgroups: 777 x 777, B = 4, T = 2: 10, 8)
+    p.path = thin ? PATH_SIMPLE : large ? PATH_256x8k32 : PATH_128x4;
     // batches: the tiling whose accumulating pass keeps its total apart from the sample in progress (accum_totals; bf16,
     // 4 x 4001 x 4001, T = 512, two-pass: 241 us, 175 and twice the error on 256 x 256 tiles, 2601 with the generic kernel)
     p.accum_path = B == 1 && !thin ? p.path : PATH_128x4;

@@ -132,7 +132,7 @@ def test_fp32_sizes_no_multiple_of_4_take_the_kernel_that_is_faster_there():
 
     for shape, side in (((1001, 1001, 4, 512), 64), ((257, 3001, 2, 1024), 64), ((255, 255, 64, 512), 64), ((200, 90, 64, 256), 64),
                         ((1001, 1001, 64, 16), 256), ((3001, 3001, 1, 2048), 256), ((255, 255, 128, 64), 256), ((769, 1025, 8, 333), 256),
-                        ((512, 512, 8, 64), 256), ((2222, 2222, 1, 2048), 64), ((509, 255, 40, 37), 64), ((509, 255, 44, 37), 256), ((3, 40000, 8, 64), 64)):
+                        ((512, 512, 8, 64), 256), ((2222, 2222, 1, 2048), 64), ((509, 255, 44, 37), 64), ((509, 255, 52, 37), 256), ((106, 2964, 50, 85), 64), ((3, 40000, 8, 64), 64)):
         assert tiles(*shape) == side, shape
 
 
@@ -149,7 +149,7 @@ def test_16_bit_sizes_no_multiple_of_8_take_the_tile_with_the_shorter_rounds():
     for shape, side in (((768, 10, 64, 1024), 128), ((300, 30, 64, 256), 128), ((265, 129, 130, 512), 128), ((4096, 33, 16, 1024), 128),
                         ((3001, 3001, 1, 2048), 256), ((250, 250, 200, 512), 256), ((513, 513, 64, 17), 256), ((2049, 129, 16, 100), 256),
                         ((768, 50257, 2, 1024), 256), ((1001, 1001, 4, 512), 128),
-                        ((1000, 10, 256, 16), 64), ((1000, 10, 256, 17), 128), ((1000, 10, 31, 16), 128), ((1000, 65, 256, 16), 128),
+                        ((1000, 10, 256, 16), 64), ((1000, 10, 256, 17), 256), ((1000, 10, 31, 16), 128), ((1000, 65, 256, 16), 128),
                         ((1000, 7, 256, 64), 64)):
         assert tiles(*shape) == side, shape
 

@@ -171,7 +171,7 @@ def test_odd_dims(schedule):
     check_case(X, dY, 1.0, 0.5, 5, 1, "bf16", schedule)
 
 
-@pytest.mark.parametrize("dtype,B,T,P,D,kernel", [(torch.float32, 44, 37, 509, 255, "gemm_mfma_f32_kernel"), (torch.float32, 1, 9, 3001, 3001, "gemm_mfma_f32_kernel"),
+@pytest.mark.parametrize("dtype,B,T,P,D,kernel", [(torch.float32, 52, 37, 509, 255, "gemm_mfma_f32_kernel"), (torch.float32, 1, 9, 3001, 3001, "gemm_mfma_f32_kernel"),
                                                   (torch.float32, 2, 40, 77, 131, "gemm_simple_kernel"), (torch.bfloat16, 3, 70, 129, 257, "gemm_mfma_kernel"),
                                                   (torch.bfloat16, 1, 33, 3001, 3001, "gemm_mfma_kernel")])
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
@@ -192,8 +192,8 @@ def test_unaligned_sizes_add_to_an_earlier_micro_batch(dtype, B, T, P, D, kernel
 @pytest.mark.parametrize("schedule", ["twopass", "scratch", "explicit"])
 @pytest.mark.parametrize("dtype,shape", [("bf16", s) for s in [(2, 33, 9, 72), (1, 1, 15, 131), (3, 70, 129, 257), (2, 64, 255, 136),
                                                                (2, 40, 264, 135), (130, 20, 265, 10), (3, 97, 2049, 2303)]]
-                         + [("f16", (2, 65, 71, 383)), ("fp32", (10, 37, 509, 255)), ("fp32", (2, 18, 769, 1021)), ("fp32", (44, 37, 509, 255)),
-                            ("fp32", (7, 18, 769, 1021))])
+                         + [("f16", (2, 65, 71, 383)), ("fp32", (10, 37, 509, 255)), ("fp32", (2, 18, 769, 1021)), ("fp32", (52, 37, 509, 255)),
+                            ("fp32", (8, 18, 769, 1021))])
 def test_sizes_no_vector_width_divides(dtype, shape, schedule):
     # edges of the 128 and 256 tiles, chunks that reach 1..7 columns past a row, one token, single short rows
     B, T, P, D = shape
@@ -207,8 +207,8 @@ def test_sizes_no_vector_width_divides(dtype, shape, schedule):
     elif dtype == "bf16":
         X, dY = ((a.view(np.uint32) >> 16).astype(np.uint16) for a in (X, dY))
     check_case(X, dY, 1.0, 1.0, 9, 2, dtype, schedule, oracle=want)
-    # fp32: the matrix-core kernel where its 256 x 256 tiles occupy enough of the chip (the 44 and the 7 samples)
-    assert F.flashdp_last_kernel() == ("gemm_mfma_kernel" if dtype != "fp32" else "gemm_mfma_f32_kernel" if B in (44, 7) else "gemm_simple_kernel")
+    # fp32: the matrix-core kernel where its 256 x 256 tiles occupy enough of the chip (the 52 and the 8 samples)
+    assert F.flashdp_last_kernel() == ("gemm_mfma_kernel" if dtype != "fp32" else "gemm_mfma_f32_kernel" if B in (52, 8) else "gemm_simple_kernel")
 
 
 @pytest.mark.parametrize("B,P,D", [(17, 1999, 2001), (16, 1999, 2001), (17, 1999, 2004)])
@@ -266,7 +266,7 @@ def test_last_group_of_the_16_bit_aggregation(B, P, D):
 
 
 @pytest.mark.parametrize("dtype,B,T,P,D", [(torch.bfloat16, 64, 128, 300, 30), (torch.bfloat16, 8, 1024, 768, 10), (torch.float16, 4, 200, 4001, 2049),
-                                           (torch.float32, 44, 37, 509, 255), (torch.float32, 3, 100, 2222, 3333)])
+                                           (torch.float32, 52, 37, 509, 255), (torch.float32, 3, 100, 2222, 3333)])
 def test_accumulation_of_unaligned_sizes_adds_whole_samples(dtype, B, T, P, D):
     # Each sample is summed by itself and then added to the total.  A sum of T products in steps of 8 to 16 rounds T / 8
     # times at the size it has grown to, 2^-24 / sqrt(3) each: 3e-7 of the result for T = 1024, less for fewer, and B
@@ -288,7 +288,7 @@ def test_accumulation_of_unaligned_sizes_adds_whole_samples(dtype, B, T, P, D):
 
 @pytest.mark.parametrize("schedule,scale,C", [("twopass", 1e13, 1.0), ("twopass", 1e7, 1e-30), ("ghost", 1e7, 1e-30)])
 @pytest.mark.parametrize("dtype,B,T,P,D", [(torch.bfloat16, 5, 37, 77, 131), (torch.bfloat16, 4, 70, 136, 257), (torch.bfloat16, 3, 20, 4001, 2049),
-                                           (torch.float32, 5, 37, 77, 131), (torch.float32, 44, 37, 509, 255), (torch.float32, 3, 9, 4001, 2049)])
+                                           (torch.float32, 5, 37, 77, 131), (torch.float32, 52, 37, 509, 255), (torch.float32, 3, 9, 4001, 2049)])
 def test_accumulation_of_unaligned_sizes_survives_a_factor_of_zero(dtype, B, T, P, D, schedule, scale, C):
     # one sample's clip factor is 0 (its norm is beyond what fp32 sums of squares hold, or 1e45 times C), its elements are
     # finite: the other samples' sum has to stay what it is, wherever in the batch that sample stands (a total rescaled by
