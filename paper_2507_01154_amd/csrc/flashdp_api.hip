@@ -667,7 +667,7 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
     g.first[l + 1] = g.first[l] + (int)(q.tiles * B);   // a few hundred each by the path's rule
     t.first[l + 1] = t.first[l] + (int)((q.S / 8 + 255) / 256);
   }
-  auto kern = gemm_mfma_grouped_kernel<Cfg128x4, DT>;
+  auto kern = gemm_mfma_kernel<Cfg128x4, MODE_SPILL, DT, false, GroupedGemmArgs>;
   hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), Cfg128x4::LDS_BYTES);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)g.first[n]), dim3(Cfg128x4::NT), Cfg128x4::LDS_BYTES, st, g);
