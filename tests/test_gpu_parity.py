@@ -10,7 +10,7 @@ Tolerances (relative Frobenius error of out_grad against the oracle):
         relative for bf16, asserted <= 4e-3;
       - norms: two-pass, ghost, explicit and fp32 paths take them from fp32 sums: asserted <= 1e-4.  The scratch
         schedule with 16-bit inputs takes the norm of the tile as parked in bfloat16 (so that the clip factor bounds
-        what is summed): each element moves by at most 2^-9 relative, hence the norm by at most 2^-9 (asserted,
+        what is summed): each element moves by at most 2^-8 relative, the norm of many by less than 2^-9 (asserted,
         + 1e-5), and for tiles of 2^16 elements or more the roundings average out (asserted <= 1e-4);
       - noise field: |z_gpu - z_oracle| <= 2e-6 per element (fp32 Box-Muller on exact 24-bit uniforms; the
         host build of the same header measures 6e-7), so out(sigma) - out(0) is compared at 4e-6 * sigma * C
