@@ -149,7 +149,7 @@ def test_16_bit_sizes_no_multiple_of_8_take_the_tile_with_the_shorter_rounds():
     for shape, side in (((768, 10, 64, 1024), 128), ((300, 30, 64, 256), 128), ((265, 129, 130, 512), 128), ((4096, 33, 16, 1024), 128),
                         ((3001, 3001, 1, 2048), 256), ((250, 250, 200, 512), 256), ((513, 513, 64, 17), 256), ((2049, 129, 16, 100), 256),
                         ((768, 50257, 2, 1024), 256), ((1001, 1001, 4, 512), 128),
-                        ((1000, 10, 256, 16), 64), ((1000, 10, 256, 17), 256), ((1000, 10, 31, 16), 128), ((1000, 65, 256, 16), 128),
+                        ((1000, 10, 256, 16), 64), ((1000, 10, 256, 17), 256), ((1000, 10, 31, 16), 128), ((1000, 65, 256, 16), 256), ((1000, 65, 256, 64), 128),
                         ((1000, 7, 256, 64), 64)):
         assert tiles(*shape) == side, shape
 
