@@ -125,7 +125,13 @@ enum { FLASHDP_BF16 = 0, FLASHDP_F32 = 1, FLASHDP_F16 = 2 };
  *            G_i still computed once (flashdp_workspace_bytes_chunked sizes such a workspace).  Only a
  *            workspace too small for a single sample falls back to TWOPASS.  Rows without a sequence (T = 1) are
  *            outer products, G_i = dy_i x_i^T with n_i = |dy_i| |x_i|: AUTO takes norms and factors from the rows and
- *            forms the clipped sum as one product over the batch in any workspace that TWOPASS accepts ("rows"). */
+ *            forms the clipped sum as one product over the batch in any workspace that TWOPASS accepts ("rows").
+ *            Short sequences of 16-bit inputs (d_in, d_out multiples of 8, two samples or more, and few enough tokens that
+ *            computing G_i twice costs less than parking it: T up to about 250 for large layers) take TWOPASS on 128 x 128
+ *            tiles, all layers of a call in shared launches, in a workspace of 4 B + 16 B ceil(d_out / 128)
+ *            ceil(d_in / 128) bytes a layer; a larger one holds partial sums over parts of the batch where the layers
+ *            alone do not fill the chip.  Which layers are together and how many parts there are decides the order
+ *            of fp32 additions, so results of different groupings agree to fp32 rounding, not bit for bit. */
 enum { FLASHDP_SCHEDULE_AUTO = 0, FLASHDP_SCHEDULE_TWOPASS = 1, FLASHDP_SCHEDULE_SCRATCH = 2, FLASHDP_SCHEDULE_EXPLICIT = 3,
        FLASHDP_SCHEDULE_OVERLAP = 4, FLASHDP_SCHEDULE_GHOST = 5, FLASHDP_SCHEDULE_FUSED = 6 };
 

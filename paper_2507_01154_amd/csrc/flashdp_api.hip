@@ -23,6 +23,7 @@
 #include "gemm_mfma_streamk.hip.h"
 #include "fused_dp.hip.h"
 #include "gemm_simple.hip.h"
+#include "gemm_tile128.hip.h"
 #include "gram_norm.hip.h"
 #include "mfma_probe.hip.h"
 #include "rows_dp.hip.h"
@@ -678,6 +679,119 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
   return hipGetLastError();
 }
 
+// Short sequences (gemm_tile128.hip.h): AUTO takes the two-pass schedule on 128 x 128 tiles, all layers of the call in its
+// three or four launches, where that is the faster way.  Parking costs about 0.68 us per million elements and sample (2 + 2
+// bytes), the second contraction 0.05 us + 1.95 ns a token of the padded tiles, and the launches 9 us (fitted to 170 calls; the
+// rule is within 1 % of the faster way where it takes this one).  bf16, a call, parked and so, in us: a GPT-2 block, B = 64: T = 16:
+// 466, 105; T = 128: 490, 266; T = 256: 633, 553; B = 4, T = 128: 67, 44; 4096 x 4096, B = 64: T = 16: 892, 190; T = 64: 911, 300;
+// 5120 x 13824, B = 4, T = 16: 290, 170; 264 x 6000, B = 64, T = 16: 131, 70; left to parking: 768 x 768, B = 16, T = 64: 22, 25;
+// 1024 x 3072, B = 64, T = 256: 223, 226; one sample (4096 x 4096, T = 64: 39, 41).
+struct ShortPlan {
+  int tiles_m, tiles_n;
+  size_t partials, sums, end;   // workspace offsets; the factors stand at `begin`
+};
+ShortPlan short_plan(int64_t B, int64_t P, int64_t D, size_t begin, int splits) {
+  ShortPlan p;
+  p.tiles_m = (int)((D + 127) / 128);
+  p.tiles_n = (int)((P + 127) / 128);
+  p.partials = begin + align_up((size_t)B * 4, 256);
+  p.sums = p.partials + align_up((size_t)B * p.tiles_m * p.tiles_n * 16, 256);
+  p.end = p.sums + (splits > 1 ? align_up((size_t)splits * P * D * 4, 256) : 0);
+  return p;
+}
+bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype) {
+  if (dtype == FLASHDP_F32 || T < 2 || B < 2 || g_ctx.stages != FLASHDP_STAGE_ALL || env().tile != 0) return false;
+  double gain = -9.0;
+  for (int l = 0; l < n; ++l) {
+    const int64_t P = layers[l].d_in, D = layers[l].d_out;
+    if (P % 8 != 0 || D % 8 != 0 || (T + 320) * std::max(P, D) * 2 >= (int64_t(1) << 31)) return false;
+    const double parked = 1e-6 * B * P * D, padded = 1e-6 * B * ((P + 127) / 128) * ((D + 127) / 128) * 16384;
+    gain += 0.68 * parked - (0.05 + 0.00195 * T) * padded;
+  }
+  return gain > 0.0;
+}
+// How many layers from the first on share the launches (0: the workspace does not hold the first), and how many workgroups
+// walk over the samples of one tile in the accumulating pass: enough to fill the chip, as far as the workspace holds their
+// partial sums.
+int short_group(const flashdp_layer_t* layers, int n, int64_t B, size_t ws_bytes, int64_t T, int* splits) {
+  size_t used = 0;
+  int64_t tiles = 0;
+  int k = 0;
+  for (; k < n && k < GROUP_MAX; ++k) {
+    const ShortPlan p = short_plan(B, layers[k].d_in, layers[k].d_out, used, 1);
+    bool apart = true;
+    for (int j = 0; j < k && apart; ++j) apart = group_disjoint(layers[j], layers[k], B, T);
+    if (p.end > ws_bytes || !apart) break;
+    used = p.end;
+    tiles += (int64_t)p.tiles_m * p.tiles_n;
+  }
+  *splits = 1;
+  for (int64_t q = std::min({B, (int64_t)8, 2 * plan_cus() / std::max<int64_t>(tiles, 1), B * ((T + 31) / 32) / 24}); q > 1; --q) {
+    size_t end = 0;
+    for (int l = 0; l < k; ++l) end = short_plan(B, layers[l].d_in, layers[l].d_out, end, (int)q).end;
+    if (end <= ws_bytes) { *splits = (int)q; break; }
+  }
+  return k;
+}
+
+template <int DT>
+hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B, int64_t T, char* ws, hipStream_t st, bool accumulate, bool add_noise) {
+  Tile128Args norm, sum;
+  Tile128ClipArgs clip;
+  Tile128SumArgs fin;
+  norm.n = sum.n = clip.n = n;
+  clip.B = (int)B;
+  fin.n = 0;
+  norm.first[0] = sum.first[0] = fin.first[0] = 0;
+  int64_t all_tiles = 0;
+  for (int l = 0; l < n; ++l) all_tiles += ((layers[l].d_out + 127) / 128) * ((layers[l].d_in + 127) / 128);
+  // two rounds of two workgroups per CU or more in the norm pass (one to eight rounds measure within 4 %)
+  const int64_t norm_splits = std::min(B, std::max<int64_t>(1, (4 * plan_cus() + all_tiles - 1) / all_tiles));
+  size_t used = 0;
+  for (int l = 0; l < n; ++l) {
+    const flashdp_layer_t& L = layers[l];
+    const ShortPlan p = short_plan(B, L.d_in, L.d_out, used, splits);
+    float* const factors = reinterpret_cast<float*>(ws + used);
+    float* const partials = reinterpret_cast<float*>(ws + p.partials);
+    float* const sums = reinterpret_cast<float*>(ws + p.sums);
+    used = p.end;
+    const int tiles = p.tiles_m * p.tiles_n;
+    const float noise_scale = add_noise ? L.sigma * L.C : 0.0f;
+    Tile128Layer& a = norm.layer[l];
+    a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
+    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
+    a.splits = (int)norm_splits;
+    a.partials = partials; a.factors = factors; a.out = nullptr;
+    a.noise_scale = noise_scale; a.accumulate = accumulate ? 1 : 0; a.seed = L.seed; a.layer = L.layer;
+    sum.layer[l] = a;
+    sum.layer[l].splits = splits;
+    sum.layer[l].out = splits > 1 ? sums : L.out_grad;
+    norm.first[l + 1] = norm.first[l] + (int)align_up((size_t)(tiles * norm_splits), 8);
+    sum.first[l + 1] = sum.first[l] + (int)align_up((size_t)(tiles * splits), 8);
+    clip.layer[l] = Tile128ClipArgs::Layer{partials, factors, L.out_norms, 4 * tiles, L.C};
+    if (splits > 1) {
+      const size_t S = (size_t)L.d_in * L.d_out;
+      fin.layer[fin.n] = Tile128SumArgs::Layer{sums, L.out_grad, S, splits, accumulate ? 1 : 0, noise_scale, L.seed, L.layer};
+      fin.first[fin.n + 1] = fin.first[fin.n] + (int)((S / 4 + 255) / 256);
+      ++fin.n;
+    }
+  }
+  auto knorm = gemm_tile128_kernel<MODE_NORM, DT>;
+  auto ksum = gemm_tile128_kernel<MODE_ACCUM, DT>;
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(knorm), Tile128Cfg::LDS_BYTES);
+  if (e == hipSuccess) e = ensure_lds_limit(reinterpret_cast<const void*>(ksum), Tile128Cfg::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(knorm, dim3((unsigned)norm.first[n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, norm);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(tile128_clip_kernel, dim3((unsigned)(n * B)), dim3(256), 0, st, clip);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(ksum, dim3((unsigned)sum.first[n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, sum);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (fin.n > 0) hipLaunchKernelGGL(tile128_sum_kernel, dim3((unsigned)fin.first[fin.n]), dim3(256), 0, st, fin);
+  g_ctx.last_kernel = "gemm_tile128_kernel";
+  return hipGetLastError();
+}
+
 // Enqueues Algorithm 1 for one layer.
 // `parts` restricts what is enqueued (a subset of the stage mask); persistent_grid > 0 selects the bounded
 // aggregation grid of the overlapped schedule.
@@ -876,6 +990,29 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     g_ctx.last_chunk = B;
     g_ctx.last_schedule = "rows";
     return FLASHDP_OK;
+  }
+  if (schedule == FLASHDP_SCHEDULE_AUTO && short_ok(layers, n_layers, B, T, dtype)) {
+    size_t need = 0;
+    for (int l = 0; l < n_layers; ++l) need = std::max(need, short_plan(B, layers[l].d_in, layers[l].d_out, 0, 1).end);
+    if (!workspace) {
+      void* p = nullptr; size_t got = 0;
+      st = owned_workspace(std::max(need, need_scratch), &p, &got);
+      if (st != FLASHDP_OK) return st;
+      ws = static_cast<char*>(p);
+      ws_bytes = got;
+    }
+    if (ws_bytes >= need) {
+      for (int k = 0; k < n_layers;) {
+        int splits = 1;
+        const int n = short_group(layers + k, n_layers - k, B, ws_bytes, T, &splits);
+        HIP_TRY(dtype == FLASHDP_BF16 ? run_short<DT_BF16>(layers + k, n, splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0)
+                                      : run_short<DT_F16>(layers + k, n, splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
+        k += n;
+      }
+      g_ctx.last_chunk = B;
+      g_ctx.last_schedule = "twopass";
+      return FLASHDP_OK;
+    }
   }
   int mode;
   int64_t chunk = B;   // samples parked at a time

@@ -87,3 +87,15 @@ long ep_walk(int n, int thread, int v, long* lo, long* hi, long* sum) {
   return count;
 }
 }
+
+// Index arithmetic of the 128 x 128 direct-to-LDS kernels.
+#include "../paper_2507_01154_amd/csrc/tile128_plan.h"
+extern "C" {
+int t128_stages() { return flashdp::tile128_plan::STAGES; }
+int t128_load_row(int wave, int lane) { return flashdp::tile128_plan::load_row(wave, lane); }
+int t128_load_chunk(int wave, int lane) { return flashdp::tile128_plan::load_chunk(wave, lane); }
+unsigned t128_load_dst_bytes(int stage, int operand, int wave, int q) { return flashdp::tile128_plan::load_dst_bytes(stage, operand, wave, q); }
+int t128_kept_at(int row, int col) { return flashdp::tile128_plan::kept_at(row, col); }
+int t128_frag_offset(int lane, int block) { return flashdp::tile128_plan::frag_offset(lane, block); }
+int t128_tile_base(int stage, int operand) { return flashdp::tile128_plan::tile_base(stage, operand); }
+}

@@ -883,6 +883,43 @@ def test_fp16_inputs_on_a_llama_sized_layer():
         print("f16 4096x4096", schedule, e)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,T,dims", [(70, 2, [(1032, 264), (8, 2048)]), (180, 33, [(136, 1000)]), (40, 31, [(1304, 648), (384, 384), (648, 1304)]),
+                                      (300, 5, [(136, 520)] * 9), (24, 100, [(776, 1544)])])
+def test_short_sequences_take_two_passes_on_small_tiles(B, T, dims, dtype):
+    # ragged tiles, k-tiles of few rows, more samples than a wave has lanes, more layers than one launch takes; workspaces
+    # that hold partial sums, none, and only one layer at a time; added to an earlier micro-batch; noise.  Everything is fp32:
+    # about sqrt(T + B) roundings of 2^-24 a term, 1e-6 with room for the largest case; norms 1e-6.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B * T)
+    layers, want = [], []
+    for l, (P, D) in enumerate(dims):
+        X = torch.randn((B, T, P), generator=g, device=DEV).to(dtype)
+        dY = (torch.randn((B, T, D), generator=g, device=DEV) * 0.05 * 10 ** (2 * torch.rand((B, 1, 1), generator=g, device=DEV) - 1)).to(dtype)
+        G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+        n = G.flatten(1).norm(dim=1)
+        want.append(((G / torch.clamp(n / (1.0 + l), min=1.0)[:, None, None]).sum(0), n))
+        layers.append(dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0 + l, sigma=0.0, seed=9 + l, layer=l,
+                           out_grad=torch.full((D, P), float("nan"), device=DEV), out_norms=torch.full((B,), float("nan"), device=DEV)))
+    code = F.dtype_code(layers[0]["X"])
+    small = max(F.flashdp_workspace_bytes([L], B, T, code, "twopass") for L in layers) * 64
+    for ws in (None, torch.empty((small,), dtype=torch.uint8, device=DEV), torch.empty((F.flashdp_workspace_bytes(layers, B, T, code, "scratch"),), dtype=torch.uint8, device=DEV)):
+        F.flashdp_block_dp_grad(layers, B, T, code, "auto", ws)
+        assert F.flashdp_last_schedule() == "twopass" and F.flashdp_last_kernel() == "gemm_tile128_kernel"
+        for L, (o, n) in zip(layers, want):
+            assert float((L["out_grad"] - o).norm() / o.norm()) <= 1e-6
+            assert float(((L["out_norms"] - n).abs() / n).max()) <= 1e-6
+    first = [L["out_grad"].clone() for L in layers]
+    noisy = [dict(L, sigma=0.5) for L in layers]
+    F.flashdp_block_dp_grad_micro(noisy, B, T, code, "auto", ws, accumulate=True, add_noise=True)
+    for L, f, (o, n) in zip(layers, first, want):
+        z = torch.empty((L["d_in"] * L["d_out"],), device=DEV)
+        F.flashdp_noise_field(L["seed"], L["layer"], z.numel(), z)
+        got = L["out_grad"].double() - 0.5 * L["C"] * z.view(L["d_out"], L["d_in"]).double()
+        # three fp32 additions of values of up to 6 sigma C beside the sum
+        assert float((got - 2 * o).abs().max()) <= 1e-6 * 2 * float(o.abs().max()) + 3 * 2.0 ** -24 * (3 * L["C"] + 2 * float(o.abs().max()))
+
+
 @pytest.mark.parametrize("schedule", ["scratch", "twopass", "explicit", "ghost"])
 def test_nan_in_one_sample_poisons_the_output_instead_of_passing_unclipped(schedule):
     base = W.WORKLOADS["gpt2_small_mlp_up"]

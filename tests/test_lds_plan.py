@@ -356,3 +356,38 @@ def test_a_chunk_is_written_whole_only_where_all_of_it_is_in_the_row(plan, n):
     for width in (4, 8):
         for col in range((n - 1) // width * width, max(-1, n - 40), -width):       # the chunks a tile's threads store, from the last
             assert bool(plan.ep_chunk_fits(col, n, width)) == (col + width <= n), (col, n, width)
+
+
+# ---- the 128 x 128 kernels (csrc/tile128_plan.h) ----
+
+def test_128_plan_loads_fragments_and_banks(plan):
+    side, rows, stages = 128, 32, plan.t128_stages()
+    n = side * rows
+    for stage in range(stages):
+        owner = -np.ones((2 * stages * n, 3), dtype=np.int64)
+        for operand in range(2):
+            for wave in range(4):
+                for q in range(2):
+                    base = plan.t128_load_dst_bytes(stage, operand, wave, q)
+                    for lane in range(64):
+                        row, chunk = plan.t128_load_row(wave, lane) + 16 * q, plan.t128_load_chunk(wave, lane)
+                        for e in range(8):
+                            slot = (base + 16 * lane) // 2 + e
+                            assert owner[slot, 0] == -1                       # nothing is written twice
+                            owner[slot] = (operand, row, 8 * chunk + e)
+            for row in range(rows):
+                for col in range(side):
+                    assert tuple(owner[plan.t128_tile_base(stage, operand) + plan.t128_kept_at(row, col)]) == (operand, row, col)
+        assert (owner[:, 0] >= 0).sum() == 2 * n                              # this stage's two tiles and nothing else
+        for operand in range(2):
+            for block in range(8):
+                for half in range(2):
+                    addr = [plan.t128_tile_base(stage, operand) + plan.t128_frag_offset(lane, block) + half * 4 * side for lane in range(64)]
+                    assert all((2 * a) % 8 == 0 for a in addr)
+                    for lane in range(64):
+                        for j in range(4):
+                            src = 16 * (lane // 16) + (lane % 16) // 4 + 4 * j
+                            assert tuple(owner[addr[src] + lane % 4]) == (operand, 8 * (lane // 16) + 4 * half + j, 16 * block + lane % 16)
+                    for hw in range(2):                                       # 32 lanes at a time: 64 banks, each once
+                        banks = [((2 * addr[32 * hw + l]) // 4 + w) % 64 for l in range(32) for w in range(2)]
+                        assert len(set(banks)) == 64
