@@ -162,11 +162,12 @@ int flashdp_linear_dp_grad(const void* X, const void* dY, int64_t B, int64_t T, 
 /* Per-block multi-layer variant: Algorithm 1 for each of n_layers layers (same B and T), enqueued in
  * order on `stream` (a hipStream_t, may be NULL).  `workspace` is caller-owned device memory of at least
  * flashdp_workspace_bytes(...) bytes, reused layer after layer.  Under SCRATCH (and AUTO where it comes to that) 16-bit
- * layers too small to fill the chip (fewer than 128 tiles of 256 x 256 over the batch; d_in and d_out multiples of 8)
+ * layers that park on 128 x 128 tiles (d_in and d_out multiples of 8, up to about 256 tiles of 256 x 256 over the batch)
  * share their launches, up to eight in a row, as far as the workspace holds them parked together: about the sum of
- * B * d_out * d_in * 2 bytes over them, where flashdp_workspace_bytes gives what the largest layer needs.  A larger
- * workspace makes such calls faster, never different (same bits; a GPT-2 block at B = 1, T = 1024: 37 us with 14 MB, 56 with
- * 9 MB).  The library-owned workspace takes that size (64 MB at most) when it has to grow anyway, and is not grown for it:
+ * B * d_out * d_in * 2 bytes over them, where flashdp_workspace_bytes gives what the largest layer needs (with the norm partials of
+ * small tiles; a few KB less, what the larger tiles' partials take, is accepted and keeps such a layer on those).  A larger
+ * workspace makes such calls faster, never different (same bits; a GPT-2 block at B = 1, T = 1024: 46 us with 9 MB, 56 before
+ * its layers were parted by their tiles).  The library-owned workspace takes that size (64 MB at most) when it has to grow anyway, and is not grown for it:
  * after calls of other sizes a process may be left with the smaller groups.  With workspace == NULL the library-owned
  * workspace is used as above (sized for the schedule asked for).  Calls that share a workspace must be
  * ordered on one stream; the library-owned workspace is one per device, so this holds for all calls on a

@@ -269,7 +269,7 @@ __device__ __forceinline__ void aggregate16_one(const void* __restrict__ scratch
   __builtin_nontemporal_store(hi, dst + 1);
 }
 
-// The tails of the layers of a grouped contraction (gemm_mfma_kernel over GroupedGemmArgs) in one launch.
+// The tails of the layers of a grouped contraction in one launch.
 struct GroupedTailArgs {
   int n, B;
   int first[GROUP_MAX + 1];

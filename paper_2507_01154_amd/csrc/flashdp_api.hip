@@ -291,6 +291,31 @@ const char* path_kernel_name(Path p) {
   }
 }
 
+// The parking pass of the scratch schedule on 128 x 128 tiles (gemm_tile128.hip.h): wherever make_plan takes that tiling, and
+// where it takes a larger one but the smaller tiles' rounds are shorter.  With two workgroups per CU a round of 256
+// tiles takes 1.4 us + 6.2 ns a token, 3 us to begin with; a round of 256 x 256 tiles 8.5 us + 21 ns, of 384 x 192 ones 8.5 us + 27 ns,
+// 2 us to begin with (fitted to 220 contractions; bf16, us, large and small tiles: 768 x 3072, B = 4, T = 1024: 31.6, 26.9; 2048 x 2048,
+// B = 2, T = 2048: 52.5, 33.2; 1024 x 1024, B = 8, T = 333: 18.4, 10.2; 1472 x 7360, B = 2, T = 333: 33.5, 23.9; 1480 x 1000, B = 16, T = 333:
+// 35.7, 29.2; left to large ones: 768 x 3072, B = 8, T = 1024: 38.6, 45.7; 2048 x 2048, B = 4, T = 2048: 55.8, 63.6; operands
+// that no cache holds: 256 x 6432, B = 16, T = 2048: 116, 148).  Several rounds of large tiles are given up for a clear gain only, and
+// not below the 128 tokens it was measured from.  by_far: enough to give up the overlapped schedule as well, which the
+// small tiles do not have (layers of one round park and are summed in shared launches instead).
+struct Park { bool small, by_far; int tiles_m, tiles_n; };
+Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
+  Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128)};
+  if (dtype == FLASHDP_F32 || p.any || env().tile != 0) return k;
+  if (p.path == PATH_128x4) k.small = k.by_far = true;
+  if (p.path == PATH_DMA16 || p.path == PATH_DMA_384x192 || p.path == PATH_DMA_192x384) {
+    const int64_t cus = plan_cus();
+    const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * B + cus - 1) / cus, rounds128 = ((int64_t)k.tiles_m * k.tiles_n * B + cus - 1) / cus;
+    const double large = 2.0 + rounds * (8.5 + (p.path == PATH_DMA16 ? 0.0212 : 0.0272) * T), small = 3.0 + rounds128 * (1.4 + 0.0062 * T);
+    const bool cached = B * T * (P + D) * 2 <= (int64_t(256) << 20);
+    k.small = cached && small < (rounds == 1 ? 0.95 : 0.9) * large && (rounds == 1 || T >= 128);
+    k.by_far = k.small && (rounds == 1 || small < 0.8 * large);
+  }
+  return k;
+}
+
 struct WsLayout { size_t factors, partials, scratch, total; };
 
 // Number of squared-norm partials per sample the explicit schedule's norm kernel writes.
@@ -309,11 +334,17 @@ int64_t gram_blocks(int64_t T, int64_t P, int64_t D, int dtype) {
 }
 
 // mode: FLASHDP_SCHEDULE_TWOPASS / _GHOST (no scratch), _SCRATCH (input-width scratch), _EXPLICIT (fp32 scratch)
-WsLayout ws_layout(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype, int mode) {
+// small: room for the norm partials of 128 x 128 tiles where the scratch schedule parks on those (park_plan); without it the
+// size that suffices with the plan's own tiles.
+WsLayout ws_layout(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype, int mode, bool small = false) {
   WsLayout w;
   w.factors = 0;
   w.partials = align_up((size_t)B * 4, 256);
   size_t n_part = (size_t)p.tiles_m * p.tiles_n;
+  if (mode == FLASHDP_SCHEDULE_SCRATCH && small) {
+    const Park k = park_plan(p, B, T, P, D, dtype);
+    if (k.small) n_part = (size_t)k.tiles_m * k.tiles_n;
+  }
   if (mode == FLASHDP_SCHEDULE_EXPLICIT) n_part = std::max(n_part, (size_t)explicit_chunks(P, D));
   if (mode == FLASHDP_SCHEDULE_GHOST) {
     const size_t nb = (size_t)gram_blocks(T, P, D, dtype);
@@ -530,7 +561,8 @@ FusedWs fused_ws(int64_t B, int64_t P, int64_t D) {
   return w;
 }
 
-size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype, int mode) {
+// small = false: the least the schedule runs in; true: what it is fastest in.
+size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype, int mode, bool small = false) {
   if (mode == FLASHDP_SCHEDULE_FUSED) {
     // a layer the single-launch form does not apply to takes the scratch schedule; without a device, assume 256 CUs
     const int cus = device_cus();
@@ -538,7 +570,7 @@ size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype,
     mode = FLASHDP_SCHEDULE_SCRATCH;
   }
   const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
-  return ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode).total;
+  return ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode, small).total;
 }
 
 // Rows without a sequence (rows_dp.hip.h) are taken by every call that leaves the schedule to the library: nothing of
@@ -590,6 +622,24 @@ bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
   return dtype != FLASHDP_F32 && B <= MAX_FUSED_CLIP_B && agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20);
 }
 
+// The parking pass on 128 x 128 tiles (gemm_tile128.hip.h) of one layer or several: one workgroup per tile and sample.
+Tile128Layer park128(const flashdp_layer_t& L, const Park& p, int64_t B, int64_t T, float* partials, void* scratch) {
+  Tile128Layer a;
+  a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
+  a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.splits = (int)B;
+  a.partials = partials; a.scratch = scratch;
+  a.factors = nullptr; a.out = nullptr; a.noise_scale = 0.0f; a.accumulate = 0; a.seed = 0; a.layer = 0;
+  return a;
+}
+template <int DT>
+hipError_t launch_park128(const Tile128Args& g, hipStream_t st) {
+  auto kern = gemm_tile128_kernel<MODE_SPILL, DT>;
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), Tile128Cfg::LDS_BYTES);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[g.n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, g);
+  return hipGetLastError();
+}
+
 // Layers of one call that share their two launches (scratch schedule): those on the 128 x 128 kernel, which by make_plan's
 // rule have too few tiles to fill the chip with large ones, as many in a row as the workspace holds parked together.
 // Same kernels' code on the same tiles: results are bit-identical to one launch per layer.
@@ -597,19 +647,21 @@ bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
 // the path takes (bf16, together against one after the other: a GPT-2 block at B = 1, T = 1024, 37 us, 83 before, 56 when
 // the workspace holds three of the four; at B = 3, 83, 112; two layers of 2048 x 2048, T = 2048, 64, 75; eight of
 // 128 x 128, T = 1024, 19, 136).
+Park park_of(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
+  return park_plan(make_plan(B, T, L.d_in, L.d_out, dtype), B, T, L.d_in, L.d_out, dtype);
+}
 struct GroupSlot { size_t partials, scratch, end; };
-GroupSlot group_slot(const Plan& p, int64_t B, int64_t P, int64_t D, size_t begin) {
+GroupSlot group_slot(const Park& k, int64_t B, int64_t P, int64_t D, size_t begin) {
   GroupSlot g;
   g.partials = begin;
-  g.scratch = g.partials + align_up((size_t)B * p.tiles_m * p.tiles_n * 4, 256);
+  g.scratch = g.partials + align_up((size_t)B * k.tiles_m * k.tiles_n * 4, 256);
   g.end = g.scratch + align_up((size_t)B * P * D * 2, 256);
   return g;
 }
 bool group_ok(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || g_ctx.stages != FLASHDP_STAGE_ALL) return false;
-  const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
-  return p.path == PATH_128x4 && !p.any &&
-         fold_clip_ok(dtype, B, p.tiles_m * p.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
+  const Park k = park_of(L, B, T, dtype);
+  return k.small && fold_clip_ok(dtype, B, k.tiles_m * k.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
 }
 // Neither layer writes what the other reads or writes (a caller may pass one buffer twice: such layers keep their order).
 bool group_disjoint(const flashdp_layer_t& x, const flashdp_layer_t& y, int64_t B, int64_t T) {
@@ -627,24 +679,64 @@ bool group_disjoint(const flashdp_layer_t& x, const flashdp_layer_t& y, int64_t 
   };
   return !clash(x, y) && !clash(y, x);
 }
-// How many layers from the first on go into one launch (1: take the ordinary way).
-int group_length(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype, size_t ws_bytes) {
-  size_t used = 0;
-  int k = 0;
-  for (; k < n && k < GROUP_MAX && group_ok(layers[k], B, T, dtype); ++k) {
-    used = group_slot(make_plan(B, T, layers[k].d_in, layers[k].d_out, dtype), B, layers[k].d_in, layers[k].d_out, used).end;
-    if (used > ws_bytes) break;
-    bool apart = true;
-    for (int j = 0; j < k && apart; ++j) apart = group_disjoint(layers[j], layers[k], B, T);
+// Which of a run of layers go into one launch: group[l] for the first `n` layers (as many, in the caller's order, as may
+// share launches at all), in groups 0 .. *n_groups - 1 that the workspace holds.  Either in order, or the largest first with
+// whatever still fits the same round of 128 x 128 tiles, whichever takes fewer rounds: tiles of a round all run at once, and
+// a few too many cost another one (a GPT-2 block at B = 1, T = 1024, with room for three of its four layers: 288 + 144 tiles in
+// order, 252 + 180 so, 51 us a call and 46).
+int group_layers(const flashdp_layer_t* layers, int n_layers, int64_t B, int64_t T, int dtype, size_t ws_bytes, int* group, int* n_groups) {
+  Park park[GROUP_MAX];
+  int n = 0;
+  for (; n < n_layers && n < GROUP_MAX && group_ok(layers[n], B, T, dtype); ++n) {
+    park[n] = park_of(layers[n], B, T, dtype);
+    bool apart = group_slot(park[n], B, layers[n].d_in, layers[n].d_out, 0).end <= ws_bytes;
+    for (int j = 0; j < n && apart; ++j) apart = group_disjoint(layers[j], layers[n], B, T);
     if (!apart) break;
   }
-  return std::max(k, 1);
+  *n_groups = 0;
+  const int64_t cus = plan_cus();
+  int order[GROUP_MAX], best[GROUP_MAX];
+  auto tiles = [&](int l) { return (int64_t)park[l].tiles_m * park[l].tiles_n * B; };
+  double best_cost = 0.0;
+  for (int strategy = 0; strategy < 2; ++strategy) {
+    for (int l = 0; l < n; ++l) { order[l] = l; group[l] = -1; }
+    if (strategy == 1) std::stable_sort(order, order + n, [&](int x, int y) { return tiles(x) > tiles(y); });
+    double cost = 0.0;
+    int count = 0;
+    for (int i = 0; i < n; ++i) {
+      if (group[order[i]] >= 0) continue;
+      size_t used = 0;
+      int64_t sum = 0;
+      for (int j = i; j < n; ++j) {
+        const int l = order[j];
+        if (group[l] >= 0) continue;
+        const size_t end = group_slot(park[l], B, layers[l].d_in, layers[l].d_out, used).end;
+        const bool same_round = sum == 0 || (sum + tiles(l) + cus - 1) / cus == (sum + cus - 1) / cus;
+        if (end > ws_bytes || (strategy == 1 && !same_round)) {
+          if (strategy == 0) break;
+          continue;
+        }
+        group[l] = count;
+        used = end;
+        sum += tiles(l);
+      }
+      cost += 8.0 + 3.0 + (double)((sum + cus - 1) / cus) * (1.4 + 0.0062 * T);   // two launches; see park_plan
+      ++count;
+    }
+    if (strategy == 0 || cost < best_cost) {
+      best_cost = cost;
+      *n_groups = count;
+      std::copy(group, group + n, best);
+    }
+  }
+  std::copy(best, best + n, group);
+  return n;
 }
 
 template <int DT>
 hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype, char* ws, hipStream_t st,
                      bool accumulate, bool add_noise) {
-  GroupedGemmArgs g;
+  Tile128Args g;
   GroupedTailArgs t;
   g.n = t.n = n;
   t.B = (int)B;
@@ -652,30 +744,21 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
   size_t used = 0;
   for (int l = 0; l < n; ++l) {
     const flashdp_layer_t& L = layers[l];
-    const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
+    const Park p = park_of(L, B, T, dtype);
     const GroupSlot s = group_slot(p, B, L.d_in, L.d_out, used);
     used = s.end;
-    GemmArgs& a = g.layer[l];
-    a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
-    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
-    a.partials = reinterpret_cast<float*>(ws + s.partials);
-    a.scratch = ws + s.scratch;
-    a.factors = nullptr; a.out = L.out_grad; a.accumulate = 0; a.trace = nullptr;
+    g.layer[l] = park128(L, p, B, T, reinterpret_cast<float*>(ws + s.partials), ws + s.scratch);
     GroupedTailArgs::Layer& q = t.layer[l];
-    q.scratch = a.scratch; q.partials = a.partials; q.out_norms = L.out_norms; q.out = L.out_grad;
+    q.scratch = ws + s.scratch; q.partials = g.layer[l].partials; q.out_norms = L.out_norms; q.out = L.out_grad;
     q.S = (size_t)L.d_in * L.d_out; q.seed = L.seed; q.C = L.C; q.noise_scale = add_noise ? L.sigma * L.C : 0.0f;
     q.layer = L.layer; q.tiles = p.tiles_m * p.tiles_n; q.accumulate = accumulate ? 1 : 0;
-    g.first[l + 1] = g.first[l] + (int)(q.tiles * B);   // a few hundred each by the path's rule
+    g.first[l + 1] = g.first[l] + (int)align_up((size_t)q.tiles * B, 8);   // a few hundred each by the path's rule
     t.first[l + 1] = t.first[l] + (int)((q.S / 8 + 255) / 256);
   }
-  auto kern = gemm_mfma_kernel<Cfg128x4, MODE_SPILL, DT, false, GroupedGemmArgs>;
-  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), Cfg128x4::LDS_BYTES);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[n]), dim3(Cfg128x4::NT), Cfg128x4::LDS_BYTES, st, g);
-  e = hipGetLastError();
+  hipError_t e = launch_park128<DT>(g, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((clip_aggregate16_grouped_kernel<DT_BF16>), dim3((unsigned)t.first[n]), dim3(256), 0, st, t);
-  g_ctx.last_kernel = path_kernel_name(PATH_128x4);
+  g_ctx.last_kernel = "gemm_tile128_kernel";
   return hipGetLastError();
 }
 
@@ -761,7 +844,7 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
     a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
     a.splits = (int)norm_splits;
-    a.partials = partials; a.factors = factors; a.out = nullptr;
+    a.partials = partials; a.scratch = nullptr; a.factors = factors; a.out = nullptr;
     a.noise_scale = noise_scale; a.accumulate = accumulate ? 1 : 0; a.seed = L.seed; a.layer = L.layer;
     sum.layer[l] = a;
     sum.layer[l].splits = splits;
@@ -797,7 +880,8 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
 // aggregation grid of the overlapped schedule.
 // Samples [s0, s0 + B) of the layer's batch are processed (B is the number of samples of THIS call: the whole
 // batch, or one chunk of it when the workspace holds fewer parked samples than the batch has).
-int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mode, char* ws, hipStream_t st,
+// ws_bytes: what the workspace holds (the schedule's need with the plan's own tiles, or more).
+int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mode, char* ws, size_t ws_bytes, hipStream_t st,
               bool accumulate, bool add_noise, int parts = FLASHDP_STAGE_ALL, int persistent_grid = 0, int64_t s0 = 0) {
   flashdp_layer_t L = L0;
   L.X = static_cast<const char*>(L0.X) + (size_t)s0 * T * L0.d_in * elt_bytes(dtype);
@@ -831,7 +915,11 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
   const int stages = g_ctx.stages & parts;
   const int64_t P = L.d_in, D = L.d_out;
   const Plan plan = make_plan(B, T, P, D, dtype);
-  const WsLayout wl = ws_layout(plan, B, T, P, D, dtype, mode);
+  // (a call of the overlapped schedule comes in parts)
+  const Park park = park_plan(plan, B, T, P, D, dtype);
+  const bool small = use_scratch && park.small && parts == FLASHDP_STAGE_ALL &&
+                     ws_layout(plan, B, T, P, D, dtype, mode, true).total <= ws_bytes;
+  const WsLayout wl = ws_layout(plan, B, T, P, D, dtype, mode, small);
   GemmArgs a;
   a.X = L.X; a.dY = L.dY;
   a.B = (int)B; a.T = (int)T; a.P = (int)P; a.D = (int)D;
@@ -843,7 +931,7 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
   a.out = L.out_grad;
   a.accumulate = accumulate ? 1 : 0;
   a.trace = nullptr;
-  const int tiles = plan.tiles_m * plan.tiles_n;
+  const int tiles = small ? park.tiles_m * park.tiles_n : plan.tiles_m * plan.tiles_n;
   const size_t S = (size_t)D * P;
   const float noise_scale = add_noise ? L.sigma * L.C : 0.0f;
   g_ctx.last_kernel = path_kernel_name(plan.path);
@@ -869,7 +957,17 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
       HIP_TRY(hipGetLastError());
     }
   } else if (use_scratch) {
-    if (stages & FLASHDP_STAGE_CONTRACT) HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
+    if (small) g_ctx.last_kernel = "gemm_tile128_kernel";
+    if ((stages & FLASHDP_STAGE_CONTRACT) && small) {
+      Tile128Args g;
+      g.n = 1;
+      g.first[0] = 0;
+      g.first[1] = (int)align_up((size_t)tiles * B, 8);
+      g.layer[0] = park128(L, park, B, T, a.partials, a.scratch);
+      HIP_TRY(dtype == FLASHDP_BF16 ? launch_park128<DT_BF16>(g, st) : launch_park128<DT_F16>(g, st));
+    } else if (stages & FLASHDP_STAGE_CONTRACT) {
+      HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
+    }
     // 16-bit scratch: the inter-block reduce and the clip factors are done by the streaming
     // kernel itself (one launch less per layer) when that is cheap: every workgroup reads all B * tiles partials, so
     // with the ordinary grid (one workgroup per 2048 elements) this is only done while those redundant reads stay
@@ -961,7 +1059,9 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
       // (not the 384x192 / 192x384 kernels: their 248 registers leave no room for an aggregation wave beside two
       // contraction waves per SIMD, and a bounded aggregation workgroup that takes a CU would keep the next
       // contraction workgroup out of it until its whole share is done)
-      ok = !p.any && (p.path == PATH_256x8k32 || p.path == PATH_256x8 || p.path == PATH_DMA || p.path == PATH_DMA16) && ((size_t)layers[l].d_in * layers[l].d_out) % 8 == 0;
+      // and layers that park on small tiles by far the faster way are left to that, unless the schedule is asked for
+      ok = !(schedule == FLASHDP_SCHEDULE_AUTO && park_plan(p, b, T, layers[l].d_in, layers[l].d_out, dtype).by_far) &&
+           !p.any && (p.path == PATH_256x8k32 || p.path == PATH_256x8 || p.path == PATH_DMA || p.path == PATH_DMA16) && ((size_t)layers[l].d_in * layers[l].d_out) % 8 == 0;
     }
     return ok;
   };
@@ -1057,13 +1157,16 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     size_t wish = 0;
     if (mode == FLASHDP_SCHEDULE_SCRATCH && n_layers >= 2) {
       for (int l = 0; l < n_layers && l < GROUP_MAX && group_ok(layers[l], B, T, dtype); ++l) {
-        const size_t end = group_slot(make_plan(B, T, layers[l].d_in, layers[l].d_out, dtype), B, layers[l].d_in, layers[l].d_out, wish).end;
+        const size_t end = group_slot(park_of(layers[l], B, T, dtype), B, layers[l].d_in, layers[l].d_out, wish).end;
         if (end > (size_t(64) << 20)) break;
         wish = end;
       }
     }
+    size_t best = need;
+    if (mode == FLASHDP_SCHEDULE_SCRATCH)
+      for (int l = 0; l < n_layers; ++l) best = std::max(best, layer_ws_bytes(layers[l], B, T, dtype, mode, true));
     void* p = nullptr; size_t got = 0;
-    st = owned_workspace(need, &p, &got, wish);
+    st = owned_workspace(best, &p, &got, wish);
     if (st != FLASHDP_OK) return st;
     ws = static_cast<char*>(p);
     ws_bytes = got;
@@ -1123,12 +1226,12 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
       const flashdp_layer_t& Lr = layers[it.layer];
       char* wsl = ws + (size_t)(k & 1) * slot;
       if (k >= 2) HIP_TRY(hipStreamWaitEvent(main_st, side->done[k - 2], 0));   // slot free again
-      st = run_layer(Lr, it.b, T, dtype, FLASHDP_SCHEDULE_SCRATCH, wsl, main_st, it.acc, it.noise, FLASHDP_STAGE_CONTRACT, 0, it.s0);
+      st = run_layer(Lr, it.b, T, dtype, FLASHDP_SCHEDULE_SCRATCH, wsl, slot, main_st, it.acc, it.noise, FLASHDP_STAGE_CONTRACT, 0, it.s0);
       if (st != FLASHDP_OK) return st;
       HIP_TRY(hipEventRecord(side->ready[k], main_st));
       HIP_TRY(hipStreamWaitEvent(side->stream, side->ready[k], 0));
       // the last item has nothing to hide behind: ordinary grid
-      st = run_layer(Lr, it.b, T, dtype, FLASHDP_SCHEDULE_SCRATCH, wsl, side->stream, it.acc, it.noise,
+      st = run_layer(Lr, it.b, T, dtype, FLASHDP_SCHEDULE_SCRATCH, wsl, slot, side->stream, it.acc, it.noise,
                      FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE, k + 1 < n_items ? grid : 0, it.s0);
       if (st != FLASHDP_OK) return st;
       HIP_TRY(hipEventRecord(side->done[k], side->stream));
@@ -1140,16 +1243,28 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
   }
   for (int k = 0; k < n_items; ++k) {
     if (mode == FLASHDP_SCHEDULE_SCRATCH && chunk == B && n_layers >= 2) {   // items are the layers in the caller's order
-      const int n = group_length(layers + k, n_layers - k, B, T, dtype, ws_bytes);
-      if (n >= 2) {
-        HIP_TRY(dtype == FLASHDP_BF16 ? run_group<DT_BF16>(layers + k, n, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0)
-                                      : run_group<DT_F16>(layers + k, n, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0));
+      int group[GROUP_MAX], n_groups = 0;
+      const int n = group_layers(layers + k, n_layers - k, B, T, dtype, ws_bytes, group, &n_groups);
+      for (int gi = 0; gi < n_groups; ++gi) {
+        flashdp_layer_t in_group[GROUP_MAX];
+        int m = 0;
+        for (int l = 0; l < n; ++l)
+          if (group[l] == gi) in_group[m++] = layers[k + l];
+        if (m == 1) {
+          st = run_layer(in_group[0], B, T, dtype, mode, ws, ws_bytes, main_st, accumulate != 0, add_noise != 0);
+          if (st != FLASHDP_OK) return st;
+        } else {
+          HIP_TRY(dtype == FLASHDP_BF16 ? run_group<DT_BF16>(in_group, m, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0)
+                                        : run_group<DT_F16>(in_group, m, B, T, dtype, ws, main_st, accumulate != 0, add_noise != 0));
+        }
+      }
+      if (n > 0) {
         k += n - 1;
         continue;
       }
     }
     const Item& it = items[k];
-    st = run_layer(layers[it.layer], it.b, T, dtype, mode, ws, main_st, it.acc, it.noise, FLASHDP_STAGE_ALL, 0, it.s0);
+    st = run_layer(layers[it.layer], it.b, T, dtype, mode, ws, ws_bytes, main_st, it.acc, it.noise, FLASHDP_STAGE_ALL, 0, it.s0);
     if (st != FLASHDP_OK) return st;
   }
   g_ctx.last_schedule = mode == FLASHDP_SCHEDULE_SCRATCH ? "scratch" : mode == FLASHDP_SCHEDULE_EXPLICIT ? "explicit"
@@ -1190,7 +1305,7 @@ int flashdp_linear_dp_grad_static(const void* X, const void* dY, int64_t B, int6
   if (st != FLASHDP_OK) return st;
   // Every part of the workspace a call reads it has written itself first (partials by the contraction, factors
   // by the clip kernel, the parked tiles by the spill), so nothing has to be cleared between calls.
-  st = run_layer(L, B, T, dtype, FLASHDP_SCHEDULE_SCRATCH, ws, static_cast<hipStream_t>(stream), false, true);
+  st = run_layer(L, B, T, dtype, FLASHDP_SCHEDULE_SCRATCH, ws, FLASHDP_STATIC_SCRATCH_BYTES, static_cast<hipStream_t>(stream), false, true);
   if (st == FLASHDP_OK) g_ctx.last_schedule = "scratch";
   return st;
 }
@@ -1201,7 +1316,7 @@ size_t flashdp_workspace_bytes(const flashdp_layer_t* layers, int n_layers, int6
   for (int l = 0; l < n_layers; ++l) {
     if (check_dims(B, T, layers[l].d_in, layers[l].d_out) != FLASHDP_OK) return 0;
     const int m = (schedule == FLASHDP_SCHEDULE_AUTO || schedule == FLASHDP_SCHEDULE_OVERLAP) ? FLASHDP_SCHEDULE_SCRATCH : schedule;
-    need = std::max(need, layer_ws_bytes(layers[l], B, T, dtype, m));
+    need = std::max(need, layer_ws_bytes(layers[l], B, T, dtype, m, true));
   }
   if (schedule == FLASHDP_SCHEDULE_OVERLAP) need = 2 * align_up(need, 256);
   return need;
@@ -1213,7 +1328,7 @@ size_t flashdp_workspace_bytes_chunked(const flashdp_layer_t* layers, int n_laye
   size_t need = 0;
   for (int l = 0; l < n_layers; ++l) {
     if (check_dims(B, T, layers[l].d_in, layers[l].d_out) != FLASHDP_OK) return 0;
-    need = std::max(need, layer_ws_bytes(layers[l], chunk_samples, T, dtype, FLASHDP_SCHEDULE_SCRATCH));
+    need = std::max(need, layer_ws_bytes(layers[l], chunk_samples, T, dtype, FLASHDP_SCHEDULE_SCRATCH, true));
   }
   return (size_t)slots * align_up(need, 256);
 }

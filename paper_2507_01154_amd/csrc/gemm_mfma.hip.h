@@ -349,35 +349,15 @@ constexpr bool accum_totals = MODE == MODE_ACCUM && ANY && Cfg::FM * Cfg::FN <= 
 // chip by themselves (a GPT-2 block at one sample has 36 to 144 workgroups per layer on 256 CUs), which are bound by the
 // length of one workgroup's reduction and by the gaps between launches, not by a rate.
 constexpr int GROUP_MAX = 8;
-struct GroupedGemmArgs {
-  int n;
-  int first[GROUP_MAX + 1];
-  GemmArgs layer[GROUP_MAX];
-};
 template <int N>
 __device__ __forceinline__ int group_of(const int (&first)[N], int n, int bid) {
   int l = 0;
   while (l + 1 < n && bid >= first[l + 1]) ++l;
   return l;
 }
-// The layer that this workgroup belongs to, and which of the layer's workgroups it is.
-__device__ __forceinline__ const GemmArgs& layer_of(const GemmArgs& a, int* bid) {
-  *bid = blockIdx.x;
-  return a;
-}
-__device__ __forceinline__ const GemmArgs& layer_of(const GroupedGemmArgs& g, int* bid) {
-  const int l = group_of(g.first, g.n, blockIdx.x);
-  *bid = (int)blockIdx.x - g.first[l];
-  return g.layer[l];
-}
 
-// Args: GemmArgs, or GroupedGemmArgs for several layers.  One kernel template for both rather than a shared device
-// function: inlined from a function, the accumulating pass of the 128 x 128 tiling waits for all of the next tile's loads
-// before it stores the first (bf16, non-private, 728 x 912, B = 6, T = 1402: 85 us, 69 so).
-template <typename Cfg, int MODE, int DT, bool ANY = false, typename Args = GemmArgs>
-__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(const Args args) {
-  int bid;
-  const GemmArgs& a = layer_of(args, &bid);
+template <typename Cfg, int MODE, int DT, bool ANY = false>
+__global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(const GemmArgs a) {
   constexpr int BM = Cfg::BM, BN = Cfg::BN, BK = Cfg::BK, NT = Cfg::NT;
   constexpr int FM = Cfg::FM, FN = Cfg::FN, LDA = Cfg::LDA, LDB = Cfg::LDB;
   constexpr int CA = Cfg::CA, CB = Cfg::CB;
@@ -390,7 +370,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::WAVES_PER_EU) void gemm_mfma_kernel(c
 
   const int tiles = a.tiles_m * a.tiles_n;
   const int total = (MODE == MODE_ACCUM) ? tiles : tiles * a.B;
-  const int item = xcd_remap(bid, total);
+  const int item = xcd_remap(blockIdx.x, total);
   const int sample0 = (MODE == MODE_ACCUM) ? 0 : item / tiles;
   const int n_samples = (MODE == MODE_ACCUM) ? a.B : 1;
   const int tile = (MODE == MODE_ACCUM) ? item : item - sample0 * tiles;

@@ -1,7 +1,9 @@
 // Contraction on 128 x 128 tiles that walks over several samples without draining its pipeline: the two passes of the
-// two-pass schedule for short sequences.
+// two-pass schedule for short sequences, and, one sample a workgroup, the parking pass of layers whose 256 x 256 tiles are
+// too few to fill the chip or end in a nearly empty round (the rule is in park_plan; 768 x 3072, B = 1, T = 1024, bf16: 14.8 us
+// with tiles staged through registers, 11.5 so; B = 4: 31.6 on 256 x 256 tiles, 26.9).
 //
-// Why.  With few tokens a per-sample gradient tile is a handful of k-tiles of work, and parking it (2 + 2 bytes an element
+// Why two passes.  With few tokens a per-sample gradient tile is a handful of k-tiles of work, and parking it (2 + 2 bytes an element
 // and sample, beside 4 T / 1e15 seconds of arithmetic) is most of the time, the rest being start and end of one workgroup per
 // tile and sample.  Computing every G_i twice costs 2 T FLOP an element and sample instead and nothing is parked; and a
 // workgroup that keeps its tile and walks over the samples loads the next sample's first k-tiles while it multiplies the
@@ -35,7 +37,8 @@ struct Tile128Layer {
   int B, T, P, D;
   int tiles_m, tiles_n;  // ceil(D / 128), ceil(P / 128)
   int splits;            // workgroups per tile: split r walks over samples [B r / splits, B (r + 1) / splits)
-  float* partials;       // [B][tiles_m * tiles_n][4] squared-norm partial sums, one per wave (NORM)
+  float* partials;       // squared-norm partial sums: [B][tiles_m * tiles_n][4], one per wave (NORM); [B][tiles_m * tiles_n] (SPILL)
+  void* scratch;         // [B][D][P] bfloat16 (SPILL)
   const float* factors;  // [B] clip factors (ACCUM)
   float* out;            // [D][P], or fp32 partial sums [splits][D][P] where splits > 1 (ACCUM)
   float noise_scale;     // added by the kernel itself where splits == 1
@@ -53,7 +56,8 @@ struct Tile128Cfg {
   static constexpr int NT = 256;
   static constexpr int LDS_BYTES = 2 * tile128_plan::STAGES * tile128_plan::OPERAND_ELEMS * 2;   // 64 KB
   static constexpr int OUT_PITCH = 128 + 4;                                                      // floats; 64 rows at a time are staged
-  static_assert(64 * OUT_PITCH * 4 <= LDS_BYTES, "output rows fit the ring");
+  static constexpr int PARK_PITCH = 128 + 8;                                                     // 16-bit elements: 16-byte aligned rows
+  static_assert(64 * OUT_PITCH * 4 <= LDS_BYTES && 128 * PARK_PITCH * 2 + 16 <= LDS_BYTES, "output rows fit the ring");
 };
 
 // The first product of a sample: c = a b.  As mfma16_inplace the accumulators are outputs of inline assembly, so that they
@@ -86,7 +90,7 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
 
 template <int MODE, int DT>
 __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args g) {
-  static_assert(MODE == MODE_NORM || MODE == MODE_ACCUM, "the two passes of the two-pass schedule");
+  static_assert(MODE == MODE_NORM || MODE == MODE_ACCUM || MODE == MODE_SPILL, "the passes this tiling has");
   namespace tp = tile128_plan;
   constexpr int STAGES = tp::STAGES;
   extern __shared__ __attribute__((aligned(16))) unsigned short lds[];
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
       const float w = wave_sum_to_lane63((ss[0] + ss[1]) + (ss[2] + ss[3]));
       const float sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), 63));
       per_lane = lane == s - s_base ? sum : per_lane;
-    } else {
+    } else if constexpr (MODE == MODE_ACCUM) {
       const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, per_lane), s - s_base));
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -257,6 +261,37 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // loads past the end still write zeros into LDS
 
   if constexpr (MODE == MODE_NORM) lanes_to_memory();
+  if constexpr (MODE == MODE_SPILL) {
+    // One sample (splits == B).  The tile leaves in bfloat16 through LDS, in whole rows, and its squared norm is taken as parked
+    // (see tile_epilogue).  acc[i][j][r] = element (64 wave_m + 16 i + lane % 16, 64 wave_n + 16 j + 4 (lane / 16) + r) of the tile.
+    constexpr int EP = Tile128Cfg::PARK_PITCH;
+    float* const red = (float*)(lds + 128 * EP);
+    unsigned short* const st = lds + (64 * wave_m + (lane & 15)) * EP + 64 * wave_n + 4 * (lane >> 4);
+    float ss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint2 v;
+        v.x = pack2_16bit<DT_BF16>(acc[i][j][0], acc[i][j][1]);
+        v.y = pack2_16bit<DT_BF16>(acc[i][j][2], acc[i][j][3]);
+        const float r0 = __builtin_bit_cast(float, v.x << 16), r1 = __builtin_bit_cast(float, v.x & 0xFFFF0000u);
+        const float r2 = __builtin_bit_cast(float, v.y << 16), r3 = __builtin_bit_cast(float, v.y & 0xFFFF0000u);
+        ss = fmaf(r0, r0, ss); ss = fmaf(r1, r1, ss); ss = fmaf(r2, r2, ss); ss = fmaf(r3, r3, ss);
+        *(uint2*)(st + (i * 16) * EP + j * 16) = v;
+      }
+    const float w = wave_sum_to_lane63(ss);
+    if (lane == 63) red[wave] = w;
+    __syncthreads();
+    if (tid == 0) a.partials[(size_t)s_begin * tiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+    unsigned short* const sc = (unsigned short*)a.scratch + (size_t)s_begin * a.D * a.P;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int r = (tid >> 4) + 16 * it, row = m0 + r, col = n0 + 8 * (tid & 15);
+      if (row < a.D && col < a.P)   // P is a multiple of 8 on this path: a chunk is all in or all out
+        __builtin_nontemporal_store(*(const u32x4_t*)(lds + r * EP + 8 * (tid & 15)), (u32x4_t*)(sc + (size_t)row * a.P + col));
+    }
+  }
   if constexpr (MODE == MODE_ACCUM) {
     // tot[i][j][r] = element (m0 + 64 wave_m + 16 i + lane % 16, n0 + 64 wave_n + 16 j + 4 (lane / 16) + r).  64 rows at a
     // time go through LDS, so that whole rows are written and the noise generator stands in one loop.

@@ -920,6 +920,36 @@ def test_short_sequences_take_two_passes_on_small_tiles(B, T, dims, dtype):
         assert float((got - 2 * o).abs().max()) <= 1e-6 * 2 * float(o.abs().max()) + 3 * 2.0 ** -24 * (3 * L["C"] + 2 * float(o.abs().max()))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,T,P,D", [(16, 97, 768, 760), (5, 333, 1032, 1928), (3, 40, 1480, 2056), (3, 2100, 1096, 2312), (12, 130, 1288, 1288)])
+def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype):
+    # layers of enough 256 x 256 tiles for the large-tile kernel that park on 128 x 128 ones; a workspace with room for no
+    # more norm partials than the large tiles have is still accepted, and takes those.  Tolerances of parked tiles.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B * T)
+    X = torch.randn((B, T, P), generator=g, device=DEV).to(dtype)
+    dY = (torch.randn((B, T, D), generator=g, device=DEV) * 0.05 * 10 ** (2 * torch.rand((B, 1, 1), generator=g, device=DEV) - 1)).to(dtype)
+    G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+    n = G.flatten(1).norm(dim=1)
+    c = 1.0 / torch.clamp(n, min=1.0)
+    want, bound = (G * c[:, None, None]).sum(0), (G.abs() * c[:, None, None]).sum(0)
+    out, norms = torch.empty((D, P), device=DEV), torch.empty((B,), device=DEV)
+    L = [dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)]
+    code = F.dtype_code(X)
+    up = lambda k: (k + 255) // 256 * 256
+    least = up(4 * B) + up(4 * B * (-(-P // 256)) * (-(-D // 256))) + up(2 * B * P * D)
+    full = F.flashdp_workspace_bytes(L, B, T, code, "scratch")
+    for size, kernel in ((full, "gemm_tile128_kernel"), (least, "gemm_mfma_dma16_kernel")):
+        out.fill_(float("nan"))
+        norms.fill_(float("nan"))
+        F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((size,), dtype=torch.uint8, device=DEV))
+        assert F.flashdp_last_schedule() == "scratch" and F.flashdp_last_kernel() == kernel
+        assert float((out - want).norm() / want.norm()) <= 4e-3 and float(((norms - n).abs() / n).max()) <= 1e-4
+        assert bool(torch.all((out - want).abs() <= 1e-4 * float(bound.pow(2).mean().sqrt()) + 2.0 ** -8 * bound))
+    with pytest.raises(F.FlashDPError):
+        F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
+
+
 @pytest.mark.parametrize("schedule", ["scratch", "twopass", "explicit", "ghost"])
 def test_nan_in_one_sample_poisons_the_output_instead_of_passing_unclipped(schedule):
     base = W.WORKLOADS["gpt2_small_mlp_up"]
