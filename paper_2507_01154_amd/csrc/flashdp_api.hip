@@ -19,6 +19,7 @@
 #include "gemm_mfma_dma.hip.h"
 #include "gemm_mfma_dma_shaped.hip.h"
 #include "gemm_mfma_dma16.hip.h"
+#include "gemm_f32x3.hip.h"
 #include "gemm_mfma_f32.hip.h"
 #include "gemm_mfma_streamk.hip.h"
 #include "fused_dp.hip.h"
@@ -303,7 +304,13 @@ const char* path_kernel_name(Path p) {
 struct Park { bool small, by_far; int tiles_m, tiles_n; };
 Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
   Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128)};
-  if (dtype == FLASHDP_F32 || p.any || env().tile != 0) return k;
+  if (p.any || env().tile != 0) return k;
+  if (dtype == FLASHDP_F32) {
+    // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for layers of one small
+    // tile and few tokens, which are all launch and latency (36 x 40, B = 4, T = 16: 8.0 us, 8.6), and T < 4 (see there).
+    k.small = P % 4 == 0 && D % 4 == 0 && (T + 96) * std::max(P, D) * 4 < (int64_t(1) << 31) && T >= (p.path == PATH_F32 ? 4 : 32);
+    return k;
+  }
   if (p.path == PATH_128x4) k.small = k.by_far = true;
   if (p.path == PATH_DMA16 || p.path == PATH_DMA_384x192 || p.path == PATH_DMA_192x384) {
     const int64_t cus = plan_cus();
@@ -633,10 +640,14 @@ Tile128Layer park128(const flashdp_layer_t& L, const Park& p, int64_t B, int64_t
 }
 template <int DT>
 hipError_t launch_park128(const Tile128Args& g, hipStream_t st) {
-  auto kern = gemm_tile128_kernel<MODE_SPILL, DT>;
-  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), Tile128Cfg::LDS_BYTES);
+  void (*kern)(Tile128Args);
+  int lds_bytes;
+  if constexpr (DT == DT_F32) { kern = gemm_f32x3_kernel; lds_bytes = F32x3Cfg::LDS_BYTES; }
+  else { kern = gemm_tile128_kernel<MODE_SPILL, DT>; lds_bytes = Tile128Cfg::LDS_BYTES; }
+  static_assert(F32x3Cfg::NT == Tile128Cfg::NT, "one launch shape");
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[g.n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, g);
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[g.n]), dim3(Tile128Cfg::NT), lds_bytes, st, g);
   return hipGetLastError();
 }
 
@@ -957,14 +968,14 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
       HIP_TRY(hipGetLastError());
     }
   } else if (use_scratch) {
-    if (small) g_ctx.last_kernel = "gemm_tile128_kernel";
+    if (small) g_ctx.last_kernel = dtype == FLASHDP_F32 ? "gemm_f32x3_kernel" : "gemm_tile128_kernel";
     if ((stages & FLASHDP_STAGE_CONTRACT) && small) {
       Tile128Args g;
       g.n = 1;
       g.first[0] = 0;
       g.first[1] = (int)align_up((size_t)tiles * B, 8);
       g.layer[0] = park128(L, park, B, T, a.partials, a.scratch);
-      HIP_TRY(dtype == FLASHDP_BF16 ? launch_park128<DT_BF16>(g, st) : launch_park128<DT_F16>(g, st));
+      HIP_TRY(dtype == FLASHDP_BF16 ? launch_park128<DT_BF16>(g, st) : dtype == FLASHDP_F16 ? launch_park128<DT_F16>(g, st) : launch_park128<DT_F32>(g, st));
     } else if (stages & FLASHDP_STAGE_CONTRACT) {
       HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
     }

@@ -1,0 +1,231 @@
+// The parking pass for fp32 inputs on the bfloat16 matrix cores: every operand element is split into three bfloat16 parts that
+// add up to it exactly, x = x1 + x2 + x3 (8 + 8 + 8 significant bits, each part the rounding of what the ones before leave),
+// and a product is formed of the six pairs that matter, x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1.  The three pairs left
+// out are below 2^-25 of the product, less than the rounding of one fp32 addition.
+//
+// Why.  Bound by the fp32 matrix rate (157 TFLOP/s) before; six bfloat16 products on a sixteen times faster unit.  A wave
+// issues six times 16 matrix instructions a k-tile, so the splitting (about 9 vector instructions an element) runs beside the other
+// workgroup's products.  128 x 128 tiles, 4 waves of 64 x 64, one 48 KB LDS stage (3 parts x 2 operands x 32 rows of 128),
+// the next k-tile in registers meanwhile, two workgroups per CU.
+//
+// fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 1954, 1314 (210 TFLOP/s); 768 x 3072,
+// B = 4, T = 1024: 257, 143; 64 x 448, B = 14, T = 1024: 235, 60; 128 x 13184, B = 1, T = 276: 79, 21; 1028 x 764, B = 8, T = 333: 96, 35.
+// Relative error of a gradient against fp64: T = 2048: 8.1e-7, 7.2e-7; T = 333: 3.3e-7, 2.8e-7; T = 16: 7.4e-8, 3.4e-8 (fewer
+// additions to one accumulator); level at T = 2, which stays with the fp32 instructions.
+//
+// What the split does not cover is left to a plain fp32 loop over the tile, decided per workgroup: sums that are not finite
+// (an infinity times a part that is zero or of the other sign is NaN; as in the other kernels it also meets the zeros
+// beyond a ragged edge, which makes the sample's norm NaN) or whose squares overflow, and operands below 2^-109,
+// whose last part would be subnormal.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gemm_mfma.hip.h"
+#include "gemm_tile128.hip.h"
+#include "tile128_plan.h"
+
+namespace flashdp {
+
+struct F32x3Cfg {
+  static constexpr int NT = 256;
+  static constexpr int PART = tile128_plan::OPERAND_ELEMS;        // elements of one part of one operand tile
+  static constexpr int LDS_BYTES = 6 * PART * 2;                  // 48 KB
+  static constexpr int OUT_PITCH = 128 + 4;
+  static_assert(64 * OUT_PITCH * 4 <= LDS_BYTES, "output rows fit the stage");
+};
+
+// The three parts of two floats (low half: a); least: the smallest magnitude so far as twice the bits less one, so that zero
+// is the largest.
+__device__ __forceinline__ void split3(float a, float b, uint32_t* parts, uint32_t* least) {
+  const uint32_t p1 = pack2_16bit<DT_BF16>(a, b);
+  const float ra = a - __builtin_bit_cast(float, p1 << 16), rb = b - __builtin_bit_cast(float, p1 & 0xFFFF0000u);
+  const uint32_t p2 = pack2_16bit<DT_BF16>(ra, rb);
+  const float sa = ra - __builtin_bit_cast(float, p2 << 16), sb = rb - __builtin_bit_cast(float, p2 & 0xFFFF0000u);
+  parts[0] = p1;
+  parts[1] = p2;
+  parts[2] = pack2_16bit<DT_BF16>(sa, sb);
+  *least = min(min(*least, (__builtin_bit_cast(uint32_t, a) << 1) - 1u), (__builtin_bit_cast(uint32_t, b) << 1) - 1u);
+}
+
+// a.scratch: [B][D][P] fp32; a.partials: [B][tiles]; a.splits == B (one workgroup per tile and sample).
+__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g) {
+  namespace tp = tile128_plan;
+  constexpr int PART = F32x3Cfg::PART;
+  extern __shared__ __attribute__((aligned(16))) unsigned short lds[];   // parts 1..3 of the dY tile, then of the X tile
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = wave >> 1;
+
+  const int l = group_of(g.first, g.n, blockIdx.x);
+  const Tile128Layer& a = g.layer[l];
+  const int bid = (int)blockIdx.x - g.first[l];
+  const int tiles = a.tiles_m * a.tiles_n, total = tiles * a.splits;
+  if (bid >= total) return;   // the whole workgroup, before any barrier
+  const int item = xcd_remap(bid, total);
+  const int sample = item / tiles, tile = item - sample * tiles;
+  int tm, tn;
+  tile_coords<8>(tile, a.tiles_m, a.tiles_n, &tm, &tn);
+  const int m0 = tm * tp::SIDE, n0 = tn * tp::SIDE;
+  const int T = a.T, P = a.P, D = a.D;
+
+  // ---- global -> registers: 8 columns (two 16-byte loads) of rows r0 and r0 + 16 of either operand; what lies outside reads 0
+  const int r0 = tid >> 4, c0 = 8 * (tid & 15);
+  const uint32_t a_bytes = (uint32_t)T * (uint32_t)D * 4u, b_bytes = (uint32_t)T * (uint32_t)P * 4u;
+  const char* const pa = (const char*)a.dY + (size_t)sample * a_bytes;
+  const char* const pb = (const char*)a.X + (size_t)sample * b_bytes;
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(pa, a_bytes), rsb = make_rsrc(pb, b_bytes);
+  uint32_t a_off[2], b_off[2];   // of the two loads; D and P are multiples of 4: a load is all in or all out
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    a_off[h] = m0 + c0 + 4 * h < D ? (uint32_t)(r0 * D + m0 + c0 + 4 * h) * 4u : 0x80000000u;
+    b_off[h] = n0 + c0 + 4 * h < P ? (uint32_t)(r0 * P + n0 + c0 + 4 * h) * 4u : 0x80000000u;
+  }
+  const uint32_t a_half = 16u * (uint32_t)D * 4u, b_half = 16u * (uint32_t)P * 4u;
+  u32x4_t raw_a[4], raw_b[4];
+  auto fetch = [&]() {   // and move on by a k-tile; rows >= T read as zeros
+#pragma unroll
+    for (int q = 0; q < 4; ++q) raw_a[q] = __builtin_amdgcn_raw_buffer_load_b128(rsa, (int)(a_off[q & 1] + (q >> 1) * a_half), 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) raw_b[q] = __builtin_amdgcn_raw_buffer_load_b128(rsb, (int)(b_off[q & 1] + (q >> 1) * b_half), 0, 0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) { a_off[h] += 2 * a_half; b_off[h] += 2 * b_half; }
+  };
+  uint32_t least = 0xFFFFFFFFu;
+  const int w_off = tp::kept_at(r0, c0);   // rows + 16 keep the swizzle
+  auto stage = [&]() {
+#pragma unroll
+    for (int op = 0; op < 2; ++op)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const u32x4_t lo = op == 0 ? raw_a[2 * q] : raw_b[2 * q], hi = op == 0 ? raw_a[2 * q + 1] : raw_b[2 * q + 1];
+        u32x4_t w[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // (copies: a bit cast of a vector's element itself reads the vector's first)
+          const uint32_t u0 = e < 2 ? lo[2 * e] : hi[2 * e - 4], u1 = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
+          uint32_t parts[3];
+          split3(__builtin_bit_cast(float, u0), __builtin_bit_cast(float, u1), parts, &least);
+#pragma unroll
+          for (int s = 0; s < 3; ++s) w[s][e] = parts[s];
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) *(u32x4_t*)(lds + (3 * op + s) * PART + w_off + q * 16 * tp::SIDE) = w[s];
+      }
+  };
+
+  int a_rd[4], b_rd[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    a_rd[i] = tp::frag_offset(lane, wave_m * 4 + i);
+    b_rd[i] = 3 * PART + tp::frag_offset(lane, wave_n * 4 + i);
+  }
+  auto frags = [&](const int (&rd)[4], int part, s16x8_t* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned short* p = lds + rd[i] + part * PART;
+      f[i] = __builtin_shufflevector(lds_read_tr(p), lds_read_tr(p + 4 * tp::SIDE), 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  };
+  f32x4_t acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  auto products = [&](const s16x8_t* fa, const s16x8_t* fb) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j], 0, 0, 0);
+  };
+
+  const int nk = (T + 31) / 32;
+  fetch();
+  stage();
+  fetch();
+  __syncthreads();
+  for (int k = 0; k < nk; ++k) {
+    s16x8_t a1[4], a2[4], a3[4], b1[4], b2[4], b3[4];
+    frags(a_rd, 0, a1);
+    frags(b_rd, 2, b3);
+    frags(b_rd, 1, b2);
+    products(a1, b3);   // the small terms first
+    frags(b_rd, 0, b1);
+    frags(a_rd, 2, a3);
+    frags(a_rd, 1, a2);
+    products(a3, b1);
+    products(a2, b2);
+    products(a1, b2);
+    products(a2, b1);
+    products(a1, b1);
+    __syncthreads();    // every wave has read its fragments
+    if (k + 1 < nk) {
+      stage();
+      fetch();
+      __syncthreads();
+    }
+  }
+
+  // acc[i][j][r] = element (64 wave_m + 16 i + lane % 16, 64 wave_n + 16 j + 4 (lane / 16) + r) of the tile
+  auto square_sum = [&]() {
+    float ss[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // short chains: a norm's rounding is its whole sample's
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss[j] = fmaf(acc[i][j][e], acc[i][j][e], ss[j]);
+    return (ss[0] + ss[1]) + (ss[2] + ss[3]);
+  };
+  float ss = square_sum();
+  const bool beyond = !(ss <= 3.0e38f) || least < (18u << 24) - 1u;   // 2^-109: exponent field 18
+  if (__syncthreads_or(beyond)) {
+    const int m = m0 + 64 * wave_m + (lane & 15), n = n0 + 64 * wave_n + 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+    for (int t = 0; t < T; ++t) {
+      float y[4];
+      f32x4_t x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = m + 16 * i < D ? ((const float*)pa)[(size_t)t * D + m + 16 * i] : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = n + 16 * j < P ? *(const f32x4_t*)((const float*)pb + (size_t)t * P + n + 16 * j) : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(y[i], x[j][e], acc[i][j][e]);
+    }
+    ss = square_sum();
+  }
+  float* const red = (float*)lds + 64 * F32x3Cfg::OUT_PITCH;
+  const float w = wave_sum_to_lane63(ss);
+  if (lane == 63) red[wave] = w;
+  float* const st = (float*)lds;
+  float* const out = (float*)a.scratch + (size_t)sample * D * P;
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {   // 64 rows at a time through LDS, so that whole rows are written
+    if (wave_m == h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          *(f32x4_t*)(st + (16 * i + (lane & 15)) * F32x3Cfg::OUT_PITCH + 64 * wave_n + 16 * j + 4 * (lane >> 4)) = acc[i][j];
+    }
+    __syncthreads();
+    if (h == 0 && tid == 0) a.partials[(size_t)sample * tiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int r = (tid >> 5) + 8 * it, row = m0 + 64 * h + r, col = n0 + 4 * (tid & 31);
+      if (row < D && col < P) *(f32x4_t*)(out + (size_t)row * P + col) = *(const f32x4_t*)(st + r * F32x3Cfg::OUT_PITCH + 4 * (tid & 31));
+    }
+    __syncthreads();
+  }
+}
+
+}  // namespace flashdp

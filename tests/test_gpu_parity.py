@@ -950,6 +950,48 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
         F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
 
 
+@pytest.mark.parametrize("B,T,P,D", [(3, 4, 128, 132), (2, 33, 136, 1028), (4, 64, 36, 60), (2, 1030, 300, 260), (9, 31, 516, 128)])
+@pytest.mark.parametrize("values", ["plain", "tiny", "mixed", "overflow", "infinite", "subnormal"])
+def test_fp32_split_into_bfloat16_parts(B, T, P, D, values):
+    # against fp64, and where values leave what the split covers (operands below 2^-109, sums or squares that overflow,
+    # infinities), against the generic kernel: there both are plain fp32 sums.  Tolerances of fp32 sums of T terms.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T * P)
+    X = torch.randn((B, T, P), generator=g, device=DEV)
+    dY = torch.randn((B, T, D), generator=g, device=DEV) * 10 ** (2 * torch.rand((B, 1, 1), generator=g, device=DEV) - 1)
+    if values == "tiny":
+        X, dY = X * 1e-36, dY * 1e30
+    elif values == "mixed":
+        X[:, ::3, ::5] *= 1e-35
+        dY[:, 1::4] *= 1e-20
+    elif values == "overflow":
+        X, dY = X * 1e18, dY * 1e4
+    elif values == "infinite":
+        X[1, T // 2, 7] = float("inf")
+    elif values == "subnormal":
+        X = X * 1e-42
+    L = dict(X=X, dY=dY, d_in=P, d_out=D, C=1e-3 if values != "tiny" else 1e-9, sigma=0.0, seed=1, layer=0)
+    res = []
+    for tile in (None, -1):
+        out, norms = torch.full((D, P), 7.0, device=DEV), torch.full((B,), 7.0, device=DEV)
+        with env(FLASHDP_TILE=tile):
+            F.flashdp_block_dp_grad([dict(L, out_grad=out, out_norms=norms)], B, T, F.F32, "scratch")
+        torch.cuda.synchronize()
+        assert F.flashdp_last_kernel() == ("gemm_simple_kernel" if tile else "gemm_f32x3_kernel")
+        res.append((out, norms))
+    (o, n), (ro, rn) = res
+    assert torch.equal(torch.isfinite(o), torch.isfinite(ro)) and torch.equal(torch.isinf(n), torch.isinf(rn)) and torch.equal(torch.isnan(n), torch.isnan(rn))
+    ok = torch.isfinite(ro)
+    assert float((o[ok] - ro[ok]).double().norm()) <= 2e-6 * float(ro[ok].double().norm())
+    fin = torch.isfinite(rn)
+    assert torch.allclose(n[fin], rn[fin], rtol=1e-6, atol=0)
+    if values in ("plain", "tiny", "mixed"):
+        G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+        nn = G.flatten(1).norm(dim=1)
+        want = (G * torch.clamp(L["C"] / nn, max=1.0)[:, None, None]).sum(0)
+        assert float((o - want).norm() / want.norm()) <= 1e-6 and float(((n - nn) / nn).abs().max()) <= 1e-6
+
+
 @pytest.mark.parametrize("schedule", ["scratch", "twopass", "explicit", "ghost"])
 def test_nan_in_one_sample_poisons_the_output_instead_of_passing_unclipped(schedule):
     base = W.WORKLOADS["gpt2_small_mlp_up"]
