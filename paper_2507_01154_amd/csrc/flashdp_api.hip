@@ -28,6 +28,7 @@
 #include "gram_norm.hip.h"
 #include "mfma_probe.hip.h"
 #include "rows_dp.hip.h"
+#include "tiny_dp.hip.h"
 
 using namespace flashdp;
 
@@ -886,6 +887,13 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
   return hipGetLastError();
 }
 
+// One launch for fp32 layers of a few thousand elements in all (tiny_dp.hip.h): a wave per sample in one workgroup, all
+// gradients in its LDS.
+bool tiny_ok(int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
+  return dtype == FLASHDP_F32 && g_ctx.stages == FLASHDP_STAGE_ALL && env().tile == 0 && P <= TINY_SIDE && D <= TINY_SIDE &&
+         T <= TINY_TOKENS && B <= TINY_SAMPLES && B * P * D * 4 <= TINY_LDS_BYTES;
+}
+
 // Enqueues Algorithm 1 for one layer.
 // `parts` restricts what is enqueued (a subset of the stage mask); persistent_grid > 0 selects the bounded
 // aggregation grid of the overlapped schedule.
@@ -947,6 +955,19 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
   const float noise_scale = add_noise ? L.sigma * L.C : 0.0f;
   g_ctx.last_kernel = path_kernel_name(plan.path);
 
+  if (use_scratch && parts == FLASHDP_STAGE_ALL && tiny_ok(B, T, P, D, dtype)) {
+    TinyArgs t;
+    t.X = static_cast<const float*>(L.X); t.dY = static_cast<const float*>(L.dY);
+    t.B = (int)B; t.T = (int)T; t.P = (int)P; t.D = (int)D;
+    t.out_norms = L.out_norms; t.out = L.out_grad; t.C = L.C; t.noise_scale = noise_scale; t.seed = L.seed; t.layer = L.layer;
+    t.accumulate = accumulate ? 1 : 0;
+    auto kern = D <= 32 ? (P <= 32 ? tiny_dp_kernel<1, 1> : tiny_dp_kernel<1, 2>) : (P <= 32 ? tiny_dp_kernel<2, 1> : tiny_dp_kernel<2, 2>);
+    HIP_TRY(ensure_lds_limit(reinterpret_cast<const void*>(kern), TINY_LDS_BYTES));
+    hipLaunchKernelGGL(kern, dim3(1), dim3((unsigned)(64 * std::max<int64_t>(B, (int64_t)(S + 255) / 256))), (size_t)B * S * 4, st, t);
+    HIP_TRY(hipGetLastError());
+    g_ctx.last_kernel = "tiny_dp_kernel";
+    return FLASHDP_OK;
+  }
   if (mode == FLASHDP_SCHEDULE_EXPLICIT) {
     // The explicit four-stage flow of Appendix B.2, every stage a kernel of its own with the fp32
     // per-sample gradients going through HBM in between: the comparison the fused schedules are measured against.

@@ -14,8 +14,7 @@
 // additions to one accumulator); level at T = 2, which stays with the fp32 instructions.
 //
 // What the split does not cover is left to a plain fp32 loop over the tile, decided per workgroup: sums that are not finite
-// (an infinity times a part that is zero or of the other sign is NaN; as in the other kernels it also meets the zeros
-// beyond a ragged edge, which makes the sample's norm NaN) or whose squares overflow, and operands below 2^-109,
+// (an infinity times a part that is zero or of the other sign is NaN) or whose squares overflow, and operands below 2^-109,
 // whose last part would be subnormal.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -186,6 +185,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    // an operand that is not finite meets the zeros beyond a ragged edge of the 256 x 256 tiles that the fp32 matrix instructions
+    // work on, which makes the norm NaN: likewise
+    const bool edge_d = D % 256 != 0 && tm == a.tiles_m - 1, edge_p = P % 256 != 0 && tn == a.tiles_n - 1;
+    float ragged = 0.0f;
 #pragma unroll 1
     for (int t = 0; t < T; ++t) {
       float y[4];
@@ -195,13 +198,16 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
 #pragma unroll
       for (int j = 0; j < 4; ++j) x[j] = n + 16 * j < P ? *(const f32x4_t*)((const float*)pb + (size_t)t * P + n + 16 * j) : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) {
+        ragged = fmaf(0.0f, edge_p ? y[i] : 0.0f, ragged);
+        ragged = fmaf(0.0f, edge_d ? (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]) : 0.0f, ragged);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(y[i], x[j][e], acc[i][j][e]);
+      }
     }
-    ss = square_sum();
+    ss = square_sum() + ragged;
   }
   float* const red = (float*)lds + 64 * F32x3Cfg::OUT_PITCH;
   const float w = wave_sum_to_lane63(ss);

@@ -950,11 +950,44 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
         F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
 
 
-@pytest.mark.parametrize("B,T,P,D", [(3, 4, 128, 132), (2, 33, 136, 1028), (4, 64, 36, 60), (2, 1030, 300, 260), (9, 31, 516, 128)])
+@pytest.mark.parametrize("B,T,P,D", [(1, 1, 1, 1), (4, 16, 32, 32), (16, 17, 32, 32), (4, 64, 64, 64), (3, 5, 33, 31), (16, 64, 30, 34), (2, 33, 7, 64), (1, 63, 64, 3)])
+def test_tiny_fp32_layers_in_one_launch(B, T, P, D):
+    # edges of the 32 x 32 blocks, one sample and the most, one element; added to an earlier micro-batch, with noise; a sample
+    # that is not finite.  Tolerances of fp32 sums of T and B terms.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B * T + P)
+    X = torch.randn((B, T, P), generator=g, device=DEV)
+    dY = torch.randn((B, T, D), generator=g, device=DEV) * 10 ** (2 * torch.rand((B, 1, 1), generator=g, device=DEV) - 1)
+    G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+    n = G.flatten(1).norm(dim=1)
+    want = (G / torch.clamp(n, min=1.0)[:, None, None]).sum(0)
+    out, norms = torch.full((D, P), float("nan"), device=DEV), torch.full((B,), float("nan"), device=DEV)
+    L = dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.5, seed=3, layer=2, out_grad=out, out_norms=norms)
+    z = torch.empty((D * P,), device=DEV)
+    F.flashdp_noise_field(3, 2, D * P, z)
+    F.flashdp_block_dp_grad_micro([L], B, T, F.F32, "scratch", accumulate=False, add_noise=False)
+    assert F.flashdp_last_kernel() == "tiny_dp_kernel"
+    assert float((out - want).abs().max()) <= 2e-6 * float(want.abs().max()) and torch.allclose(norms.double(), n, rtol=1e-6, atol=0)
+    F.flashdp_block_dp_grad_micro([L], B, T, F.F32, "scratch", accumulate=True, add_noise=True)
+    assert float((out - 2 * want - 0.5 * z.view(D, P)).abs().max()) <= 4e-6 * (float(want.abs().max()) + 1.0)
+    F.flashdp_linear_dp_grad_static(X, dY, B, T, P, D, F.F32, 1.0, 0.0, 3, 2, out, norms)
+    assert F.flashdp_last_kernel() == "tiny_dp_kernel" and float((out - want).abs().max()) <= 2e-6 * float(want.abs().max())
+    X[B - 1, T - 1, P - 1] = float("inf")
+    res = []
+    for tile in (None, -1):
+        with env(FLASHDP_TILE=tile):
+            F.flashdp_block_dp_grad([dict(L, sigma=0.0)], B, T, F.F32, "scratch")
+        torch.cuda.synchronize()
+        res.append((torch.isfinite(out).clone(), torch.isnan(norms).clone()))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+@pytest.mark.parametrize("B,T,P,D", [(3, 4, 128, 132), (2, 33, 136, 1028), (4, 64, 36, 68), (2, 1030, 300, 260), (9, 31, 516, 128)])
 @pytest.mark.parametrize("values", ["plain", "tiny", "mixed", "overflow", "infinite", "subnormal"])
 def test_fp32_split_into_bfloat16_parts(B, T, P, D, values):
     # against fp64, and where values leave what the split covers (operands below 2^-109, sums or squares that overflow,
-    # infinities), against the generic kernel: there both are plain fp32 sums.  Tolerances of fp32 sums of T terms.
+    # infinities), against the generic kernel resp. the two-pass schedule's: there both are plain fp32 sums.  Tolerances of
+    # fp32 sums of T terms.
     g = torch.Generator(device=DEV)
     g.manual_seed(T * P)
     X = torch.randn((B, T, P), generator=g, device=DEV)
@@ -974,10 +1007,11 @@ def test_fp32_split_into_bfloat16_parts(B, T, P, D, values):
     res = []
     for tile in (None, -1):
         out, norms = torch.full((D, P), 7.0, device=DEV), torch.full((B,), 7.0, device=DEV)
-        with env(FLASHDP_TILE=tile):
-            F.flashdp_block_dp_grad([dict(L, out_grad=out, out_norms=norms)], B, T, F.F32, "scratch")
+        two = values == "infinite" and tile is not None   # (the tiles that a ragged edge is counted in)
+        with env(FLASHDP_TILE=None if two else tile):
+            F.flashdp_block_dp_grad([dict(L, out_grad=out, out_norms=norms)], B, T, F.F32, "twopass" if two else "scratch")
         torch.cuda.synchronize()
-        assert F.flashdp_last_kernel() == ("gemm_simple_kernel" if tile else "gemm_f32x3_kernel")
+        assert two or F.flashdp_last_kernel() == ("gemm_simple_kernel" if tile else "gemm_f32x3_kernel")
         res.append((out, norms))
     (o, n), (ro, rn) = res
     assert torch.equal(torch.isfinite(o), torch.isfinite(ro)) and torch.equal(torch.isinf(n), torch.isinf(rn)) and torch.equal(torch.isnan(n), torch.isnan(rn))
