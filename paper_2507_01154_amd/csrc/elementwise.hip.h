@@ -346,13 +346,17 @@ __global__ __launch_bounds__(256) void explicit_clip_kernel(float* __restrict__ 
 // for such samples only where the caches (256 MB) could not hold them (fp32, one call, through the caches and past them:
 // 257 x 130, B = 256, 168 and 205 us; 1999 x 2001, B = 16, 127 and 137, B = 64, 655 and 583).
 inline bool aggregate32_streams(int64_t B, size_t S) { return S % 4 == 0 || (size_t)B * S >= ((size_t)1 << 26); }
-template <bool STREAM>
-__global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restrict__ G, const float* __restrict__ factors, int B,
-                                                          size_t S, float noise_scale, uint64_t seed, uint32_t layer,
-                                                          float* __restrict__ out, int accumulate) {
-  const size_t g4 = (size_t)blockIdx.x * 256 + threadIdx.x;
+
+// DEEP: four samples' loads are in flight per thread and the noise is generated while they are on their way, as in
+// aggregate16_one; the sums keep the sample order.  For layers whose threads do not keep the memory busy with one load each
+// (512 x 512, B = 64: 34.7 us with the clip factors, 22.8; 257 x 130, B = 256: 136, 97); those of many more workgroups than
+// the chip holds are better off with the registers (4208 x 9808, B = 20: 584, 598).
+inline bool aggregate32_deep(size_t grid) { return grid <= 8192; }
+template <bool STREAM, bool DEEP>
+__device__ __forceinline__ void aggregate32_one(const float* __restrict__ G, const float* __restrict__ factors, int B, size_t S,
+                                                size_t g4, float noise_scale, uint64_t seed, uint32_t layer,
+                                                float* __restrict__ out, int accumulate) {
   const size_t e = g4 * 4;
-  if (e >= S) return;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   const bool vec = e + 3 < S;
   if (accumulate) {
@@ -360,22 +364,51 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
     for (int q = 0; q < 4; ++q)
       if (e + q < S) acc[q] = out[e + q];
   }
-  for (int i = 0; i < B; ++i) {
+  auto load = [&](int i) -> f32x4_any_t {
     const float* g = G + (size_t)i * S + e;
-    const float c = factors ? factors[i] : 1.0f;
     if (vec) {
-      f32x4_any_t v;
-      if constexpr (STREAM) v = __builtin_nontemporal_load((const f32x4_any_t*)g);
-      else v = *(const f32x4_any_t*)g;
-      acc[0] = fmaf(c, v.x, acc[0]); acc[1] = fmaf(c, v.y, acc[1]); acc[2] = fmaf(c, v.z, acc[2]); acc[3] = fmaf(c, v.w, acc[3]);
-    } else {
+      if constexpr (STREAM) return __builtin_nontemporal_load((const f32x4_any_t*)g);
+      else return *(const f32x4_any_t*)g;
+    }
+    f32x4_any_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (e + q < S) v[q] = g[q];
+    return v;
+  };
+  Normals4 z = {};
+  if constexpr (DEEP) {
+    f32x4_any_t raw[4] = {};
+    const int first = B < 4 ? B : 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q < first) raw[q] = load(q);
+    if (noise_scale != 0.0f) z = noise_group(seed, layer, g4);
+    for (int i = 0; i < B; i += 4) {
+      f32x4_any_t cur[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) cur[q] = raw[q];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (e + q < S) acc[q] = fmaf(c, g[q], acc[q]);
+        if (i + 4 + q < B) raw[q] = load(i + 4 + q);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + q < B) {
+          const float c = factors ? factors[i + q] : 1.0f;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[r] = fmaf(c, cur[q][r], acc[r]);
+        }
     }
+  } else {
+    for (int i = 0; i < B; ++i) {
+      const f32x4_any_t v = load(i);
+      const float c = factors ? factors[i] : 1.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = fmaf(c, v[r], acc[r]);
+    }
+    if (noise_scale != 0.0f) z = noise_group(seed, layer, g4);
   }
   if (noise_scale != 0.0f) {
-    const Normals4 z = noise_group(seed, layer, g4);
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[q] = fmaf(noise_scale, z.z[q], acc[q]);
   }
@@ -386,6 +419,27 @@ __global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restric
     for (int q = 0; q < 4; ++q)
       if (e + q < S) out[e + q] = acc[q];
   }
+}
+
+template <bool STREAM, bool DEEP>
+__global__ __launch_bounds__(256) void aggregate32_kernel(const float* __restrict__ G, const float* __restrict__ factors, int B,
+                                                          size_t S, float noise_scale, uint64_t seed, uint32_t layer,
+                                                          float* __restrict__ out, int accumulate) {
+  const size_t g4 = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (g4 * 4 < S) aggregate32_one<STREAM, DEEP>(G, factors, B, S, g4, noise_scale, seed, layer, out, accumulate);
+}
+
+// With the inter-block reduce and the clip factors in front, every workgroup for itself (see clip_aggregate16_kernel): a launch
+// less, 2 us of a small layer's call.
+template <bool STREAM>
+__global__ __launch_bounds__(256) void clip_aggregate32_kernel(const float* __restrict__ G, const float* __restrict__ partials, int tiles,
+                                                               float C, float* __restrict__ out_norms, int B, size_t S,
+                                                               float noise_scale, uint64_t seed, uint32_t layer,
+                                                               float* __restrict__ out, int accumulate) {
+  __shared__ float fac[MAX_FUSED_CLIP_B];
+  clip_factors_to_lds(partials, tiles, C, B, fac, out_norms, blockIdx.x == 0);
+  const size_t g4 = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (g4 * 4 < S) aggregate32_one<STREAM, true>(G, fac, B, S, g4, noise_scale, seed, layer, out, accumulate);
 }
 
 // out[e] = (ADD ? out[e] : 0) + scale * z[e]: the noise step alone (second pass of the two-pass schedule,

@@ -444,6 +444,12 @@ hipError_t launch_gemm(const Plan& p, int dtype, const GemmArgs& a, hipStream_t 
   }
 }
 
+auto aggregate32_of(int64_t B, size_t S) {
+  const bool deep = aggregate32_deep(((S + 3) / 4 + 255) / 256);
+  return aggregate32_streams(B, S) ? (deep ? aggregate32_kernel<true, true> : aggregate32_kernel<true, false>)
+                                   : (deep ? aggregate32_kernel<false, true> : aggregate32_kernel<false, false>);
+}
+
 hipError_t launch_aggregate(int dtype, const void* scratch, const float* factors, int B, size_t S, float noise_scale,
                             uint64_t seed, uint32_t layer, float* out, int accumulate, hipStream_t st, int persistent_grid = 0) {
   if (persistent_grid > 0 && dtype != FLASHDP_F32 && S % 8 == 0) {
@@ -461,7 +467,7 @@ hipError_t launch_aggregate(int dtype, const void* scratch, const float* factors
   } else {
     const size_t groups = (S + 3) / 4;
     const unsigned grid = (unsigned)((groups + 255) / 256);
-    auto kern = aggregate32_streams(B, S) ? aggregate32_kernel<true> : aggregate32_kernel<false>;
+    auto kern = aggregate32_of(B, S);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const float*)scratch, factors, B, S, noise_scale, seed, layer, out, accumulate);
   }
   return hipGetLastError();
@@ -626,8 +632,8 @@ hipError_t run_rows(const flashdp_layer_t& L, int64_t B, int dtype, char* ws, hi
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) { (void)hipGetLastError(); return FLASHDP_HIP_ERROR; } } while (0)
 
 // Whether the streaming kernel of the scratch schedule works out the clip factors itself (see run_layer).
-bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
-  return dtype != FLASHDP_F32 && B <= MAX_FUSED_CLIP_B && agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20);
+bool fold_clip_ok(int64_t B, int tiles, size_t agg_grid) {
+  return B <= MAX_FUSED_CLIP_B && agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20);
 }
 
 // The parking pass on 128 x 128 tiles (gemm_tile128.hip.h) of one layer or several: one workgroup per tile and sample.
@@ -673,7 +679,7 @@ GroupSlot group_slot(const Park& k, int64_t B, int64_t P, int64_t D, size_t begi
 bool group_ok(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || g_ctx.stages != FLASHDP_STAGE_ALL) return false;
   const Park k = park_of(L, B, T, dtype);
-  return k.small && fold_clip_ok(dtype, B, k.tiles_m * k.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
+  return k.small && fold_clip_ok(B, k.tiles_m * k.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
 }
 // Neither layer writes what the other reads or writes (a caller may pass one buffer twice: such layers keep their order).
 bool group_disjoint(const flashdp_layer_t& x, const flashdp_layer_t& y, int64_t B, int64_t T) {
@@ -983,7 +989,7 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
       HIP_TRY(hipGetLastError());
     }
     if (stages & FLASHDP_STAGE_AGGREGATE) {
-      auto kern = aggregate32_streams(B, S) ? aggregate32_kernel<true> : aggregate32_kernel<false>;
+      auto kern = aggregate32_of(B, S);
       hipLaunchKernelGGL(kern, dim3((unsigned)(((S + 3) / 4 + 255) / 256)), dim3(256), 0, st, G, (const float*)nullptr, (int)B, S,
                          noise_scale, L.seed, L.layer, L.out_grad, accumulate ? 1 : 0);                                                             // stage 4
       HIP_TRY(hipGetLastError());
@@ -1000,17 +1006,22 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
     } else if (stages & FLASHDP_STAGE_CONTRACT) {
       HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
     }
-    // 16-bit scratch: the inter-block reduce and the clip factors are done by the streaming
+    // The inter-block reduce and the clip factors are done by the streaming
     // kernel itself (one launch less per layer) when that is cheap: every workgroup reads all B * tiles partials, so
     // with the ordinary grid (one workgroup per 2048 elements) this is only done while those redundant reads stay
     // below 64 MB (a 4096 x 4096 layer: 32 MB; the Llama-13B layers would re-read 0.16-1.2 GB, and a grid bounded
     // to avoid that streams measurably slower: 191 vs 153 + 7 us per layer); the bounded grid of the overlapped
     // schedule always qualifies.
-    const size_t n8_all = (S + 7) / 8, full_grid = (n8_all + 255) / 256;
+    const size_t n8_all = (S + 7) / 8, full_grid = dtype == FLASHDP_F32 ? ((S + 3) / 4 + 255) / 256 : (n8_all + 255) / 256;
     const size_t agg_grid = persistent_grid > 0 ? std::min((size_t)persistent_grid, full_grid) : full_grid;
-    const bool fold_clip = S >= 8 && fold_clip_ok(dtype, B, tiles, agg_grid) &&
+    const bool fold_clip = (dtype == FLASHDP_F32 || S >= 8) && fold_clip_ok(B, tiles, agg_grid) &&
                            (stages & (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE)) == (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE);
-    if (fold_clip) {
+    if (fold_clip && dtype == FLASHDP_F32) {
+      auto kern = aggregate32_streams(B, S) ? clip_aggregate32_kernel<true> : clip_aggregate32_kernel<false>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)agg_grid), dim3(256), 0, st, static_cast<const float*>(a.scratch), a.partials, tiles, L.C, L.out_norms,
+                         (int)B, S, noise_scale, L.seed, L.layer, L.out_grad, accumulate ? 1 : 0);
+      HIP_TRY(hipGetLastError());
+    } else if (fold_clip) {
       auto kern = persistent_grid > 0 ? clip_aggregate16_kernel<DT_BF16, false>   // (S is a multiple of 8 there)
                   : S % 8 == 0 ? clip_aggregate16_kernel<DT_BF16, true> : clip_aggregate16_any_kernel<DT_BF16>;
       hipLaunchKernelGGL(kern, dim3((unsigned)agg_grid), dim3(256), 0, st, a.scratch, a.partials, tiles,
