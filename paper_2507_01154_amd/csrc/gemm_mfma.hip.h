@@ -150,7 +150,9 @@ __device__ __forceinline__ uint32_t pack2_16bit(float lo, float hi) {
 // more).  A chunk that reaches past the end of its row is fetched from the last 8 columns of the row instead - always
 // inside the tensor - and moved down by the difference (shift_down), which brings in zeros for the columns that do not
 // exist; rows past the end of a sample are fetched from its last row and replaced by zeros.  A copy into aligned rows
-// first would cost a pass over both operands and a workspace; direct loads to LDS need 4-byte alignment.
+// first would cost a pass over both operands and a workspace; direct loads to LDS need 4-byte alignment.  (At addresses 2 mod 4 a
+// 16-byte load runs at a third of the rate, from the L2 9.4 TB/s against 27.7; loading from two bytes earlier and putting
+// the chunk together in registers is slower all the same: 768 x 50257, B = 2, T = 1024: 264 us a call, 292.)
 // 768 x 50257, B = 2, T = 1024: 2650 us per call on the vector ALUs, 245 us here (0.65 PFLOP/s with the aggregation).
 typedef u32x4_t __attribute__((aligned(2))) u32x4_any_t;
 typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
