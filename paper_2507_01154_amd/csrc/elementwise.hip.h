@@ -16,6 +16,9 @@ namespace flashdp {
 // paper's inter-block reduce; the kernel boundary before it is the block-wise synchronisation.
 __device__ __forceinline__ double sample_norm_sq(const float* __restrict__ partials_i, int n, int lane) {
   double s = 0.0;
+  // (four loads on their way at a time: 4096 x 4096, T = 128, 1024 tiles: B = 1 49.8 us a call
+  // one by one, 43.7 so; B = 2: 61.0, 57.4)
+#pragma unroll 4
   for (int k = lane; k < n; k += 64) s += (double)partials_i[k];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
