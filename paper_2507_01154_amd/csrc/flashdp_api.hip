@@ -575,7 +575,8 @@ FusedWs fused_ws(int64_t B, int64_t P, int64_t D) {
   return w;
 }
 
-// small = false: the least the schedule runs in; true: what it is fastest in.
+// small = false: the least the schedule runs in; true: what it is fastest in, which is never less (small tiles may need
+// fewer norm partials than the plan's own, fp32 layers planned on 64 x 64 tiles for instance, but a call asks for those).
 size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype, int mode, bool small = false) {
   if (mode == FLASHDP_SCHEDULE_FUSED) {
     // a layer the single-launch form does not apply to takes the scratch schedule; without a device, assume 256 CUs
@@ -584,7 +585,8 @@ size_t layer_ws_bytes(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype,
     mode = FLASHDP_SCHEDULE_SCRATCH;
   }
   const Plan p = make_plan(B, T, L.d_in, L.d_out, dtype);
-  return ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode, small).total;
+  const size_t least = ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode).total;
+  return small ? std::max(least, ws_layout(p, B, T, L.d_in, L.d_out, dtype, mode, true).total) : least;
 }
 
 // Rows without a sequence (rows_dp.hip.h) are taken by every call that leaves the schedule to the library: nothing of

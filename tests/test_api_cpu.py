@@ -92,6 +92,31 @@ def test_workspace_bytes_formula():
     assert L.flashdp_set_schedule(0) == F.OK
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "fp32"])
+def test_workspace_sizes_suffice_for_the_tiles_a_call_asks_room_for(dtype):
+    # a call is refused, or goes through the batch in chunks, below the clip factors, the norm partials of the plan's own
+    # tiles (both together are the two-pass workspace) and the parked samples; the sizing calls may give more, never less.
+    # fp32 layers of fewer than 128 x 128 elements are planned on 64 x 64 tiles and park on 128 x 128 ones from T = 32 on.
+    import random
+    rng = random.Random(5)
+    up = lambda n: (n + 255) // 256 * 256
+    code, e = {"bf16": (F.BF16, 2), "f16": (F.F16, 2), "fp32": (F.F32, 4)}[dtype]
+    shapes = [(8, 64, 768, 16), (64, 1024, 120, 120), (4, 1024, 8, 2044), (16, 512, 96, 160), (8, 1024, 768, 3072), (5, 333, 1096, 2312)]
+    for _ in range(400):
+        a = rng.choice([1, 4, 8, 64])
+        shapes.append((rng.randint(1, 300), rng.choice([rng.randint(1, 64), rng.randint(32, 2048)]),
+                       *(max(a, int(2 ** rng.uniform(2, 12)) // a * a) for _ in range(2))))
+    for B, T, P, D in shapes:
+        L = [dict(X=None, dY=None, d_in=P, d_out=D, C=1.0, sigma=1.0, seed=0, layer=0, out_grad=None)]
+        least = lambda b: F.flashdp_workspace_bytes(L, b, T, code, "twopass") + up(e * b * P * D)
+        for schedule in ("scratch", "auto"):
+            assert F.flashdp_workspace_bytes(L, B, T, code, schedule) >= least(B), (B, T, P, D)
+        assert F.flashdp_workspace_bytes(L, B, T, code, "overlap") >= 2 * least(B), (B, T, P, D)
+        k = rng.randint(1, B)
+        for slots in (1, 2):
+            assert F.flashdp_workspace_bytes_chunked(L, B, T, code, k, slots) >= slots * least(k), (B, T, P, D, k)
+
+
 def test_tile_shape_follows_the_rounds_of_equally_long_work_items(monkeypatch):
     # host logic only, read off the number of norm partials (B x tiles floats, rounded up to 256 bytes) in the two-pass
     # workspace.  Without a device 256 compute units are assumed.

@@ -950,6 +950,28 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
         F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
 
 
+@pytest.mark.parametrize("B,T,P,D", [(8, 64, 768, 16), (64, 100, 120, 120), (4, 100, 8, 2044), (16, 70, 96, 160)])
+def test_thin_fp32_layers_run_in_the_workspace_they_are_told_to_allocate(B, T, P, D):
+    # the whole batch in the size that flashdp_workspace_bytes gives, k samples at a time in the chunked one; against fp64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P)
+    X = torch.randn((B, T, P), generator=g, device=DEV)
+    dY = torch.randn((B, T, D), generator=g, device=DEV)
+    G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+    n = G.flatten(1).norm(dim=1)
+    want = (G / torch.clamp(n, min=1.0)[:, None, None]).sum(0)
+    out, norms = torch.empty((D, P), device=DEV), torch.empty((B,), device=DEV)
+    L = [dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)]
+    full = F.flashdp_workspace_bytes(L, B, T, F.F32, "scratch")
+    k = B // 2 + 1
+    for schedule, size, chunk in (("scratch", full, B), ("auto", full, B), ("auto", F.flashdp_workspace_bytes_chunked(L, B, T, F.F32, k, 1), k)):
+        out.fill_(float("nan"))
+        norms.fill_(float("nan"))
+        F.flashdp_block_dp_grad(L, B, T, F.F32, schedule, torch.empty((size,), dtype=torch.uint8, device=DEV))
+        assert F.flashdp_last_schedule() == "scratch" and F.flashdp_last_chunk() == chunk
+        assert float((out - want).norm() / want.norm()) <= 1e-6 and float(((norms - n).abs() / n).max()) <= 1e-6
+
+
 @pytest.mark.parametrize("B,T,P,D", [(1, 1, 1, 1), (4, 16, 32, 32), (16, 17, 32, 32), (4, 64, 64, 64), (3, 5, 33, 31), (16, 64, 30, 34), (2, 33, 7, 64), (1, 63, 64, 3)])
 def test_tiny_fp32_layers_in_one_launch(B, T, P, D):
     # edges of the 32 x 32 blocks, one sample and the most, one element; added to an earlier micro-batch, with noise; a sample
