@@ -308,8 +308,9 @@ Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dt
   if (p.any || env().tile != 0) return k;
   if (dtype == FLASHDP_F32) {
     // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for layers of one small
-    // tile and few tokens, which are all launch and latency (36 x 40, B = 4, T = 16: 8.0 us, 8.6), and T < 4 (see there).
-    k.small = P % 4 == 0 && D % 4 == 0 && (T + 96) * std::max(P, D) * 4 < (int64_t(1) << 31) && T >= (p.path == PATH_F32 ? 4 : 32);
+    // tile and few tokens, which are all launch and latency (36 x 40, B = 4, T = 16: 8.0 us, 8.6), and T < 16, where its
+    // error can be the larger one (see there).
+    k.small = P % 4 == 0 && D % 4 == 0 && (T + 96) * std::max(P, D) * 4 < (int64_t(1) << 31) && T >= (p.path == PATH_F32 ? 16 : 32);
     return k;
   }
   if (p.path == PATH_128x4) k.small = k.by_far = true;

@@ -1,17 +1,24 @@
 // The parking pass for fp32 inputs on the bfloat16 matrix cores: every operand element is split into three bfloat16 parts that
-// add up to it exactly, x = x1 + x2 + x3 (8 + 8 + 8 significant bits, each part the rounding of what the ones before leave),
-// and a product is formed of the six pairs that matter, x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1.  The three pairs left
-// out are below 2^-25 of the product, less than the rounding of one fp32 addition.
+// add up to it exactly, x = x1 + x2 + x3 (8 + 8 + 8 significant bits, each part the rounding of what the ones before leave;
+// the technique of Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", 2019), and a product is formed of all pairs of parts but x3 y3, which is below 2^-33 of it.
 //
-// Why.  Bound by the fp32 matrix rate (157 TFLOP/s) before; six bfloat16 products on a sixteen times faster unit.  A wave
-// issues six times 16 matrix instructions a k-tile, so the splitting (about 9 vector instructions an element) runs beside the other
+// Why.  Bound by the fp32 matrix rate (157 TFLOP/s) before; eight bfloat16 products on a sixteen times faster unit.  A wave
+// issues eight times 16 matrix instructions a k-tile, so the splitting (about 9 vector instructions an element) runs beside the other
 // workgroup's products.  128 x 128 tiles, 4 waves of 64 x 64, one 48 KB LDS stage (3 parts x 2 operands x 32 rows of 128),
 // the next k-tile in registers meanwhile, two workgroups per CU.
 //
-// fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 1954, 1314 (210 TFLOP/s); 768 x 3072,
-// B = 4, T = 1024: 257, 143; 64 x 448, B = 14, T = 1024: 235, 60; 128 x 13184, B = 1, T = 276: 79, 21; 1028 x 764, B = 8, T = 333: 96, 35.
-// Relative error of a gradient against fp64: T = 2048: 8.1e-7, 7.2e-7; T = 333: 3.3e-7, 2.8e-7; T = 16: 7.4e-8, 3.4e-8 (fewer
-// additions to one accumulator); level at T = 2, which stays with the fp32 instructions.
+// The products x1 y1 have an accumulator of their own, the seven smaller ones share another, and the two are added at the
+// end.  So the large accumulator is rounded once in 32 tokens (matrix instructions do not round an addition as carefully as
+// an fp32 one), the other's roundings are 2^-8 of that, and a product that stands alone is rounded once.  Relative error of a
+// gradient against fp64 (2-norm), on the fp32 matrix instructions, with six products in one accumulator, and so: normal data, T = 2048:
+// 8.1e-7, 7.0e-7, 2.7e-7; T = 333: 3.3e-7, 2.7e-7, 1.0e-7; T = 16: 7.4e-8, 3.4e-8, 3.2e-8; one token alone: 2.54e-8, 3.4e-8, 2.54e-8
+// (largest element 5.96e-8, 1.5e-7, 5.97e-8); one token a thousand times the others, T = 2048: 8.1e-7, 5.1e-7, 2.9e-7; T = 16: 7.2e-8,
+// 5.0e-8, 5.6e-8; T = 8: 5.1e-8, 5.1e-8, 5.4e-8; T = 4: 3.6e-8, 4.2e-8, 4.5e-8: below 16 tokens the fp32 instructions keep the layer.
+//
+// fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 2158, 1702 (162 TFLOP/s; six products 1402);
+// 768 x 3072, B = 4, T = 1024: 251, 161; 64 x 448, B = 14, T = 1024: 236, 64; 128 x 13184, B = 1, T = 276: 76, 24; 1028 x 764, B = 8, T = 333:
+// 95, 44.
 //
 // What the split does not cover is left to a plain fp32 loop over the tile, decided per workgroup: sums that are not finite
 // (an infinity times a part that is zero or of the other sign is NaN) or whose squares overflow, and operands below 2^-109,
@@ -126,17 +133,17 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
       f[i] = __builtin_shufflevector(lds_read_tr(p), lds_read_tr(p + 4 * tp::SIDE), 0, 1, 2, 3, 4, 5, 6, 7);
     }
   };
-  f32x4_t acc[4][4];
+  f32x4_t acc[4][4], low[4][4];   // the products of the first parts; all others
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  auto products = [&](const s16x8_t* fa, const s16x8_t* fb) {
+    for (int j = 0; j < 4; ++j) acc[i][j] = low[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  auto products = [&](f32x4_t (&c)[4][4], const s16x8_t* fa, const s16x8_t* fb) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j], 0, 0, 0);
+        c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), c[i][j], 0, 0, 0);
   };
 
   const int nk = (T + 31) / 32;
@@ -145,19 +152,22 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
   fetch();
   __syncthreads();
   for (int k = 0; k < nk; ++k) {
+    // (in an order that keeps at most five of the six operand parts in registers)
     s16x8_t a1[4], a2[4], a3[4], b1[4], b2[4], b3[4];
-    frags(a_rd, 0, a1);
-    frags(b_rd, 2, b3);
-    frags(b_rd, 1, b2);
-    products(a1, b3);   // the small terms first
-    frags(b_rd, 0, b1);
-    frags(a_rd, 2, a3);
     frags(a_rd, 1, a2);
-    products(a3, b1);
-    products(a2, b2);
-    products(a1, b2);
-    products(a2, b1);
-    products(a1, b1);
+    frags(b_rd, 2, b3);
+    frags(a_rd, 0, a1);
+    products(low, a2, b3);
+    frags(b_rd, 1, b2);
+    products(low, a1, b3);
+    frags(a_rd, 2, a3);
+    products(low, a1, b2);
+    products(low, a2, b2);
+    frags(b_rd, 0, b1);
+    products(low, a3, b2);
+    products(low, a3, b1);
+    products(low, a2, b1);
+    products(acc, a1, b1);
     __syncthreads();    // every wave has read its fragments
     if (k + 1 < nk) {
       stage();
@@ -165,6 +175,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
       __syncthreads();
     }
   }
+
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] += low[i][j];
 
   // acc[i][j][r] = element (64 wave_m + 16 i + lane % 16, 64 wave_n + 16 j + 4 (lane / 16) + r) of the tile
   auto square_sum = [&]() {
