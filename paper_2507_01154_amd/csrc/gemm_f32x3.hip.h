@@ -218,7 +218,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         ragged = fmaf(0.0f, edge_p ? y[i] : 0.0f, ragged);
-        ragged = fmaf(0.0f, edge_d ? (x[i][0] + x[i][1]) + (x[i][2] + x[i][3]) : 0.0f, ragged);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ragged = fmaf(0.0f, edge_d ? x[i][e] : 0.0f, ragged);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll

@@ -1099,6 +1099,27 @@ def test_fp32_values_next_to_nothing_leave_their_tile_as_it_is(small):
     assert bool(torch.all((res[1][7] - want).abs() <= 8 * 2.0 ** -24 * mag + 2.0 ** -149))
 
 
+@pytest.mark.parametrize("P,D", [(300, 260), (128, 132), (516, 256)])
+def test_fp32_largest_values_beside_a_ragged_edge_stay_finite(P, D):
+    # neighbouring operands whose sum overflows, in gradients that do not: against the generic kernel
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P)
+    B, T = 2, 40
+    X, dY = torch.randn((B, T, P), generator=g, device=DEV), torch.randn((B, T, D), generator=g, device=DEV) * 1e-35
+    X[0, 3, :] = 2e38
+    X[1, 5, ::3] = -2e38
+    res = []
+    for tile in (None, -1):
+        out, norms = torch.empty((D, P), device=DEV), torch.empty((B,), device=DEV)
+        with env(FLASHDP_TILE=tile):
+            F.flashdp_block_dp_grad([dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)], B, T, F.F32, "scratch")
+        assert F.flashdp_last_kernel() == ("gemm_simple_kernel" if tile else "gemm_f32x3_kernel")
+        res.append((out, norms))
+    (o, n), (ro, rn) = res
+    assert bool(torch.all(torch.isfinite(o))) and torch.allclose(n, rn, rtol=1e-6, atol=0)
+    assert float((o - ro).double().norm()) <= 2e-6 * float(ro.double().norm())
+
+
 @pytest.mark.parametrize("schedule", ["scratch", "twopass", "explicit", "ghost"])
 def test_nan_in_one_sample_poisons_the_output_instead_of_passing_unclipped(schedule):
     base = W.WORKLOADS["gpt2_small_mlp_up"]
