@@ -634,9 +634,14 @@ hipError_t run_rows(const flashdp_layer_t& L, int64_t B, int dtype, char* ws, hi
 
 #define HIP_TRY(expr) do { if ((expr) != hipSuccess) { (void)hipGetLastError(); return FLASHDP_HIP_ERROR; } } while (0)
 
-// Whether the streaming kernel of the scratch schedule works out the clip factors itself (see run_layer).
-bool fold_clip_ok(int64_t B, int tiles, size_t agg_grid) {
-  return B <= MAX_FUSED_CLIP_B && agg_grid * (size_t)B * tiles * 4 <= (size_t(64) << 20);
+// Whether the streaming kernel of the scratch schedule works out the clip factors itself (see run_layer).  Each of its four
+// waves takes every fourth sample one after the other, about 0.7 us each, in front of the sum; the launch saved is worth 2 us.
+// fp32 (us a call, so and with a launch for the factors): up to 8 samples and 8 MB of redundant reads: 512 x 512, T = 32, B = 2: 12.5,
+// 15.2, B = 8: 16.4, 17.1; 2048 x 2048, B = 2 (8 MB): 27.6, 30.2; beyond: B = 12: 19.0, 19.1, B = 24: 27.9, 26.2, B = 64: 47.0, 37.3;
+// 32 x 32, B = 64: 28.1, 19.5; 768 x 3072, B = 8 (11 MB): 43.5, 42.4; 4096 x 4096, B = 1 (64 MB): 57.7, 49.5.
+bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
+  const size_t reads = agg_grid * (size_t)B * tiles * 4;
+  return dtype == FLASHDP_F32 ? B <= 8 && reads <= (size_t(8) << 20) : B <= MAX_FUSED_CLIP_B && reads <= (size_t(64) << 20);
 }
 
 // The parking pass on 128 x 128 tiles (gemm_tile128.hip.h) of one layer or several: one workgroup per tile and sample.
@@ -682,7 +687,7 @@ GroupSlot group_slot(const Park& k, int64_t B, int64_t P, int64_t D, size_t begi
 bool group_ok(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || g_ctx.stages != FLASHDP_STAGE_ALL) return false;
   const Park k = park_of(L, B, T, dtype);
-  return k.small && fold_clip_ok(B, k.tiles_m * k.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
+  return k.small && fold_clip_ok(dtype, B, k.tiles_m * k.tiles_n, ((size_t)L.d_in * L.d_out / 8 + 255) / 256);
 }
 // Neither layer writes what the other reads or writes (a caller may pass one buffer twice: such layers keep their order).
 bool group_disjoint(const flashdp_layer_t& x, const flashdp_layer_t& y, int64_t B, int64_t T) {
@@ -1017,7 +1022,7 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
     // schedule always qualifies.
     const size_t n8_all = (S + 7) / 8, full_grid = dtype == FLASHDP_F32 ? ((S + 3) / 4 + 255) / 256 : (n8_all + 255) / 256;
     const size_t agg_grid = persistent_grid > 0 ? std::min((size_t)persistent_grid, full_grid) : full_grid;
-    const bool fold_clip = (dtype == FLASHDP_F32 || S >= 8) && fold_clip_ok(B, tiles, agg_grid) &&
+    const bool fold_clip = (dtype == FLASHDP_F32 || S >= 8) && fold_clip_ok(dtype, B, tiles, agg_grid) &&
                            (stages & (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE)) == (FLASHDP_STAGE_CLIP | FLASHDP_STAGE_AGGREGATE);
     if (fold_clip && dtype == FLASHDP_F32) {
       auto kern = aggregate32_streams(B, S) ? clip_aggregate32_kernel<true> : clip_aggregate32_kernel<false>;
