@@ -245,3 +245,28 @@ def test_register_budget_of_the_overlapped_schedule():
             assert u.get("ScratchSize [bytes/lane]", 0) <= 64, (k, u)
             continue
         assert u.get("VGPRs Spill", 0) == 0 and u.get("ScratchSize [bytes/lane]", 0) == 0, (k, u)
+
+
+@pytest.mark.parametrize("dt", ["DT_BF16", "DT_F16"])
+def test_the_accumulating_pass_of_short_sequences_does_not_drain_its_loads_at_every_sample(dt, tmp_path):
+    """The compiler does not see the direct loads to LDS (inline assembly), but its waits for loads that it does see count
+    them: a wait for all of them belongs only where the clip factors of the next 64 samples are fetched, not where one
+    is used.  Read off the basic blocks between the first and the last matrix instruction."""
+    import re
+    import subprocess
+    from paper_2507_01154_amd import build as B
+    src = tmp_path / "accum.hip"
+    src.write_text('#include "gemm_tile128.hip.h"\n'
+                   f"template __global__ void flashdp::gemm_tile128_kernel<flashdp::MODE_ACCUM, flashdp::{dt}>(const flashdp::Tile128Args);\n")
+    out = tmp_path / "accum.s"
+    res = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature",
+                          "-Xclang", "-packed-fp32-ops", "--cuda-device-only", "-S", "-I" + B.CSRC, str(src), "-o", str(out)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    start = re.search(r"\n(_ZN7flashdp19gemm_tile128_kernel\w+):", text)
+    blocks = re.split(r"\n(?=\.LBB\w+:|; %bb)", text[start.end():text.index(".Lfunc_end", start.end())])
+    with_products = [i for i, b in enumerate(blocks) if "v_mfma" in b]
+    loop = blocks[with_products[0]:with_products[-1] + 1]
+    assert len(with_products) == 8 and sum("v_readlane_b32" in b for b in loop) >= 3      # (four k-tiles, each with a sample's first products)
+    full = [b for b in loop if re.search(r"s_waitcnt[^\n]*vmcnt\(0\)", b)]
+    assert len(full) >= 3 and all("global_load" in b for b in full)
