@@ -131,7 +131,9 @@ enum { FLASHDP_BF16 = 0, FLASHDP_F32 = 1, FLASHDP_F16 = 2 };
  *            tiles, all layers of a call in shared launches, in a workspace of 4 B + 16 B ceil(d_out / 128)
  *            ceil(d_in / 128) bytes a layer; a larger one holds partial sums over parts of the batch where the layers
  *            alone do not fill the chip.  Which layers are together and how many parts there are decides the order
- *            of fp32 additions, so results of different groupings agree to fp32 rounding, not bit for bit. */
+ *            of fp32 additions, so results of different groupings agree to fp32 rounding, not bit for bit.  A caller's
+ *            workspace decides both by its size; without one both follow from the call alone, whatever earlier calls
+ *            have left in the library's workspace. */
 enum { FLASHDP_SCHEDULE_AUTO = 0, FLASHDP_SCHEDULE_TWOPASS = 1, FLASHDP_SCHEDULE_SCRATCH = 2, FLASHDP_SCHEDULE_EXPLICIT = 3,
        FLASHDP_SCHEDULE_OVERLAP = 4, FLASHDP_SCHEDULE_GHOST = 5, FLASHDP_SCHEDULE_FUSED = 6 };
 

@@ -808,6 +808,7 @@ ShortPlan short_plan(int64_t B, int64_t P, int64_t D, size_t begin, int splits) 
   p.end = p.sums + (splits > 1 ? align_up((size_t)splits * P * D * 4, 256) : 0);
   return p;
 }
+constexpr int64_t SHORT_SPLITS = 8;
 bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || T < 2 || B < 2 || g_ctx.stages != FLASHDP_STAGE_ALL || env().tile != 0) return false;
   double gain = -9.0;
@@ -819,28 +820,27 @@ bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dt
   }
   return gain > 0.0;
 }
-// How many layers from the first on share the launches (0: the workspace does not hold the first), and how many workgroups
-// walk over the samples of one tile in the accumulating pass: enough to fill the chip, as far as the workspace holds their
-// partial sums.
-int short_group(const flashdp_layer_t* layers, int n, int64_t B, size_t ws_bytes, int64_t T, int* splits) {
-  size_t used = 0;
+// The first layers of a call that share their launches, as many as `budget` bytes hold (n = 0: not the first), and how many workgroups walk over
+// the samples of one tile in the accumulating pass: enough to fill the chip, each with two dozen k-tiles or more, as far as the budget
+// holds their partial sums (34 MB at most: two tiles a CU).
+struct ShortGroup { int n, splits; size_t bytes; };
+ShortGroup short_group(const flashdp_layer_t* layers, int n_layers, int64_t B, int64_t T, size_t budget) {
+  ShortGroup g{0, 1, 0};
   int64_t tiles = 0;
-  int k = 0;
-  for (; k < n && k < GROUP_MAX; ++k) {
-    const ShortPlan p = short_plan(B, layers[k].d_in, layers[k].d_out, used, 1);
+  for (; g.n < n_layers && g.n < GROUP_MAX && (g.n + 1) * B <= (int64_t(1) << 23); ++g.n) {   // (a workgroup per layer and sample: 2^32 threads)
+    const ShortPlan p = short_plan(B, layers[g.n].d_in, layers[g.n].d_out, g.bytes, 1);
     bool apart = true;
-    for (int j = 0; j < k && apart; ++j) apart = group_disjoint(layers[j], layers[k], B, T);
-    if (p.end > ws_bytes || !apart) break;
-    used = p.end;
+    for (int j = 0; j < g.n && apart; ++j) apart = group_disjoint(layers[j], layers[g.n], B, T);
+    if (p.end > budget || !apart) break;
+    g.bytes = p.end;
     tiles += (int64_t)p.tiles_m * p.tiles_n;
   }
-  *splits = 1;
-  for (int64_t q = std::min({B, (int64_t)8, 2 * plan_cus() / std::max<int64_t>(tiles, 1), B * ((T + 31) / 32) / 24}); q > 1; --q) {
+  for (int64_t q = std::min({B, SHORT_SPLITS, 2 * plan_cus() / std::max<int64_t>(tiles, 1), B * ((T + 31) / 32) / 24}); q > 1; --q) {
     size_t end = 0;
-    for (int l = 0; l < k; ++l) end = short_plan(B, layers[l].d_in, layers[l].d_out, end, (int)q).end;
-    if (end <= ws_bytes) { *splits = (int)q; break; }
+    for (int l = 0; l < g.n; ++l) end = short_plan(B, layers[l].d_in, layers[l].d_out, end, (int)q).end;
+    if (end <= budget) { g.splits = (int)q; g.bytes = end; break; }
   }
-  return k;
+  return g;
 }
 
 template <int DT>
@@ -1143,22 +1143,33 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     return FLASHDP_OK;
   }
   if (schedule == FLASHDP_SCHEDULE_AUTO && short_ok(layers, n_layers, B, T, dtype)) {
-    size_t need = 0;
-    for (int l = 0; l < n_layers; ++l) need = std::max(need, short_plan(B, layers[l].d_in, layers[l].d_out, 0, 1).end);
+    size_t least = 0;   // one layer at a time
+    for (int l = 0; l < n_layers; ++l) least = std::max(least, short_plan(B, layers[l].d_in, layers[l].d_out, 0, 1).end);
+    size_t budget = workspace_bytes;
     if (!workspace) {
+      // Of the library's workspace what the call is fastest in, whatever earlier calls have left there: the groups decide
+      // the order of additions, and equal calls give equal bits.  (Memory too short for that: the least.)
+      budget = 0;
+      for (int k = 0; k < n_layers;) {
+        const ShortGroup g = short_group(layers + k, n_layers - k, B, T, SIZE_MAX);
+        if (g.n == 0) break;
+        budget = std::max(budget, g.bytes);
+        k += g.n;
+      }
       void* p = nullptr; size_t got = 0;
-      st = owned_workspace(std::max(need, need_scratch), &p, &got);
+      if ((st = owned_workspace(budget, &p, &got)) == FLASHDP_HIP_ERROR && least < budget) {
+        budget = least;
+        st = owned_workspace(least, &p, &got);
+      }
       if (st != FLASHDP_OK) return st;
       ws = static_cast<char*>(p);
-      ws_bytes = got;
     }
-    if (ws_bytes >= need) {
+    if (budget >= least && B <= (int64_t(1) << 23)) {
       for (int k = 0; k < n_layers;) {
-        int splits = 1;
-        const int n = short_group(layers + k, n_layers - k, B, ws_bytes, T, &splits);
-        HIP_TRY(dtype == FLASHDP_BF16 ? run_short<DT_BF16>(layers + k, n, splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0)
-                                      : run_short<DT_F16>(layers + k, n, splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
-        k += n;
+        const ShortGroup g = short_group(layers + k, n_layers - k, B, T, budget);
+        HIP_TRY(dtype == FLASHDP_BF16 ? run_short<DT_BF16>(layers + k, g.n, g.splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0)
+                                      : run_short<DT_F16>(layers + k, g.n, g.splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
+        k += g.n;
       }
       g_ctx.last_chunk = B;
       g_ctx.last_schedule = "twopass";

@@ -920,6 +920,41 @@ def test_short_sequences_take_two_passes_on_small_tiles(B, T, dims, dtype):
         assert float((got - 2 * o).abs().max()) <= 1e-6 * 2 * float(o.abs().max()) + 3 * 2.0 ** -24 * (3 * L["C"] + 2 * float(o.abs().max()))
 
 
+FRESH_PROCESS = """
+import torch, paper_2507_01154_amd as F
+g = torch.Generator(device="cuda:0"); g.manual_seed(1)
+def call(B, T, dims):
+    g.manual_seed(B)
+    Ls = [dict(X=torch.randn((B, T, P), generator=g, device="cuda:0").bfloat16(), dY=torch.randn((B, T, D), generator=g, device="cuda:0").bfloat16(),
+               d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=l, out_grad=torch.empty((D, P), device="cuda:0")) for l, (P, D) in enumerate(dims)]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    F.flashdp_block_dp_grad(Ls, B, T, F.BF16, "auto")
+    torch.cuda.synchronize()
+    return [L["out_grad"] for L in Ls], F.flashdp_last_schedule(), free - torch.cuda.mem_get_info()[0]
+small = (16, 200, [(1024, 1024)] * 4)
+a, s, _ = call(*small)
+assert s == "twopass", s
+_, s, taken = call(64, 16, [(5120, 13824)])
+assert s == "twopass" and taken < 1 << 30, (s, taken)
+_, s, _ = call(4, 1024, [(4096, 4096)])
+assert s == "scratch", s
+b, s, _ = call(*small)
+assert s == "twopass" and all(torch.equal(x, y) for x, y in zip(a, b))
+"""
+
+
+def test_short_sequences_give_the_same_bits_whatever_the_library_workspace_holds():
+    # in a process of its own, where the library's workspace is still empty: the number of partial sums is that of the call, not
+    # of what an earlier, larger call has left; and no room for parked samples is taken where none are parked (9 GB there)
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", FRESH_PROCESS], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,T,P,D", [(16, 97, 768, 760), (5, 333, 1032, 1928), (3, 40, 1480, 2056), (3, 2100, 1096, 2312), (12, 130, 1288, 1288)])
 def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype):
