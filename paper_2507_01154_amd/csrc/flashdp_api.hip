@@ -521,13 +521,19 @@ int device_or_error(int* dev) {
   return FLASHDP_OK;
 }
 
-// wish: the size to take, if more than need, when the workspace has to grow anyway.
-int owned_workspace(size_t need, void** ptr, size_t* bytes, size_t wish = 0) {
+// wish: the size to take, if more than need, when the workspace has to grow anyway.  least: what the caller on `stream` can do
+// with where the workspace must not grow, while a graph is captured (growing would end the capture).
+int owned_workspace(size_t need, void** ptr, size_t* bytes, size_t wish = 0, size_t least = SIZE_MAX, hipStream_t stream = nullptr) {
   int dev = 0;
   int st = device_or_error(&dev);
   if (st != FLASHDP_OK) return st;
   std::lock_guard<std::mutex> lock(g_ws_mutex);
   OwnedWs& w = g_owned[dev];
+  if (w.bytes < need && w.bytes >= least) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) need = least;
+  }
   if (w.bytes < need) {
     // Growing costs a device-wide synchronisation (earlier calls may still use the old block), a free and an
     // allocation, inside what may be a training step: grow by at least half, so that a sequence of slowly growing
@@ -1148,7 +1154,8 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     size_t budget = workspace_bytes;
     if (!workspace) {
       // Of the library's workspace what the call is fastest in, whatever earlier calls have left there: the groups decide
-      // the order of additions, and equal calls give equal bits.  (Memory too short for that: the least.)
+      // the order of additions, and equal calls give equal bits.  (The least where memory is too short, or the workspace while a
+      // graph is captured.)
       budget = 0;
       for (int k = 0; k < n_layers;) {
         const ShortGroup g = short_group(layers + k, n_layers - k, B, T, SIZE_MAX);
@@ -1157,11 +1164,10 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
         k += g.n;
       }
       void* p = nullptr; size_t got = 0;
-      if ((st = owned_workspace(budget, &p, &got)) == FLASHDP_HIP_ERROR && least < budget) {
-        budget = least;
+      if ((st = owned_workspace(budget, &p, &got, 0, least, static_cast<hipStream_t>(stream))) == FLASHDP_HIP_ERROR && least < budget)
         st = owned_workspace(least, &p, &got);
-      }
       if (st != FLASHDP_OK) return st;
+      if (got < budget) budget = least;
       ws = static_cast<char*>(p);
     }
     if (budget >= least && B <= (int64_t(1) << 23)) {
@@ -1228,7 +1234,7 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     if (mode == FLASHDP_SCHEDULE_SCRATCH)
       for (int l = 0; l < n_layers; ++l) best = std::max(best, layer_ws_bytes(layers[l], B, T, dtype, mode, true));
     void* p = nullptr; size_t got = 0;
-    st = owned_workspace(best, &p, &got, wish);
+    st = owned_workspace(best, &p, &got, wish, need, static_cast<hipStream_t>(stream));
     if (st != FLASHDP_OK) return st;
     ws = static_cast<char*>(p);
     ws_bytes = got;
