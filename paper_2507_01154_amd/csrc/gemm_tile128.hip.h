@@ -7,7 +7,7 @@
 // and sample, beside 4 T / 1e15 seconds of arithmetic) is most of the time, the rest being start and end of one workgroup per
 // tile and sample.  Computing every G_i twice costs 2 T FLOP an element and sample instead and nothing is parked; and a
 // workgroup that keeps its tile and walks over the samples loads the next sample's first k-tiles while it multiplies the
-// last ones of this sample.  Every term stays in fp32, where parking rounds it to 8 bits once.
+// last ones of this sample (the accumulating pass up to 64 tokens; see in_step).  Every term stays in fp32, where parking rounds it to 8 bits once.
 //
 // Pipeline as gemm_mfma_dma_kernel: operand tiles straight into a ring of 4 LDS stages, the loads of k-tile k + 3 issued
 // at the top of k-tile k, one barrier per k-tile, waits for the direct loads by hand (they complete in order).  4 waves of
@@ -184,8 +184,11 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
   };
   auto lanes_from_memory = [&]() { per_lane = a.factors[min(s_base + lane, a.B - 1)]; };
   // The compiler waits here for the load above, and not where the value is used: as it does not see the direct loads, that would
-  // be a wait for all of them at every sample (bf16, a call, with that and so: 4096 x 4096, B = 64, T = 16: 199 us, 186; 256 x 256,
-  // B = 4096, T = 128: 952, 716).
+  // be a wait for all of them at every sample.  Such a wait is worth its time where a sample has more than two k-tiles: without it the
+  // workgroups that share operands drift apart, and the loads they run ahead with come from farther away.  bf16, a call, with a
+  // wait at every sample and without: 4096 x 4096, T = 16, B = 64: 189 us, 179; a GPT-2 block, B = 256, T = 16: 337, 315, T = 64: 597, 593,
+  // T = 128: 1176, 1271; 4096 x 4096, B = 128, T = 192: 1831, 2073; 1024 x 4096, B = 200, T = 128: 420, 414.
+  const bool in_step = a.T > 64;
   auto lanes_arrived = [&]() { asm volatile("" : "+v"(per_lane)); };
   if constexpr (MODE == MODE_ACCUM) lanes_from_memory();
   auto sample_done = [&]() {
@@ -201,6 +204,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
       const float sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), 63));
       per_lane = lane == s - s_base ? sum : per_lane;
     } else if constexpr (MODE == MODE_ACCUM) {
+      if (in_step) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, per_lane), s - s_base));
 #pragma unroll
       for (int i = 0; i < 4; ++i)

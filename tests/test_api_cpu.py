@@ -250,7 +250,7 @@ def test_register_budget_of_the_overlapped_schedule():
 @pytest.mark.parametrize("dt", ["DT_BF16", "DT_F16"])
 def test_the_accumulating_pass_of_short_sequences_does_not_drain_its_loads_at_every_sample(dt, tmp_path):
     """The compiler does not see the direct loads to LDS (inline assembly), but its waits for loads that it does see count
-    them: a wait for all of them belongs only where the clip factors of the next 64 samples are fetched, not where one
+    them: a wait for all of them belongs where the clip factors of the next 64 samples are fetched, not where one
     is used.  Read off the basic blocks between the first and the last matrix instruction."""
     import re
     import subprocess
@@ -269,4 +269,6 @@ def test_the_accumulating_pass_of_short_sequences_does_not_drain_its_loads_at_ev
     loop = blocks[with_products[0]:with_products[-1] + 1]
     assert len(with_products) == 8 and sum("v_readlane_b32" in b for b in loop) >= 3      # (four k-tiles, each with a sample's first products)
     full = [b for b in loop if re.search(r"s_waitcnt[^\n]*vmcnt\(0\)", b)]
-    assert len(full) >= 3 and all("global_load" in b for b in full)
+    # where the factors are fetched, and in a branch of its own for longer sequences
+    fetch, own = [b for b in full if "global_load" in b], [b for b in full if "global_load" not in b]
+    assert len(fetch) >= 3 and all("v_readlane" not in b and "v_mfma" not in b for b in own)
