@@ -814,7 +814,10 @@ ShortPlan short_plan(int64_t B, int64_t P, int64_t D, size_t begin, int splits) 
   p.end = p.sums + (splits > 1 ? align_up((size_t)splits * P * D * 4, 256) : 0);
   return p;
 }
-constexpr int64_t SHORT_SPLITS = 8;
+// Workgroups per tile in the accumulating pass, at most: layers of few tiles and many samples leave the chip idle with fewer, and
+// adding up more partial sums takes longer than they save (bf16, a call, with up to 8, 16, 32, 64, 128: 128 x 128, B = 1024, T = 16: 75, 48, 36, 35,
+// 35 us; 256 x 256, B = 4096, T = 128: 733, 414, 274, 218, 230 (893 parked); 128 x 256, B = 1024, T = 128: 162, 98, 65, 56, 59).
+constexpr int64_t SHORT_SPLITS = 64;
 bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || T < 2 || B < 2 || g_ctx.stages != FLASHDP_STAGE_ALL || env().tile != 0) return false;
   double gain = -9.0;

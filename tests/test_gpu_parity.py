@@ -920,6 +920,30 @@ def test_short_sequences_take_two_passes_on_small_tiles(B, T, dims, dtype):
         assert float((got - 2 * o).abs().max()) <= 1e-6 * 2 * float(o.abs().max()) + 3 * 2.0 ** -24 * (3 * L["C"] + 2 * float(o.abs().max()))
 
 
+@pytest.mark.parametrize("B,T,P,D", [(1600, 5, 256, 128), (2000, 65, 128, 248), (300, 40, 256, 256)])
+def test_short_sequences_of_many_samples_on_few_tiles(B, T, P, D):
+    # more partial sums than layers that fill the chip have (up to 64), and the sample ends with a wait (T > 64) and without; with
+    # the workspace that holds all of them, fewer and none.  fp32 sums of T and B terms: 1e-6, as above
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B)
+    X = torch.randn((B, T, P), generator=g, device=DEV).bfloat16()
+    dY = (torch.randn((B, T, D), generator=g, device=DEV) * 0.05 * 10 ** (2 * torch.rand((B, 1, 1), generator=g, device=DEV) - 1)).bfloat16()
+    G = torch.matmul(dY.float().transpose(1, 2).contiguous(), X.float())
+    n = G.flatten(1).double().norm(dim=1)
+    want = torch.zeros((D, P), dtype=torch.float64, device=DEV)
+    for k in range(0, B, 64):
+        y = dY[k:k + 64].double() * torch.clamp(1.0 / n[k:k + 64], max=1.0)[:, None, None]
+        want += y.flatten(0, 1).T.contiguous() @ X[k:k + 64].double().flatten(0, 1)
+    out, norms = torch.empty((D, P), device=DEV), torch.empty((B,), device=DEV)
+    L = [dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)]
+    full = F.flashdp_workspace_bytes(L, B, T, F.BF16, "auto")
+    for size in (None, full, (1 << 20) + 5 * 4 * P * D, 1 << 18):
+        out.fill_(float("nan"))
+        F.flashdp_block_dp_grad(L, B, T, F.BF16, "auto", None if size is None else torch.empty((size,), dtype=torch.uint8, device=DEV))
+        assert F.flashdp_last_schedule() == "twopass" and F.flashdp_last_kernel() == "gemm_tile128_kernel"
+        assert float((out - want).norm() / want.norm()) <= 1e-6 and float(((norms - n).abs() / n).max()) <= 1e-6
+
+
 FRESH_PROCESS = """
 import torch, paper_2507_01154_amd as F
 g = torch.Generator(device="cuda:0"); g.manual_seed(1)
