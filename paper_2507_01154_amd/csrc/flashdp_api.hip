@@ -796,8 +796,8 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
 
 // Short sequences (gemm_tile128.hip.h): AUTO takes the two-pass schedule on 128 x 128 tiles, all layers of the call in its
 // three or four launches, where that is the faster way.  Parking costs about 0.68 us per million elements and sample (2 + 2
-// bytes), the second contraction 0.05 us + 1.95 ns a token of the padded tiles, and the launches 9 us (fitted to 170 calls; the
-// rule is within 1 % of the faster way where it takes this one).  bf16, a call, parked and so, in us: a GPT-2 block, B = 64: T = 16:
+// bytes), the second contraction 0.05 us + 1.95 ns a token of the padded tiles, and the launches 9 us (fitted to 170 calls;
+// in a band of some 20 tokens about the limit the way taken may be a few per cent the slower one).  bf16, a call, parked and so, in us: a GPT-2 block, B = 64: T = 16:
 // 466, 105; T = 128: 490, 266; T = 256: 633, 553; B = 4, T = 128: 67, 44; 4096 x 4096, B = 64: T = 16: 892, 190; T = 64: 911, 300;
 // 5120 x 13824, B = 4, T = 16: 290, 170; 264 x 6000, B = 64, T = 16: 131, 70; left to parking: 768 x 768, B = 16, T = 64: 22, 25;
 // 1024 x 3072, B = 64, T = 256: 223, 226; one sample (4096 x 4096, T = 64: 39, 41).
@@ -820,12 +820,24 @@ ShortPlan short_plan(int64_t B, int64_t P, int64_t D, size_t begin, int splits) 
 constexpr int64_t SHORT_SPLITS = 64;
 bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dtype) {
   if (dtype == FLASHDP_F32 || T < 2 || B < 2 || g_ctx.stages != FLASHDP_STAGE_ALL || env().tile != 0) return false;
+  // Operands that no cache holds, read by several rounds of workgroups: the passes take longer from about 200 tokens on (parked and
+  // two passes: a GPT-2 block, B = 128: T = 224: 1151, 1059; T = 256: 1162, 1247; T = 288: 1289, 1447; 4096 x 4096, B = 128: T = 224: 2519, 2150; T = 288:
+  // 2819, 2978; B = 64, T = 312: 1454, 1512; left as they are: 1024 x 4096, B = 200, T = 312: 1151, 1109; 512 x 512, B = 1024, T = 256: 480, 332;
+  // 5120 x 13824, B = 16, T = 288: 1385, 1228, whose 189 MB stay in the cache).
+  double operands = 0.0;   // MB
+  int64_t tiles = 0;
+  for (int l = 0; l < n; ++l) {
+    operands += (double)B * T * (layers[l].d_in + layers[l].d_out) * 2.0 / (1 << 20);
+    tiles += ((layers[l].d_in + 127) / 128) * ((layers[l].d_out + 127) / 128);
+  }
+  const int64_t slots = 2 * plan_cus();
+  const bool far = operands > 256.0 && 2 * tiles >= slots && operands * ((tiles + slots - 1) / slots) > 620.0;
   double gain = -9.0;
   for (int l = 0; l < n; ++l) {
     const int64_t P = layers[l].d_in, D = layers[l].d_out;
     if (P % 8 != 0 || D % 8 != 0 || (T + 320) * std::max(P, D) * 2 >= (int64_t(1) << 31)) return false;
     const double parked = 1e-6 * B * P * D, padded = 1e-6 * B * ((P + 127) / 128) * ((D + 127) / 128) * 16384;
-    gain += 0.68 * parked - (0.05 + 0.00195 * T) * padded;
+    gain += 0.68 * parked - (0.05 + (far ? 0.00252 : 0.00195) * T) * padded;
   }
   return gain > 0.0;
 }
