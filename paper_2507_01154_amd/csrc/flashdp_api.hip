@@ -300,7 +300,10 @@ const char* path_kernel_name(Path p) {
 // B = 2, T = 2048: 52.5, 33.2; 1024 x 1024, B = 8, T = 333: 18.4, 10.2; 1472 x 7360, B = 2, T = 333: 33.5, 23.9; 1480 x 1000, B = 16, T = 333:
 // 35.7, 29.2; left to large ones: 768 x 3072, B = 8, T = 1024: 38.6, 45.7; 2048 x 2048, B = 4, T = 2048: 55.8, 63.6; operands
 // that no cache holds: 256 x 6432, B = 16, T = 2048: 116, 148).  Several rounds of large tiles are given up for a clear gain only, and
-// not below the 128 tokens it was measured from.  by_far: enough to give up the overlapped schedule as well, which the
+// not below the 128 tokens it was measured from.  Rows that are no multiple of 128 bytes: the 256 bytes that a small tile takes of
+// a row lie in three lines instead of two, where a large tile's 512 lie in five instead of four: a round takes 2.0 us + 7.0 ns a token
+// (fitted to 460 contractions; a call, large and small: left to large ones so: 1480 x 1000, B = 64, T = 256: 125, 140; 1000 x 1000, B = 64, T = 200:
+// 89, 98; 1288 x 1288, B = 24, T = 2048: 205, 217; small: 1032 x 1928, B = 8, T = 512: 48, 39; 2000 x 2000, B = 5, T = 333: 48, 39).  by_far: enough to give up the overlapped schedule as well, which the
 // small tiles do not have (layers of one round park and are summed in shared launches instead).
 struct Park { bool small, by_far; int tiles_m, tiles_n; };
 Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
@@ -317,9 +320,12 @@ Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dt
   if (p.path == PATH_DMA16 || p.path == PATH_DMA_384x192 || p.path == PATH_DMA_192x384) {
     const int64_t cus = plan_cus();
     const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * B + cus - 1) / cus, rounds128 = ((int64_t)k.tiles_m * k.tiles_n * B + cus - 1) / cus;
-    const double large = 2.0 + rounds * (8.5 + (p.path == PATH_DMA16 ? 0.0212 : 0.0272) * T), small = 3.0 + rounds128 * (1.4 + 0.0062 * T);
+    const bool lines = P % 64 == 0 && D % 64 == 0;
+    const double large = 2.0 + rounds * (8.5 + (p.path == PATH_DMA16 ? 0.0212 : 0.0272) * T);
+    const double small = 3.0 + rounds128 * (lines ? 1.4 + 0.0062 * T : 2.0 + 0.007 * T);
+    const double margin = lines ? (rounds == 1 ? 0.95 : 0.9) : (rounds == 1 ? 0.97 : 0.93);
     const bool cached = B * T * (P + D) * 2 <= (int64_t(256) << 20);
-    k.small = cached && small < (rounds == 1 ? 0.95 : 0.9) * large && (rounds == 1 || T >= 128);
+    k.small = cached && small < margin * large && (rounds == 1 || T >= 128);
     k.by_far = k.small && (rounds == 1 || small < 0.8 * large);
   }
   return k;
