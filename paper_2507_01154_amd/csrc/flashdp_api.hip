@@ -305,9 +305,13 @@ const char* path_kernel_name(Path p) {
 // (fitted to 460 contractions; a call, large and small: left to large ones so: 1480 x 1000, B = 64, T = 256: 125, 140; 1000 x 1000, B = 64, T = 200:
 // 89, 98; 1288 x 1288, B = 24, T = 2048: 205, 217; small: 1032 x 1928, B = 8, T = 512: 48, 39; 2000 x 2000, B = 5, T = 333: 48, 39).  by_far: enough to give up the overlapped schedule as well, which the
 // small tiles do not have (layers of one round park and are summed in shared launches instead).
-struct Park { bool small, by_far; int tiles_m, tiles_n; };
+struct Park { bool small, by_far; int tiles_m, tiles_n; int edges; };
+// Where the plan's own tiles, larger than 128 x 128, reach beyond the layer (any_not_finite).
+int large_edges(const Plan& p, int64_t P, int64_t D) {
+  return (p.bm > 128 && D % p.bm != 0 ? 1 : 0) | (p.bn > 128 && P % p.bn != 0 ? 2 : 0);
+}
 Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
-  Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128)};
+  Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128), large_edges(p, P, D)};
   if (p.any || env().tile != 0) return k;
   if (dtype == FLASHDP_F32) {
     // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for layers of one small
@@ -660,7 +664,7 @@ bool fold_clip_ok(int dtype, int64_t B, int tiles, size_t agg_grid) {
 Tile128Layer park128(const flashdp_layer_t& L, const Park& p, int64_t B, int64_t T, float* partials, void* scratch) {
   Tile128Layer a;
   a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
-  a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.splits = (int)B;
+  a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.edges = p.edges; a.splits = (int)B;
   a.partials = partials; a.scratch = scratch;
   a.factors = nullptr; a.out = nullptr; a.noise_scale = 0.0f; a.accumulate = 0; a.seed = 0; a.layer = 0;
   return a;
@@ -871,12 +875,13 @@ ShortGroup short_group(const flashdp_layer_t* layers, int n_layers, int64_t B, i
 }
 
 template <int DT>
-hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B, int64_t T, char* ws, hipStream_t st, bool accumulate, bool add_noise) {
+hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B, int64_t T, int dtype, char* ws, hipStream_t st, bool accumulate, bool add_noise) {
   Tile128Args norm, sum;
   Tile128ClipArgs clip;
   Tile128SumArgs fin;
   norm.n = sum.n = clip.n = n;
   clip.B = (int)B;
+  clip.T = (int)T;
   fin.n = 0;
   norm.first[0] = sum.first[0] = fin.first[0] = 0;
   int64_t all_tiles = 0;
@@ -896,6 +901,7 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
     Tile128Layer& a = norm.layer[l];
     a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
+    a.edges = large_edges(make_plan(B, T, L.d_in, L.d_out, dtype), L.d_in, L.d_out);
     a.splits = (int)norm_splits;
     a.partials = partials; a.scratch = nullptr; a.factors = factors; a.out = nullptr;
     a.noise_scale = noise_scale; a.accumulate = accumulate ? 1 : 0; a.seed = L.seed; a.layer = L.layer;
@@ -904,7 +910,7 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
     sum.layer[l].out = splits > 1 ? sums : L.out_grad;
     norm.first[l + 1] = norm.first[l] + (int)align_up((size_t)(tiles * norm_splits), 8);
     sum.first[l + 1] = sum.first[l] + (int)align_up((size_t)(tiles * splits), 8);
-    clip.layer[l] = Tile128ClipArgs::Layer{partials, factors, L.out_norms, 4 * tiles, L.C};
+    clip.layer[l] = Tile128ClipArgs::Layer{partials, factors, L.out_norms, 4 * tiles, L.C, L.X, L.dY, (int)L.d_in, (int)L.d_out, a.edges};
     if (splits > 1) {
       const size_t S = (size_t)L.d_in * L.d_out;
       fin.layer[fin.n] = Tile128SumArgs::Layer{sums, L.out_grad, S, splits, accumulate ? 1 : 0, noise_scale, L.seed, L.layer};
@@ -919,7 +925,7 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(knorm, dim3((unsigned)norm.first[n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, norm);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(tile128_clip_kernel, dim3((unsigned)(n * B)), dim3(256), 0, st, clip);
+  hipLaunchKernelGGL(tile128_clip_kernel<DT>, dim3((unsigned)(n * B)), dim3(256), 0, st, clip);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(ksum, dim3((unsigned)sum.first[n]), dim3(Tile128Cfg::NT), Tile128Cfg::LDS_BYTES, st, sum);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1194,8 +1200,8 @@ int flashdp_block_dp_grad_micro(const flashdp_layer_t* layers, int n_layers, int
     if (budget >= least && B <= (int64_t(1) << 23)) {
       for (int k = 0; k < n_layers;) {
         const ShortGroup g = short_group(layers + k, n_layers - k, B, T, budget);
-        HIP_TRY(dtype == FLASHDP_BF16 ? run_short<DT_BF16>(layers + k, g.n, g.splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0)
-                                      : run_short<DT_F16>(layers + k, g.n, g.splits, B, T, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
+        HIP_TRY(dtype == FLASHDP_BF16 ? run_short<DT_BF16>(layers + k, g.n, g.splits, B, T, dtype, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0)
+                                      : run_short<DT_F16>(layers + k, g.n, g.splits, B, T, dtype, ws, static_cast<hipStream_t>(stream), accumulate != 0, add_noise != 0));
         k += g.n;
       }
       g_ctx.last_chunk = B;

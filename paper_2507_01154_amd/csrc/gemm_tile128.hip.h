@@ -37,6 +37,7 @@ struct Tile128Layer {
   const void* dY;        // [B][T][D]
   int B, T, P, D;
   int tiles_m, tiles_n;  // ceil(D / 128), ceil(P / 128)
+  int edges;             // bits: the layer's large tiles reach beyond D (1), beyond P (2); see any_not_finite
   int splits;            // workgroups per tile: split r walks over samples [B r / splits, B (r + 1) / splits)
   float* partials;       // squared-norm partial sums: [B][tiles_m * tiles_n][4], one per wave (NORM); [B][tiles_m * tiles_n] (SPILL)
   void* scratch;         // [B][D][P] bfloat16 (SPILL)
@@ -87,6 +88,25 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
   v = add_dpp<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
   v = add_dpp<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
   return v;
+}
+
+// An operand that is not finite meets the zeros beyond the edge of a 256 x 256 (384 x 192) tile, and the norm is NaN, which poisons
+// the output.  Where that edge is not one of a 128 x 128 tile, the norm would be infinite instead and the factor 0.  Which
+// tiles a layer takes must not decide that, so a norm that is infinite has its operands looked through: whether any of
+// rows x 8 chunks elements, a row every `pitch` elements, is not finite (by the calling thread's share of them).
+template <int DT>
+__device__ __forceinline__ bool any_not_finite(const void* p, int64_t rows, int chunks, int64_t pitch) {
+  constexpr uint32_t EXP = DT == DT_BF16 ? 0x7F807F80u : 0x7C007C00u;
+  bool found = false;
+  for (int c = threadIdx.x & 15; c < chunks; c += 16)
+#pragma unroll 4
+    for (int64_t r = threadIdx.x >> 4; r < rows; r += 16) {
+      const u32x4_t v = *(const u32x4_t*)((const unsigned short*)p + r * pitch + 8 * c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        found |= (v[q] & EXP & 0xFFFFu) == (EXP & 0xFFFFu) || (v[q] & EXP & 0xFFFF0000u) == (EXP & 0xFFFF0000u);
+    }
+  return found;
 }
 
 template <int MODE, int DT>
@@ -293,7 +313,14 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
     const float w = wave_sum_to_lane63(ss);
     if (lane == 63) red[wave] = w;
     __syncthreads();
-    if (tid == 0) a.partials[(size_t)s_begin * tiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+    float part = (red[0] + red[1]) + (red[2] + red[3]);
+    if (a.edges != 0 && part == __builtin_inff()) {
+      bool found = false;
+      if (a.edges & 1) found |= any_not_finite<DT>((const unsigned short*)a.X + (size_t)s_begin * a.T * a.P + n0, a.T, min(16, (a.P - n0) / 8), a.P);
+      if (a.edges & 2) found |= any_not_finite<DT>((const unsigned short*)a.dY + (size_t)s_begin * a.T * a.D + m0, a.T, min(16, (a.D - m0) / 8), a.D);
+      if (__syncthreads_or(found)) part = __builtin_nanf("");
+    }
+    if (tid == 0) a.partials[(size_t)s_begin * tiles + tile] = part;
     unsigned short* const sc = (unsigned short*)a.scratch + (size_t)s_begin * a.D * a.P;
 #pragma unroll
     for (int it = 0; it < 8; ++it) {
@@ -344,9 +371,10 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
 
 // n_i and c_i from the partials of gemm_tile128_kernel, one workgroup per sample and layer; fixed order of additions.
 struct Tile128ClipArgs {
-  int n, B;
-  struct Layer { const float* partials; float* factors; float* out_norms; int per_sample; float C; } layer[GROUP_MAX];
+  int n, B, T;
+  struct Layer { const float* partials; float* factors; float* out_norms; int per_sample; float C; const void* X; const void* dY; int P, D, edges; } layer[GROUP_MAX];
 };
+template <int DT>
 __global__ __launch_bounds__(256) void tile128_clip_kernel(const Tile128ClipArgs g) {
   __shared__ double red[4];
   const int l = blockIdx.x / g.B, i = blockIdx.x - l * g.B, tid = threadIdx.x;
@@ -362,8 +390,14 @@ __global__ __launch_bounds__(256) void tile128_clip_kernel(const Tile128ClipArgs
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((tid & 63) == 0) red[tid >> 6] = s;
   __syncthreads();
+  double n = sqrt((red[0] + red[1]) + (red[2] + red[3]));
+  if (a.edges != 0 && n == __builtin_inf()) {
+    bool found = false;
+    if (a.edges & 1) found |= any_not_finite<DT>((const unsigned short*)a.X + (size_t)i * g.T * a.P, g.T, a.P / 8, a.P);
+    if (a.edges & 2) found |= any_not_finite<DT>((const unsigned short*)a.dY + (size_t)i * g.T * a.D, g.T, a.D / 8, a.D);
+    if (__syncthreads_or(found)) n = __builtin_nan("");
+  }
   if (tid == 0) {
-    const double n = sqrt((red[0] + red[1]) + (red[2] + red[3]));
     a.factors[i] = clip_factor_of(n, a.C);
     if (a.out_norms) a.out_norms[i] = (float)n;
   }

@@ -1009,6 +1009,38 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
         F.flashdp_block_dp_grad(L, B, T, code, "scratch", torch.empty((least - 256,), dtype=torch.uint8, device=DEV))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("B,T,P,D,schedule,tile", [(3, 70, 1536, 1920, "scratch", 9), (5, 512, 1152, 1920, "scratch", 9), (2, 45, 2176, 2304, "scratch", 9), (12, 130, 768, 2432, "scratch", 9),
+                                                   (64, 16, 896, 1152, "auto", 7), (64, 16, 1024, 1152, "auto", 9), (64, 5, 1152, 1024, "auto", 9), (32, 16, 768, 3200, "auto", 9)])
+@pytest.mark.parametrize("operand,column,value", [("X", 0, "inf"), ("X", -1, "inf"), ("dY", 300, "inf"), ("dY", -1, "-inf"), ("X", 200, "nan"), ("dY", 7, "large")])
+def test_operands_that_are_not_finite_poison_on_small_tiles_what_they_poison_on_large_ones(B, T, P, D, schedule, tile, dtype, operand, column, value):
+    # a sample with an infinity beside the edge of a large tile has a norm of NaN, and all of the output with it; away from one an
+    # infinite norm and a factor of 0, as finite values whose squares overflow have.  Small tiles have fewer edges: sizes
+    # that are odd multiples of 128.  A sample that is finite keeps its norm.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P + D)
+    t = {"X": torch.randn((B, T, P), generator=g, device=DEV).to(dtype), "dY": torch.randn((B, T, D), generator=g, device=DEV).to(dtype)}
+    if value == "large":
+        t["dY"][B - 1] = 1e20 if dtype == torch.bfloat16 else 6e4
+        t["X"][B - 1] = 3e18 if dtype == torch.bfloat16 else 6e4
+    else:
+        t[operand][B - 1, T // 2, column] = float(value)
+    code = F.dtype_code(t["X"])
+    res = []
+    for how, forced in ((schedule, None), ("scratch", tile)):
+        out, norms = torch.full((D, P), 7.0, device=DEV), torch.full((B,), 7.0, device=DEV)
+        with env(FLASHDP_TILE=forced):
+            F.flashdp_block_dp_grad([dict(X=t["X"], dY=t["dY"], d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)], B, T, code, how)
+        torch.cuda.synchronize()
+        if forced is None:
+            assert F.flashdp_last_kernel() == "gemm_tile128_kernel" and F.flashdp_last_schedule() == ("twopass" if how == "auto" else "scratch")
+        res.append((out, norms))
+    (o, n), (ro, rn) = res
+    assert torch.equal(torch.isnan(n), torch.isnan(rn)) and torch.equal(torch.isinf(n), torch.isinf(rn))
+    assert torch.equal(torch.isfinite(o), torch.isfinite(ro))
+    assert bool(torch.all(torch.isfinite(n[:B - 1]))) and torch.allclose(n[:B - 1], rn[:B - 1], rtol=1e-4)
+
+
 @pytest.mark.parametrize("B,T,P,D", [(8, 64, 768, 16), (64, 100, 120, 120), (4, 100, 8, 2044), (16, 70, 96, 160)])
 def test_thin_fp32_layers_run_in_the_workspace_they_are_told_to_allocate(B, T, P, D):
     # the whole batch in the size that flashdp_workspace_bytes gives, k samples at a time in the chunked one; against fp64
