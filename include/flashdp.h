@@ -127,7 +127,7 @@ enum { FLASHDP_BF16 = 0, FLASHDP_F32 = 1, FLASHDP_F16 = 2 };
  *            outer products, G_i = dy_i x_i^T with n_i = |dy_i| |x_i|: AUTO takes norms and factors from the rows and
  *            forms the clipped sum as one product over the batch in any workspace that TWOPASS accepts ("rows").
  *            Short sequences of 16-bit inputs (d_in, d_out multiples of 8, two samples or more, and few enough tokens that
- *            computing G_i twice costs less than parking it: T up to about 250 for large layers) take TWOPASS on 128 x 128
+ *            computing G_i twice costs less than parking it: T up to about 320, 250 for operands beyond the caches) take TWOPASS on 128 x 128
  *            tiles, all layers of a call in shared launches, in a workspace of 4 B + 16 B ceil(d_out / 128)
  *            ceil(d_in / 128) bytes a layer; a larger one holds partial sums over parts of the batch where the layers
  *            alone do not fill the chip.  Which layers are together and how many parts there are decides the order
@@ -167,9 +167,9 @@ int flashdp_linear_dp_grad(const void* X, const void* dY, int64_t B, int64_t T, 
  * layers that park on 128 x 128 tiles (d_in and d_out multiples of 8, up to about 256 tiles of 256 x 256 over the batch)
  * share their launches, up to eight in a row, as far as the workspace holds them parked together: about the sum of
  * B * d_out * d_in * 2 bytes over them, where flashdp_workspace_bytes gives what the largest layer needs (with the norm partials of
- * small tiles; a few KB less, what the larger tiles' partials take, is accepted and keeps such a layer on those).  A larger
- * workspace makes such calls faster, never different (same bits; a GPT-2 block at B = 1, T = 1024: 46 us with 9 MB, 56 before
- * its layers were parted by their tiles).  The library-owned workspace takes that size (64 MB at most) when it has to grow anyway, and is not grown for it:
+ * small tiles; a few KB less, what the larger tiles' partials take, is accepted and keeps such a layer on those, whose norm partials
+ * are added up in another order).  From that size up a larger workspace makes such calls faster, never different (same bits; a
+ * GPT-2 block at B = 1, T = 1024: 46 us with 9 MB, 41 with 14 MB).  The library-owned workspace takes that size (64 MB at most) when it has to grow anyway, and is not grown for it:
  * after calls of other sizes a process may be left with the smaller groups.  With workspace == NULL the library-owned
  * workspace is used as above (sized for the schedule asked for).  Calls that share a workspace must be
  * ordered on one stream; the library-owned workspace is one per device, so this holds for all calls on a
@@ -306,8 +306,10 @@ int flashdp_release(void);
 const char* flashdp_last_schedule(void);
 
 /* Name of the contraction kernel the last layer enqueued on this thread took (the per-sample pass of Algorithm 1):
- * "gemm_mfma_dma_kernel" (16-bit inputs, tiles loaded straight into LDS), "gemm_mfma_kernel" (16-bit, register-staged,
- * small shapes), "gemm_mfma_f32_kernel" (fp32 inputs), "rows_accum_kernel" (T = 1, AUTO), "gemm_simple_kernel" (any shape); "none" before any call. */
+ * "gemm_mfma_dma16_kernel", "gemm_mfma_dma_kernel", "gemm_mfma_dma_shaped_kernel" (16-bit inputs, large tiles loaded straight into LDS),
+ * "gemm_tile128_kernel" (16-bit, 128 x 128 tiles), "gemm_mfma_kernel" (16-bit, register-staged, odd sizes), "gemm_f32x3_kernel" and
+ * "gemm_mfma_f32_kernel" (fp32 inputs), "tiny_dp_kernel" (tiny fp32 layers), "rows_accum_kernel" (T = 1, AUTO), "gemm_simple_kernel" (any
+ * shape); "none" before any call. */
 const char* flashdp_last_kernel(void);
 
 const char* flashdp_status_string(int status);

@@ -303,8 +303,10 @@ const char* path_kernel_name(Path p) {
 // not below the 128 tokens it was measured from.  Rows that are no multiple of 128 bytes: the 256 bytes that a small tile takes of
 // a row lie in three lines instead of two, where a large tile's 512 lie in five instead of four: a round takes 2.0 us + 7.0 ns a token
 // (fitted to 460 contractions; a call, large and small: left to large ones so: 1480 x 1000, B = 64, T = 256: 125, 140; 1000 x 1000, B = 64, T = 200:
-// 89, 98; 1288 x 1288, B = 24, T = 2048: 205, 217; small: 1032 x 1928, B = 8, T = 512: 48, 39; 2000 x 2000, B = 5, T = 333: 48, 39).  by_far: enough to give up the overlapped schedule as well, which the
-// small tiles do not have (layers of one round park and are summed in shared launches instead).
+// 89, 98; 1288 x 1288, B = 24, T = 2048: 205, 217; small: 1032 x 1928, B = 8, T = 512: 48, 39; 2000 x 2000, B = 5, T = 333: 48, 39).
+// by_far: enough to give up the overlapped schedule as well, which the small tiles do not have (layers of one round park and
+// are summed in shared launches instead; overlapped and so: 2 of 768 x 3072, B = 4, T = 330: 80, 37; 2048 x 2048 and 4096 x 4096, B = 2,
+// T = 1024: 183, 122).
 struct Park { bool small, by_far; int tiles_m, tiles_n; int edges; };
 // Where the plan's own tiles, larger than 128 x 128, reach beyond the layer (any_not_finite).
 int large_edges(const Plan& p, int64_t P, int64_t D) {
@@ -314,9 +316,10 @@ Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dt
   Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128), large_edges(p, P, D)};
   if (p.any || env().tile != 0) return k;
   if (dtype == FLASHDP_F32) {
-    // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for layers of one small
-    // tile and few tokens, which are all launch and latency (36 x 40, B = 4, T = 16: 8.0 us, 8.6), and T < 16, where its
-    // error can be the larger one (see there).
+    // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for T < 16, where its error
+    // can be the larger one (see there), and fewer than 32 tokens of layers below 128 x 128 elements, thin ones among them, which
+    // the generic kernel takes otherwise (us a call, generic and so: 36 x 40, B = 4, T = 16: 8.0, 8.6; T = 32: 8 x 1024, B = 64: 36, 22;
+    // 24 x 640, B = 64: 36, 23; 4 x 4000, B = 8: 15, 13, B = 64: 49, 41; level at 16 x 1000, B = 8 to 40: 13.3, 13.5 and 19.7, 19.5).
     k.small = P % 4 == 0 && D % 4 == 0 && (T + 96) * std::max(P, D) * 4 < (int64_t(1) << 31) && T >= (p.path == PATH_F32 ? 16 : 32);
     return k;
   }
@@ -420,6 +423,7 @@ hipError_t launch_gemm_dt(const Plan& p, const GemmArgs& args, hipStream_t st) {
   if constexpr (DT != DT_F32) {
     switch (MODE == MODE_ACCUM ? p.accum_path : p.path) {
       case PATH_256x8: return launch_mfma<Cfg256x8, MODE, DT>(a, st);
+      // (aligned rows park on this tiling only where FLASHDP_TILE asks for it: park_plan)
       case PATH_128x4: return p.any ? launch_mfma<Cfg128x4, MODE, DT, true>(a, st) : launch_mfma<Cfg128x4, MODE, DT>(a, st);
       case PATH_256x8k32: return p.any ? launch_mfma<Cfg256x8k32, MODE, DT, true>(a, st) : launch_mfma<Cfg256x8k32, MODE, DT>(a, st);
       case PATH_DMA: return launch_tiled<CfgDma>(gemm_mfma_dma_kernel<CfgDma, MODE, DT>, MODE, a, st, /*lockstep=*/true);
@@ -682,13 +686,12 @@ hipError_t launch_park128(const Tile128Args& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Layers of one call that share their two launches (scratch schedule): those on the 128 x 128 kernel, which by make_plan's
-// rule have too few tiles to fill the chip with large ones, as many in a row as the workspace holds parked together.
+// Layers of one call that share their two launches (scratch schedule): those that park on 128 x 128 tiles (park_plan), whether they have
+// too few large tiles to fill the chip or shorter rounds on small ones, as many in a row as the workspace holds parked together.
 // Same kernels' code on the same tiles: results are bit-identical to one launch per layer.
-// Such layers are bound by the length of one workgroup's reduction and by launches, so sharing them helps at every size
-// the path takes (bf16, together against one after the other: a GPT-2 block at B = 1, T = 1024, 37 us, 83 before, 56 when
-// the workspace holds three of the four; at B = 3, 83, 112; two layers of 2048 x 2048, T = 2048, 64, 75; eight of
-// 128 x 128, T = 1024, 19, 136).
+// Launches are saved and rounds filled up, which helps at every size that parks so (bf16, a call, together and one after the
+// other: a GPT-2 block, B = 1, T = 1024: 41 us, 67; B = 4, T = 512: 69, 85; B = 12, T = 330: 134, 151; six layers of 512 x 512, T = 330, B = 1: 27, 62,
+// B = 32: 106, 150; four of 1024 x 1024, B = 24, T = 512: 174, 190).
 Park park_of(const flashdp_layer_t& L, int64_t B, int64_t T, int dtype) {
   return park_plan(make_plan(B, T, L.d_in, L.d_out, dtype), B, T, L.d_in, L.d_out, dtype);
 }

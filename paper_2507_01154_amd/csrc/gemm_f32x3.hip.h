@@ -16,9 +16,9 @@
 // (largest element 5.96e-8, 1.5e-7, 5.97e-8); one token a thousand times the others, T = 2048: 8.1e-7, 5.1e-7, 2.9e-7; T = 16: 7.2e-8,
 // 5.0e-8, 5.6e-8; T = 8: 5.1e-8, 5.1e-8, 5.4e-8; T = 4: 3.6e-8, 4.2e-8, 4.5e-8: below 16 tokens the fp32 instructions keep the layer.
 //
-// fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 2158, 1702 (162 TFLOP/s; six products 1402);
-// 768 x 3072, B = 4, T = 1024: 251, 161; 64 x 448, B = 14, T = 1024: 236, 64; 128 x 13184, B = 1, T = 276: 76, 24; 1028 x 764, B = 8, T = 333:
-// 95, 44.
+// fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 2163, 1621 (170 TFLOP/s; six products 1402);
+// 768 x 3072, B = 4, T = 1024: 248, 166; 64 x 448, B = 14, T = 1024: 237, 65; 128 x 13184, B = 1, T = 276: 76, 24; 1028 x 764, B = 8, T = 333:
+// 93, 44.  The large ones are limited by power: a first call after a pause takes 1.7 to 2.0 ms where calls in a row take 1.6.
 //
 // Operands are scaled by 2^24 on their way into the parts and the sums by 2^-48 on their way out, both exact, so that the last part
 // of the smallest float is a normal number and no product of parts is subnormal unless the product itself vanishes.

@@ -98,7 +98,7 @@ FLASHDP_HD float bits_float(uint32_t u) {
 }
 
 // -2 ln u for u = (2k+1) / 2^25, k = r >> 8 (the 24-bit uniform with the half-step offset).
-// u is written as 2^(e-25) * (1+f) with 1+f in [0.75, 1.5]: f = (n - 2^e) / 2^e is an exact
+// u is written as 2^(e-25) * (1+f) with 1+f from just below 0.75 (n = 3 * 2^23 - 1, which rounds up) to 1.5: f = (n - 2^e) / 2^e is an exact
 // fp32 number because |n - 2^e| <= 2^24, so there is no rounding before the logarithm and no
 // cancellation as u -> 1 (there e = 25 and the result is -2 log1p(f) alone).  e is read off n as a rounded float:
 // its exponent, one more from 1.5 * 2^exponent up.

@@ -3,8 +3,9 @@
 // Such a call is all launches and latency (32 x 32, B = 4, T = 16: contraction 5.0 us, clip factors 1.7, aggregation 3.2, and the gaps
 // between them).  A wave forms its sample's gradient on v_mfma_f32_32x32x2 straight from memory - all loads of 16 tokens
 // in flight at once, no staging -, takes its norm and factor, and leaves the gradient in LDS, where the workgroup then sums
-// the samples in order and adds the noise as the streaming kernel would.  A call, before and so, us: 32 x 32, B = 4, T = 16: 11.8, 7.5;
-// B = 16: 14.3, 8.1; 64 x 64, B = 4, T = 16: 12.1, 7.8, T = 64: 17.6, 12.8; 30 x 34, B = 16, T = 64: 21.5, 20.1.
+// the samples in order and adds the noise as the streaming kernel would.  32 x 32, B = 4, T = 16, calls back to back, before and so, us:
+// 10.2, 4.9 (the kernel 5.0).  One by one from Python, which takes 7 of them itself: 11.8, 7.5; B = 16: 14.3, 8.1; 64 x 64, B = 4, T = 16:
+// 12.1, 7.8, T = 64: 17.6, 12.8; 30 x 34, B = 16, T = 64: 21.5, 20.1.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
