@@ -93,15 +93,15 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
 // An operand that is not finite meets the zeros beyond the edge of a 256 x 256 (384 x 192) tile, and the norm is NaN, which poisons
 // the output.  Where that edge is not one of a 128 x 128 tile, the norm would be infinite instead and the factor 0.  Which
 // tiles a layer takes must not decide that, so a norm that is infinite has its operands looked through: whether any of
-// rows x 8 chunks elements, a row every `pitch` elements, is not finite (by the calling thread's share of them).
-template <int DT>
-__device__ __forceinline__ bool any_not_finite(const void* p, int64_t rows, int chunks, int64_t pitch) {
+// rows x 8 chunks elements, a row every `pitch` elements, is not finite (the share of thread `me` of N, in rows of N_CHUNKS chunks).
+template <int DT, int N, int N_CHUNKS>
+__device__ __forceinline__ bool any_not_finite(const unsigned short* p, int64_t rows, int chunks, int64_t pitch, int me) {
   constexpr uint32_t EXP = DT == DT_BF16 ? 0x7F807F80u : 0x7C007C00u;
   bool found = false;
-  for (int c = threadIdx.x & 15; c < chunks; c += 16)
+  for (int c = me % N_CHUNKS; c < chunks; c += N_CHUNKS)
 #pragma unroll 4
-    for (int64_t r = threadIdx.x >> 4; r < rows; r += 16) {
-      const u32x4_t v = *(const u32x4_t*)((const unsigned short*)p + r * pitch + 8 * c);
+    for (int64_t r = me / N_CHUNKS; r < rows; r += N / N_CHUNKS) {
+      const u32x4_t v = *(const u32x4_t*)(p + r * pitch + 8 * c);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         found |= (v[q] & EXP & 0xFFFFu) == (EXP & 0xFFFFu) || (v[q] & EXP & 0xFFFF0000u) == (EXP & 0xFFFF0000u);
@@ -310,17 +310,17 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
         ss = fmaf(r0, r0, ss); ss = fmaf(r1, r1, ss); ss = fmaf(r2, r2, ss); ss = fmaf(r3, r3, ss);
         *(uint2*)(st + (i * 16) * EP + j * 16) = v;
       }
-    const float w = wave_sum_to_lane63(ss);
+    float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_to_lane63(ss)), 63));
+    if (__builtin_expect(w == __builtin_inff(), 0)) {   // of this wave's 64 x 64 elements
+      const int m = m0 + 64 * wave_m, n = n0 + 64 * wave_n;
+      bool found = false;
+      if (a.edges & 1) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.X + (size_t)s_begin * a.T * a.P + n, a.T, min(8, (a.P - n) / 8), a.P, lane);
+      if (a.edges & 2) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.dY + (size_t)s_begin * a.T * a.D + m, a.T, min(8, (a.D - m) / 8), a.D, lane);
+      if (__any(found)) w = __builtin_nanf("");
+    }
     if (lane == 63) red[wave] = w;
     __syncthreads();
-    float part = (red[0] + red[1]) + (red[2] + red[3]);
-    if (a.edges != 0 && part == __builtin_inff()) {
-      bool found = false;
-      if (a.edges & 1) found |= any_not_finite<DT>((const unsigned short*)a.X + (size_t)s_begin * a.T * a.P + n0, a.T, min(16, (a.P - n0) / 8), a.P);
-      if (a.edges & 2) found |= any_not_finite<DT>((const unsigned short*)a.dY + (size_t)s_begin * a.T * a.D + m0, a.T, min(16, (a.D - m0) / 8), a.D);
-      if (__syncthreads_or(found)) part = __builtin_nanf("");
-    }
-    if (tid == 0) a.partials[(size_t)s_begin * tiles + tile] = part;
+    if (tid == 0) a.partials[(size_t)s_begin * tiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
     unsigned short* const sc = (unsigned short*)a.scratch + (size_t)s_begin * a.D * a.P;
 #pragma unroll
     for (int it = 0; it < 8; ++it) {
@@ -393,8 +393,8 @@ __global__ __launch_bounds__(256) void tile128_clip_kernel(const Tile128ClipArgs
   double n = sqrt((red[0] + red[1]) + (red[2] + red[3]));
   if (a.edges != 0 && n == __builtin_inf()) {
     bool found = false;
-    if (a.edges & 1) found |= any_not_finite<DT>((const unsigned short*)a.X + (size_t)i * g.T * a.P, g.T, a.P / 8, a.P);
-    if (a.edges & 2) found |= any_not_finite<DT>((const unsigned short*)a.dY + (size_t)i * g.T * a.D, g.T, a.D / 8, a.D);
+    if (a.edges & 1) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.X + (size_t)i * g.T * a.P, g.T, a.P / 8, a.P, tid);
+    if (a.edges & 2) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.dY + (size_t)i * g.T * a.D, g.T, a.D / 8, a.D, tid);
     if (__syncthreads_or(found)) n = __builtin_nan("");
   }
   if (tid == 0) {
