@@ -308,12 +308,13 @@ const char* path_kernel_name(Path p) {
 // are summed in shared launches instead; overlapped and so: 2 of 768 x 3072, B = 4, T = 330: 80, 37; 2048 x 2048 and 4096 x 4096, B = 2,
 // T = 1024: 183, 122).
 struct Park { bool small, by_far; int tiles_m, tiles_n; int edges; };
-// Where the plan's own tiles, larger than 128 x 128, reach beyond the layer (any_not_finite).
-int large_edges(const Plan& p, int64_t P, int64_t D) {
-  return (p.bm > 128 && D % p.bm != 0 ? 1 : 0) | (p.bn > 128 && P % p.bn != 0 ? 2 : 0);
+// Where the plan's own tiles, larger than 128 x 128, reach beyond the layer, and where only 128 x 128 ones do.
+int plan_edges(const Plan& p, int64_t P, int64_t D) {
+  return (p.bm > 128 && D % p.bm != 0 ? EDGE_LARGE_D : 0) | (p.bn > 128 && P % p.bn != 0 ? EDGE_LARGE_P : 0) |
+         (D % p.bm == 0 && D % 128 != 0 ? EDGE_ONLY_D : 0) | (P % p.bn == 0 && P % 128 != 0 ? EDGE_ONLY_P : 0);
 }
 Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dtype) {
-  Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128), large_edges(p, P, D)};
+  Park k{false, false, (int)((D + 127) / 128), (int)((P + 127) / 128), plan_edges(p, P, D)};
   if (p.any || env().tile != 0) return k;
   if (dtype == FLASHDP_F32) {
     // Split into bfloat16 parts (gemm_f32x3.hip.h) at all sizes with rows of whole 16-byte accesses, but for T < 16, where its error
@@ -904,7 +905,7 @@ hipError_t run_short(const flashdp_layer_t* layers, int n, int splits, int64_t B
     Tile128Layer& a = norm.layer[l];
     a.X = L.X; a.dY = L.dY; a.B = (int)B; a.T = (int)T; a.P = (int)L.d_in; a.D = (int)L.d_out;
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n;
-    a.edges = large_edges(make_plan(B, T, L.d_in, L.d_out, dtype), L.d_in, L.d_out);
+    a.edges = plan_edges(make_plan(B, T, L.d_in, L.d_out, dtype), L.d_in, L.d_out);
     a.splits = (int)norm_splits;
     a.partials = partials; a.scratch = nullptr; a.factors = factors; a.out = nullptr;
     a.noise_scale = noise_scale; a.accumulate = accumulate ? 1 : 0; a.seed = L.seed; a.layer = L.layer;

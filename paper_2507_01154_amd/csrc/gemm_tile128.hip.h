@@ -32,12 +32,18 @@
 
 namespace flashdp {
 
+// What the tiles that a layer is planned on have at its edges and 128 x 128 tiles have not, or the other way round: an operand that
+// is not finite and meets the zeros beyond an edge makes the norm NaN, which poisons the output, where it would be infinite
+// otherwise and the factor 0.  Which tiles a layer takes must not decide that.
+enum { EDGE_LARGE_D = 1, EDGE_LARGE_P = 2,   // larger tiles reach beyond D, beyond P (any_not_finite)
+       EDGE_ONLY_D = 4, EDGE_ONLY_P = 8 };   // 128 x 128 tiles reach beyond D, P and the plan's do not (odd multiples of 64; wave_outside)
+
 struct Tile128Layer {
   const void* X;         // [B][T][P]
   const void* dY;        // [B][T][D]
   int B, T, P, D;
   int tiles_m, tiles_n;  // ceil(D / 128), ceil(P / 128)
-  int edges;             // bits: the layer's large tiles reach beyond D (1), beyond P (2); see any_not_finite
+  int edges;             // EDGE_ bits
   int splits;            // workgroups per tile: split r walks over samples [B r / splits, B (r + 1) / splits)
   float* partials;       // squared-norm partial sums: [B][tiles_m * tiles_n][4], one per wave (NORM); [B][tiles_m * tiles_n] (SPILL)
   void* scratch;         // [B][D][P] bfloat16 (SPILL)
@@ -90,9 +96,13 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
   return v;
 }
 
-// An operand that is not finite meets the zeros beyond the edge of a 256 x 256 (384 x 192) tile, and the norm is NaN, which poisons
-// the output.  Where that edge is not one of a 128 x 128 tile, the norm would be infinite instead and the factor 0.  Which
-// tiles a layer takes must not decide that, so a norm that is infinite has its operands looked through: whether any of
+// EDGE_ONLY_D, EDGE_ONLY_P: whether all of a wave's 64 x 64 elements from (m, n) on lie beyond such an edge, where its squares do not
+// count.  (They are zero unless an operand is not finite.)
+__device__ __forceinline__ bool wave_outside(int edges, int m, int n, int D, int P) {
+  return ((edges & EDGE_ONLY_D) && m >= D) || ((edges & EDGE_ONLY_P) && n >= P);
+}
+
+// EDGE_LARGE_D, EDGE_LARGE_P: a norm that is infinite has its operands looked through: whether any of
 // rows x 8 chunks elements, a row every `pitch` elements, is not finite (the share of thread `me` of N, in rows of N_CHUNKS chunks).
 template <int DT, int N, int N_CHUNKS>
 __device__ __forceinline__ bool any_not_finite(const unsigned short* p, int64_t rows, int chunks, int64_t pitch, int me) {
@@ -193,6 +203,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
       for (int j = 0; j < 4; ++j) tot[i][j] = zero4;
   }
 
+  const bool outside = wave_outside(a.edges, m0 + 64 * wave_m, n0 + 64 * wave_n, a.D, a.P);
+
   // End of a sample: its squared norm is noted (NORM), or its clipped gradient joins the total (ACCUM).  Totals of their own,
   // so that no sample's products are added to a large sum one by one and a clip factor of 0 is harmless.  Lane q holds the
   // sum of this wave's squares resp. the clip factor of sample s_base + q, so that memory is met once in 64 samples: a store
@@ -221,7 +233,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
 #pragma unroll
           for (int e = 0; e < 4; ++e) ss[e] = fmaf(acc[i][j][e], acc[i][j][e], ss[e]);
       const float w = wave_sum_to_lane63((ss[0] + ss[1]) + (ss[2] + ss[3]));
-      const float sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), 63));
+      const float sum = outside ? 0.0f : __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), 63));
       per_lane = lane == s - s_base ? sum : per_lane;
     } else if constexpr (MODE == MODE_ACCUM) {
       if (in_step) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -311,11 +323,12 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
         *(uint2*)(st + (i * 16) * EP + j * 16) = v;
       }
     float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_to_lane63(ss)), 63));
+    if (outside) w = 0.0f;
     if (__builtin_expect(w == __builtin_inff(), 0)) {   // of this wave's 64 x 64 elements
       const int m = m0 + 64 * wave_m, n = n0 + 64 * wave_n;
       bool found = false;
-      if (a.edges & 1) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.X + (size_t)s_begin * a.T * a.P + n, a.T, min(8, (a.P - n) / 8), a.P, lane);
-      if (a.edges & 2) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.dY + (size_t)s_begin * a.T * a.D + m, a.T, min(8, (a.D - m) / 8), a.D, lane);
+      if (a.edges & EDGE_LARGE_D) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.X + (size_t)s_begin * a.T * a.P + n, a.T, min(8, (a.P - n) / 8), a.P, lane);
+      if (a.edges & EDGE_LARGE_P) found |= any_not_finite<DT, 64, 8>((const unsigned short*)a.dY + (size_t)s_begin * a.T * a.D + m, a.T, min(8, (a.D - m) / 8), a.D, lane);
       if (__any(found)) w = __builtin_nanf("");
     }
     if (lane == 63) red[wave] = w;
@@ -391,10 +404,10 @@ __global__ __launch_bounds__(256) void tile128_clip_kernel(const Tile128ClipArgs
   if ((tid & 63) == 0) red[tid >> 6] = s;
   __syncthreads();
   double n = sqrt((red[0] + red[1]) + (red[2] + red[3]));
-  if (a.edges != 0 && n == __builtin_inf()) {
+  if ((a.edges & (EDGE_LARGE_D | EDGE_LARGE_P)) && n == __builtin_inf()) {
     bool found = false;
-    if (a.edges & 1) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.X + (size_t)i * g.T * a.P, g.T, a.P / 8, a.P, tid);
-    if (a.edges & 2) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.dY + (size_t)i * g.T * a.D, g.T, a.D / 8, a.D, tid);
+    if (a.edges & EDGE_LARGE_D) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.X + (size_t)i * g.T * a.P, g.T, a.P / 8, a.P, tid);
+    if (a.edges & EDGE_LARGE_P) found |= any_not_finite<DT, 256, 16>((const unsigned short*)a.dY + (size_t)i * g.T * a.D, g.T, a.D / 8, a.D, tid);
     if (__syncthreads_or(found)) n = __builtin_nan("");
   }
   if (tid == 0) {

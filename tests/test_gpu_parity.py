@@ -1011,12 +1011,14 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,T,P,D,schedule,tile", [(3, 70, 1536, 1920, "scratch", 9), (5, 512, 1152, 1920, "scratch", 9), (2, 45, 2176, 2304, "scratch", 9), (12, 130, 768, 2432, "scratch", 9),
-                                                   (64, 16, 896, 1152, "auto", 7), (64, 16, 1024, 1152, "auto", 9), (64, 5, 1152, 1024, "auto", 9), (32, 16, 768, 3200, "auto", 9)])
+                                                   (64, 16, 896, 1152, "auto", 7), (64, 16, 1024, 1152, "auto", 9), (64, 5, 1152, 1024, "auto", 9), (32, 16, 768, 3200, "auto", 9),
+                                                   (16, 333, 576, 1344, "scratch", 7), (13, 40, 960, 1152, "scratch", 7), (25, 333, 1024, 576, "scratch", 8),
+                                                   (28, 16, 576, 1152, "auto", 7), (14, 16, 1920, 576, "auto", 8), (25, 65, 576, 2048, "auto", 7)])
 @pytest.mark.parametrize("operand,column,value", [("X", 0, "inf"), ("X", -1, "inf"), ("dY", 300, "inf"), ("dY", -1, "-inf"), ("X", 200, "nan"), ("dY", 7, "large")])
 def test_operands_that_are_not_finite_poison_on_small_tiles_what_they_poison_on_large_ones(B, T, P, D, schedule, tile, dtype, operand, column, value):
     # a sample with an infinity beside the edge of a large tile has a norm of NaN, and all of the output with it; away from one an
-    # infinite norm and a factor of 0, as finite values whose squares overflow have.  Small tiles have fewer edges: sizes
-    # that are odd multiples of 128.  A sample that is finite keeps its norm.
+    # infinite norm and a factor of 0, as finite values whose squares overflow have.  Small tiles have fewer edges (sizes
+    # that are odd multiples of 128) or more (odd multiples of 192, on 384 x 192 tiles).  A sample that is finite keeps its norm.
     g = torch.Generator(device=DEV)
     g.manual_seed(P + D)
     t = {"X": torch.randn((B, T, P), generator=g, device=DEV).to(dtype), "dY": torch.randn((B, T, D), generator=g, device=DEV).to(dtype)}
