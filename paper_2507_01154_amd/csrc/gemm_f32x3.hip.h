@@ -203,9 +203,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    // an operand that is not finite meets the zeros beyond a ragged edge of the 256 x 256 tiles that the fp32 matrix instructions
-    // work on, which makes the norm NaN: likewise
-    const bool edge_d = D % 256 != 0 && tm == a.tiles_m - 1, edge_p = P % 256 != 0 && tn == a.tiles_n - 1;
+    // an operand that is not finite meets the zeros beyond a ragged edge of the tiles that the layer is planned on, 256 x 256 for the
+    // fp32 matrix instructions and 64 x 64 for the generic kernel, which makes the norm NaN: likewise (EDGE_ bits)
+    const bool edge_d = (a.edges & EDGE_LARGE_D) && tm == a.tiles_m - 1, edge_p = (a.edges & EDGE_LARGE_P) && tn == a.tiles_n - 1;
     float ragged = 0.0f;
 #pragma unroll 1
     for (int t = 0; t < T; ++t) {
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
           for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(y[i], x[j][e], acc[i][j][e]);
       }
     }
-    ss = square_sum() + ragged;
+    ss = wave_outside(a.edges, m0 + 64 * wave_m, n0 + 64 * wave_n, D, P) ? 0.0f : square_sum() + ragged;
   }
   float* const red = (float*)lds + 64 * F32x3Cfg::OUT_PITCH;
   const float w = wave_sum_to_lane63(ss);

@@ -1043,6 +1043,29 @@ def test_operands_that_are_not_finite_poison_on_small_tiles_what_they_poison_on_
     assert bool(torch.all(torch.isfinite(n[:B - 1]))) and torch.allclose(n[:B - 1], rn[:B - 1], rtol=1e-4)
 
 
+@pytest.mark.parametrize("B,T,P,D", [(3, 40, 64, 128), (2, 33, 192, 64), (5, 32, 64, 240), (2, 100, 252, 64), (2, 50, 8, 1024), (3, 64, 128, 124)])
+@pytest.mark.parametrize("operand,column", [("X", 0), ("X", -1), ("dY", 0), ("dY", -1)])
+def test_infinities_in_thin_fp32_layers_poison_what_they_poison_on_64_by_64_tiles(B, T, P, D, operand, column):
+    # layers planned on the generic kernel's tiles that park on 128 x 128 ones, split into bfloat16 parts: a dimension of an odd multiple
+    # of 64 has no edge there that an infinity could meet zeros beyond
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P + D)
+    t = {"X": torch.randn((B, T, P), generator=g, device=DEV), "dY": torch.randn((B, T, D), generator=g, device=DEV)}
+    t[operand][B - 1, T // 2, column] = float("inf")
+    res = []
+    for tile in (None, -1):
+        out, norms = torch.full((D, P), 7.0, device=DEV), torch.full((B,), 7.0, device=DEV)
+        with env(FLASHDP_TILE=tile):
+            F.flashdp_block_dp_grad([dict(X=t["X"], dY=t["dY"], d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out, out_norms=norms)], B, T, F.F32, "scratch")
+        torch.cuda.synchronize()
+        assert F.flashdp_last_kernel() == ("gemm_simple_kernel" if tile else "gemm_f32x3_kernel")
+        res.append((out, norms))
+    (o, n), (ro, rn) = res
+    assert torch.equal(torch.isnan(n), torch.isnan(rn)) and torch.equal(torch.isinf(n), torch.isinf(rn))
+    assert torch.equal(torch.isfinite(o), torch.isfinite(ro))
+    assert torch.allclose(n[:B - 1], rn[:B - 1], rtol=1e-6)
+
+
 @pytest.mark.parametrize("B,T,P,D", [(8, 64, 768, 16), (64, 100, 120, 120), (4, 100, 8, 2044), (16, 70, 96, 160)])
 def test_thin_fp32_layers_run_in_the_workspace_they_are_told_to_allocate(B, T, P, D):
     # the whole batch in the size that flashdp_workspace_bytes gives, k samples at a time in the chunked one; against fp64
