@@ -674,16 +674,16 @@ Tile128Layer park128(const flashdp_layer_t& L, const Park& p, int64_t B, int64_t
   a.factors = nullptr; a.out = nullptr; a.noise_scale = 0.0f; a.accumulate = 0; a.seed = 0; a.layer = 0;
   return a;
 }
-template <int DT>
-hipError_t launch_park128(const Tile128Args& g, hipStream_t st) {
-  void (*kern)(Tile128Args);
+template <int DT, typename Args>
+hipError_t launch_park128(const Args& g, unsigned grid, hipStream_t st) {
+  void (*kern)(Args);
   int lds_bytes;
   if constexpr (DT == DT_F32) { kern = gemm_f32x3_kernel; lds_bytes = F32x3Cfg::LDS_BYTES; }
-  else { kern = gemm_tile128_kernel<MODE_SPILL, DT>; lds_bytes = Tile128Cfg::LDS_BYTES; }
+  else { kern = gemm_tile128_kernel<MODE_SPILL, DT, Args>; lds_bytes = Tile128Cfg::LDS_BYTES; }
   static_assert(F32x3Cfg::NT == Tile128Cfg::NT, "one launch shape");
   hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.first[g.n]), dim3(Tile128Cfg::NT), lds_bytes, st, g);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(Tile128Cfg::NT), lds_bytes, st, g);
   return hipGetLastError();
 }
 
@@ -801,7 +801,7 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
     g.first[l + 1] = g.first[l] + (int)align_up((size_t)q.tiles * B, 8);   // a few hundred each by the path's rule
     t.first[l + 1] = t.first[l] + (int)((q.S / 8 + 255) / 256);
   }
-  hipError_t e = launch_park128<DT>(g, st);
+  hipError_t e = launch_park128<DT>(g, (unsigned)g.first[n], st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((clip_aggregate16_grouped_kernel<DT_BF16>), dim3((unsigned)t.first[n]), dim3(256), 0, st, t);
   g_ctx.last_kernel = "gemm_tile128_kernel";
@@ -1042,12 +1042,9 @@ int run_layer(const flashdp_layer_t& L0, int64_t B, int64_t T, int dtype, int mo
   } else if (use_scratch) {
     if (small) g_ctx.last_kernel = dtype == FLASHDP_F32 ? "gemm_f32x3_kernel" : "gemm_tile128_kernel";
     if ((stages & FLASHDP_STAGE_CONTRACT) && small) {
-      Tile128Args g;
-      g.n = 1;
-      g.first[0] = 0;
-      g.first[1] = (int)align_up((size_t)tiles * B, 8);
-      g.layer[0] = park128(L, park, B, T, a.partials, a.scratch);
-      HIP_TRY(dtype == FLASHDP_BF16 ? launch_park128<DT_BF16>(g, st) : dtype == FLASHDP_F16 ? launch_park128<DT_F16>(g, st) : launch_park128<DT_F32>(g, st));
+      const Tile128Layer g = park128(L, park, B, T, a.partials, a.scratch);
+      const unsigned grid = (unsigned)align_up((size_t)tiles * B, 8);
+      HIP_TRY(dtype == FLASHDP_BF16 ? launch_park128<DT_BF16>(g, grid, st) : dtype == FLASHDP_F16 ? launch_park128<DT_F16>(g, grid, st) : launch_park128<DT_F32>(g, grid, st));
     } else if (stages & FLASHDP_STAGE_CONTRACT) {
       HIP_TRY(launch_gemm<MODE_SPILL>(plan, dtype, a, st));
     }

@@ -60,7 +60,7 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t* parts) {
 }
 
 // a.scratch: [B][D][P] fp32; a.partials: [B][tiles]; a.splits == B (one workgroup per tile and sample).
-__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g) {
+__global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Layer a) {
   namespace tp = tile128_plan;
   constexpr int PART = F32x3Cfg::PART;
   extern __shared__ __attribute__((aligned(16))) unsigned short lds[];   // parts 1..3 of the dY tile, then of the X tile
@@ -68,12 +68,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32x3_kernel(const Tile128Args g)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = wave >> 1;
 
-  const int l = group_of(g.first, g.n, blockIdx.x);
-  const Tile128Layer& a = g.layer[l];
-  const int bid = (int)blockIdx.x - g.first[l];
   const int tiles = a.tiles_m * a.tiles_n, total = tiles * a.splits;
-  if (bid >= total) return;   // the whole workgroup, before any barrier
-  const int item = xcd_remap(bid, total);
+  if ((int)blockIdx.x >= total) return;   // the whole workgroup, before any barrier
+  const int item = xcd_remap(blockIdx.x, total);
   const int sample = item / tiles, tile = item - sample * tiles;
   int tm, tn;
   tile_coords<8>(tile, a.tiles_m, a.tiles_n, &tm, &tn);

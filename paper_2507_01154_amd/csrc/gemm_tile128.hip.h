@@ -60,6 +60,19 @@ struct Tile128Args {
   Tile128Layer layer[GROUP_MAX];
 };
 
+// The layer that this workgroup belongs to, and which of the layer's workgroups it is.  A layer by itself is passed by
+// itself (parking pass): eight layers' arguments are a kilobyte, which the host takes 0.6 us longer to hand over, and small calls in
+// a row are bound by the host (16 x 648, f16, B = 1, T = 8: 11.8 us a call, 11.2 so; 768 x 768, bf16, B = 1, T = 1024: 15.2, 14.6).
+__device__ __forceinline__ const Tile128Layer& layer_of(const Tile128Layer& a, int* bid) {
+  *bid = blockIdx.x;
+  return a;
+}
+__device__ __forceinline__ const Tile128Layer& layer_of(const Tile128Args& g, int* bid) {
+  const int l = group_of(g.first, g.n, blockIdx.x);
+  *bid = (int)blockIdx.x - g.first[l];
+  return g.layer[l];
+}
+
 struct Tile128Cfg {
   static constexpr int NT = 256;
   static constexpr int LDS_BYTES = 2 * tile128_plan::STAGES * tile128_plan::OPERAND_ELEMS * 2;   // 64 KB
@@ -119,8 +132,8 @@ __device__ __forceinline__ bool any_not_finite(const unsigned short* p, int64_t 
   return found;
 }
 
-template <int MODE, int DT>
-__global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args g) {
+template <int MODE, int DT, typename Args = Tile128Args>
+__global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Args g) {
   static_assert(MODE == MODE_NORM || MODE == MODE_ACCUM || MODE == MODE_SPILL, "the passes this tiling has");
   namespace tp = tile128_plan;
   constexpr int STAGES = tp::STAGES;
@@ -129,9 +142,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tile128_kernel(const Tile128Args 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = wave >> 1;
 
-  const int l = group_of(g.first, g.n, blockIdx.x);
-  const Tile128Layer& a = g.layer[l];
-  const int bid = (int)blockIdx.x - g.first[l];
+  int bid;
+  const Tile128Layer& a = layer_of(g, &bid);
   const int tiles = a.tiles_m * a.tiles_n, total = tiles * a.splits;
   if (bid >= total) return;   // the whole workgroup, before any barrier
   const int item = xcd_remap(bid, total);
