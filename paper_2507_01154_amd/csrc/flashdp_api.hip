@@ -304,6 +304,11 @@ const char* path_kernel_name(Path p) {
 // a row lie in three lines instead of two, where a large tile's 512 lie in five instead of four: a round takes 2.0 us + 7.0 ns a token
 // (fitted to 460 contractions; a call, large and small: left to large ones so: 1480 x 1000, B = 64, T = 256: 125, 140; 1000 x 1000, B = 64, T = 200:
 // 89, 98; 1288 x 1288, B = 24, T = 2048: 205, 217; small: 1032 x 1928, B = 8, T = 512: 48, 39; 2000 x 2000, B = 5, T = 333: 48, 39).
+// All that holds for operands that the caches still hold from the call before.  The small tiles wait longer for operands that come from
+// memory: 0.08 us per MB in the balance of both (303 contractions; a call on large and small tiles, operands in the caches, then
+// from memory: left to large ones so: 3072 x 768, B = 58, T = 512: 219, 214 and 230, 264; 384 x 4352, B = 10, T = 1566: 68, 67 and 69, 81;
+// 3768 x 184, B = 11, T = 1891: 54, 55 and 57, 77; 2048 x 2048, B = 29, T = 484: 197, 183 and 208, 205; a GPT-2 block, B = 64, T = 330:
+// 727, 771; small: 464 x 2800, B = 7, T = 412: 29, 25 and 28, 29; 1400 x 3128, B = 4, T = 395: 53, 41 and 55, 44).
 // by_far: enough to give up the overlapped schedule as well, which the small tiles do not have (layers of one round park and
 // are summed in shared launches instead; overlapped and so: 2 of 768 x 3072, B = 4, T = 330: 80, 37; 2048 x 2048 and 4096 x 4096, B = 2,
 // T = 1024: 183, 122).
@@ -329,11 +334,11 @@ Park park_plan(const Plan& p, int64_t B, int64_t T, int64_t P, int64_t D, int dt
     const int64_t cus = plan_cus();
     const int64_t rounds = ((int64_t)p.tiles_m * p.tiles_n * B + cus - 1) / cus, rounds128 = ((int64_t)k.tiles_m * k.tiles_n * B + cus - 1) / cus;
     const bool lines = P % 64 == 0 && D % 64 == 0;
+    const double operands = (double)B * T * (P + D) * 2.0 / (1 << 20);   // MB
     const double large = 2.0 + rounds * (8.5 + (p.path == PATH_DMA16 ? 0.0212 : 0.0272) * T);
-    const double small = 3.0 + rounds128 * (lines ? 1.4 + 0.0062 * T : 2.0 + 0.007 * T);
+    const double small = 3.0 + rounds128 * (lines ? 1.4 + 0.0062 * T : 2.0 + 0.007 * T) + 0.08 * operands;
     const double margin = lines ? (rounds == 1 ? 0.95 : 0.9) : (rounds == 1 ? 0.97 : 0.93);
-    const bool cached = B * T * (P + D) * 2 <= (int64_t(256) << 20);
-    k.small = cached && small < margin * large && (rounds == 1 || T >= 128);
+    k.small = operands <= 256.0 && small < margin * large && (rounds == 1 || T >= 128);
     k.by_far = k.small && (rounds == 1 || small < 0.8 * large);
   }
   return k;

@@ -117,6 +117,20 @@ def test_workspace_sizes_suffice_for_the_tiles_a_call_asks_room_for(dtype):
             assert F.flashdp_workspace_bytes_chunked(L, B, T, code, k, slots) >= slots * least(k), (B, T, P, D, k)
 
 
+@pytest.mark.parametrize("B,T,P,D,small", [
+    (10, 1566, 384, 4352, False), (25, 1279, 1408, 384, False), (58, 512, 3072, 768, False),
+    (11, 1891, 3768, 184, False), (13, 716, 4224, 512, False), (64, 330, 768, 3072, False),
+    (7, 412, 2800, 464, True), (4, 1024, 768, 3072, True), (5, 333, 1032, 1928, True)])
+def test_operands_that_come_from_memory_count_in_the_choice_of_small_tiles(B, T, P, D, small):
+    # host logic only: small tiles would be the faster ones for all of these with operands in the caches, and are the slower ones
+    # for the first six with operands that come from memory.  Read off the room for norm partials.
+    up = lambda n: (n + 255) // 256 * 256
+    size = lambda bm, bn: up(4 * B) + up(4 * B * -(-D // bm) * -(-P // bn)) + up(2 * B * P * D)
+    L = [dict(X=None, dY=None, d_in=P, d_out=D, C=1.0, sigma=1.0, seed=0, layer=0, out_grad=None)]
+    got = F.flashdp_workspace_bytes(L, B, T, F.BF16, "scratch")
+    assert got == size(128, 128) if small else got < size(128, 128)
+
+
 def test_tile_shape_follows_the_rounds_of_equally_long_work_items(monkeypatch):
     # host logic only, read off the number of norm partials (B x tiles floats, rounded up to 256 bytes) in the two-pass
     # workspace.  Without a device 256 compute units are assumed.

@@ -980,7 +980,7 @@ def test_short_sequences_give_the_same_bits_whatever_the_library_workspace_holds
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("B,T,P,D", [(16, 97, 768, 760), (5, 333, 1032, 1928), (3, 40, 1480, 2056), (3, 2100, 1096, 2312), (12, 130, 1288, 1288)])
+@pytest.mark.parametrize("B,T,P,D", [(16, 97, 768, 760), (5, 333, 1032, 1928), (3, 40, 1480, 2056), (3, 2100, 1032, 2056), (12, 130, 1288, 1288)])
 def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype):
     # layers of enough 256 x 256 tiles for the large-tile kernel that park on 128 x 128 ones; a workspace with room for no
     # more norm partials than the large tiles have is still accepted, and takes those.  Tolerances of parked tiles.
@@ -1012,7 +1012,7 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("B,T,P,D,schedule,tile", [(3, 70, 1536, 1920, "scratch", 9), (5, 512, 1152, 1920, "scratch", 9), (2, 45, 2176, 2304, "scratch", 9), (12, 130, 768, 2432, "scratch", 9),
                                                    (64, 16, 896, 1152, "auto", 7), (64, 16, 1024, 1152, "auto", 9), (64, 5, 1152, 1024, "auto", 9), (32, 16, 768, 3200, "auto", 9),
-                                                   (16, 333, 576, 1344, "scratch", 7), (13, 40, 960, 1152, "scratch", 7), (25, 333, 1024, 576, "scratch", 8),
+                                                   (16, 333, 576, 1344, "scratch", 7), (13, 40, 960, 1152, "scratch", 7), (13, 200, 1408, 1728, "scratch", 8),
                                                    (28, 16, 576, 1152, "auto", 7), (14, 16, 1920, 576, "auto", 8), (25, 65, 576, 2048, "auto", 7)])
 @pytest.mark.parametrize("operand,column,value", [("X", 0, "inf"), ("X", -1, "inf"), ("dY", 300, "inf"), ("dY", -1, "-inf"), ("X", 200, "nan"), ("dY", 7, "large")])
 def test_operands_that_are_not_finite_poison_on_small_tiles_what_they_poison_on_large_ones(B, T, P, D, schedule, tile, dtype, operand, column, value):
