@@ -308,7 +308,7 @@ const char* path_kernel_name(Path p) {
 // memory: 0.08 us per MB in the balance of both (303 contractions; a call on large and small tiles, operands in the caches, then
 // from memory: left to large ones so: 3072 x 768, B = 58, T = 512: 219, 214 and 230, 264; 384 x 4352, B = 10, T = 1566: 68, 67 and 69, 81;
 // 3768 x 184, B = 11, T = 1891: 54, 55 and 57, 77; 2048 x 2048, B = 29, T = 484: 197, 183 and 208, 205; a GPT-2 block, B = 64, T = 330:
-// 727, 771; small: 464 x 2800, B = 7, T = 412: 29, 25 and 28, 29; 1400 x 3128, B = 4, T = 395: 53, 41 and 55, 44).
+// 727, 771; small: 1400 x 3128, B = 4, T = 395: 53, 41 and 55, 44; 544 x 2712, B = 13, T = 197: 37, 33 and 39, 39).
 // by_far: enough to give up the overlapped schedule as well, which the small tiles do not have (layers of one round park and
 // are summed in shared launches instead; overlapped and so: 2 of 768 x 3072, B = 4, T = 330: 80, 37; 2048 x 2048 and 4096 x 4096, B = 2,
 // T = 1024: 183, 122).
