@@ -851,7 +851,10 @@ bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dt
   }
   const int64_t slots = 2 * plan_cus();
   const bool far = operands > 256.0 && 2 * tiles >= slots && operands * ((tiles + slots - 1) / slots) > 620.0;
-  double gain = -9.0;
+  // Few tiles and few k-tiles: one workgroup per tile walks over all samples (short_group), 0.15 us each while the rest of the chip waits
+  // (fitted to 638 calls; parked and two passes: 1152 x 640, B = 20, T = 5: 18, 27; 2304 x 256, B = 27, T = 11: 25, 35; 144 x 2944, B = 47, T = 16: 45, 59).
+  const bool alone = std::min(slots / std::max<int64_t>(tiles, 1), B * ((T + 31) / 32) / 24) < 2;
+  double gain = -9.0 - (alone ? 0.15 * B * std::max(0.0, 1.0 - (double)tiles / slots) : 0.0);
   for (int l = 0; l < n; ++l) {
     const int64_t P = layers[l].d_in, D = layers[l].d_out;
     if (P % 8 != 0 || D % 8 != 0 || (T + 320) * std::max(P, D) * 2 >= (int64_t(1) << 31)) return false;

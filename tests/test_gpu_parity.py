@@ -920,6 +920,23 @@ def test_short_sequences_take_two_passes_on_small_tiles(B, T, dims, dtype):
         assert float((got - 2 * o).abs().max()) <= 1e-6 * 2 * float(o.abs().max()) + 3 * 2.0 ** -24 * (3 * L["C"] + 2 * float(o.abs().max()))
 
 
+@pytest.mark.parametrize("B,T,P,D,how", [(20, 5, 1152, 640, "scratch"), (27, 11, 2304, 256, "scratch"), (47, 16, 144, 2944, "scratch"), (16, 5, 896, 1088, "scratch"),
+                                         (25, 65, 576, 2048, "twopass"), (48, 16, 768, 896, "twopass")])
+def test_short_sequences_of_few_tiles_that_one_workgroup_each_would_walk_over_are_parked(B, T, P, D, how):
+    # the rule, and either way's result against fp64: parked tiles are rounded to bfloat16 (2^-9 each), the rest is fp32
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B * P)
+    X, dY = torch.randn((B, T, P), generator=g, device=DEV).bfloat16(), torch.randn((B, T, D), generator=g, device=DEV).bfloat16()
+    G = torch.matmul(dY.double().transpose(1, 2).contiguous(), X.double())
+    want = (G / torch.clamp(G.flatten(1).norm(dim=1), min=1.0)[:, None, None]).sum(0)
+    out = torch.empty((D, P), device=DEV)
+    L = [dict(X=X, dY=dY, d_in=P, d_out=D, C=1.0, sigma=0.0, seed=1, layer=0, out_grad=out)]
+    F.flashdp_block_dp_grad(L, B, T, F.BF16, "auto", torch.empty((F.flashdp_workspace_bytes(L, B, T, F.BF16, "auto"),), dtype=torch.uint8, device=DEV))
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert F.flashdp_last_schedule() == how
+    assert float((out - want).norm() / want.norm()) <= 4e-3
+
+
 @pytest.mark.parametrize("B,T,P,D", [(1600, 5, 256, 128), (2000, 65, 128, 248), (300, 40, 256, 256)])
 def test_short_sequences_of_many_samples_on_few_tiles(B, T, P, D):
     # more partial sums than layers that fill the chip have (up to 64), and the sample ends with a wait (T > 64) and without; with
@@ -1013,7 +1030,7 @@ def test_parking_on_small_tiles_where_their_rounds_are_shorter(B, T, P, D, dtype
 @pytest.mark.parametrize("B,T,P,D,schedule,tile", [(3, 70, 1536, 1920, "scratch", 9), (5, 512, 1152, 1920, "scratch", 9), (2, 45, 2176, 2304, "scratch", 9), (12, 130, 768, 2432, "scratch", 9),
                                                    (64, 16, 896, 1152, "auto", 7), (64, 16, 1024, 1152, "auto", 9), (64, 5, 1152, 1024, "auto", 9), (32, 16, 768, 3200, "auto", 9),
                                                    (16, 333, 576, 1344, "scratch", 7), (13, 40, 960, 1152, "scratch", 7), (13, 200, 1408, 1728, "scratch", 8),
-                                                   (28, 16, 576, 1152, "auto", 7), (14, 16, 1920, 576, "auto", 8), (25, 65, 576, 2048, "auto", 7)])
+                                                   (25, 16, 960, 1408, "auto", 7), (25, 16, 1472, 960, "auto", 8), (25, 65, 576, 2048, "auto", 7)])
 @pytest.mark.parametrize("operand,column,value", [("X", 0, "inf"), ("X", -1, "inf"), ("dY", 300, "inf"), ("dY", -1, "-inf"), ("X", 200, "nan"), ("dY", 7, "large")])
 def test_operands_that_are_not_finite_poison_on_small_tiles_what_they_poison_on_large_ones(B, T, P, D, schedule, tile, dtype, operand, column, value):
     # a sample with an infinity beside the edge of a large tile has a norm of NaN, and all of the output with it; away from one an
