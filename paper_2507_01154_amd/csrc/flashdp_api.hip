@@ -816,7 +816,8 @@ hipError_t run_group(const flashdp_layer_t* layers, int n, int64_t B, int64_t T,
 // Short sequences (gemm_tile128.hip.h): AUTO takes the two-pass schedule on 128 x 128 tiles, all layers of the call in its
 // three or four launches, where that is the faster way.  Parking costs about 0.68 us per million elements and sample (2 + 2
 // bytes), the second contraction 0.05 us + 1.95 ns a token of the padded tiles, and the launches 9 us (fitted to 170 calls;
-// in a band of some 20 tokens about the limit the way taken may be a few per cent the slower one).  bf16, a call, parked and so, in us: a GPT-2 block, B = 64: T = 16:
+// in a band of some 20 tokens about the limit the way taken may be a few per cent the slower one, or 20 where tiles are a little more than a
+// round of the chip: 2944 x 3264, B = 4, T = 190: 56, 66).  bf16, a call, parked and so, in us: a GPT-2 block, B = 64: T = 16:
 // 466, 105; T = 128: 490, 266; T = 256: 633, 553; B = 4, T = 128: 67, 44; 4096 x 4096, B = 64: T = 16: 892, 190; T = 64: 911, 300;
 // 5120 x 13824, B = 4, T = 16: 290, 170; 264 x 6000, B = 64, T = 16: 131, 70; left to parking: 768 x 768, B = 16, T = 64: 22, 25;
 // 1024 x 3072, B = 64, T = 256: 223, 226; one sample (4096 x 4096, T = 64: 39, 41).
@@ -852,7 +853,7 @@ bool short_ok(const flashdp_layer_t* layers, int n, int64_t B, int64_t T, int dt
   const int64_t slots = 2 * plan_cus();
   const bool far = operands > 256.0 && 2 * tiles >= slots && operands * ((tiles + slots - 1) / slots) > 620.0;
   // Few tiles and few k-tiles: one workgroup per tile walks over all samples (short_group), 0.15 us each while the rest of the chip waits
-  // (fitted to 638 calls; parked and two passes: 1152 x 640, B = 20, T = 5: 18, 27; 2304 x 256, B = 27, T = 11: 25, 35; 144 x 2944, B = 47, T = 16: 45, 59).
+  // (fitted to 638 calls; parked and two passes: 1152 x 640, B = 20, T = 5: 21, 31; 2304 x 256, B = 27, T = 11: 25, 35; 144 x 2944, B = 47, T = 16: 45, 59).
   const bool alone = std::min(slots / std::max<int64_t>(tiles, 1), B * ((T + 31) / 32) / 24) < 2;
   double gain = -9.0 - (alone ? 0.15 * B * std::max(0.0, 1.0 - (double)tiles / slots) : 0.0);
   for (int l = 0; l < n; ++l) {

@@ -15,6 +15,9 @@
 // 8.1e-7, 7.0e-7, 2.7e-7; T = 333: 3.3e-7, 2.7e-7, 1.0e-7; T = 16: 7.4e-8, 3.4e-8, 3.2e-8; one token alone: 2.54e-8, 3.4e-8, 2.54e-8
 // (largest element 5.96e-8, 1.5e-7, 5.97e-8); one token a thousand times the others, T = 2048: 8.1e-7, 5.1e-7, 2.9e-7; T = 16: 7.2e-8,
 // 5.0e-8, 5.6e-8; T = 8: 5.1e-8, 5.1e-8, 5.4e-8; T = 4: 3.6e-8, 4.2e-8, 4.5e-8: below 16 tokens the fp32 instructions keep the layer.
+// Larger than theirs, at about one rounding of fp32: a dominating token that comes last (products a hundred times the others' and more, any T: 2.5e-8,
+// 4.5e-8 to 6.4e-8; they round it once, a matrix instruction of 32 tokens cuts the small products off beside it), and softmax-shaped values
+// in both operands up to T = 33 (T = 16: 3.9e-8, 5.5e-8; T = 33: 6.4e-8, 6.6e-8; T = 100: 1.14e-7, 8.9e-8).
 //
 // fp32, contraction in us, on the fp32 matrix instructions and so: 4096 x 4096, B = 4, T = 2048: 2163, 1621 (170 TFLOP/s; six products 1402);
 // 768 x 3072, B = 4, T = 1024: 248, 166; 64 x 448, B = 14, T = 1024: 237, 65; 128 x 13184, B = 1, T = 276: 76, 24; 1028 x 764, B = 8, T = 333:
